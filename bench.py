@@ -405,7 +405,7 @@ def tile_timing(steps, warmup, copy_ref=False):
     launch_s = e0.elapsed_time(e1) / 1e3 / steps
     bytes_per_launch = 4 * C * N * T + 8 * T          # criteria read once, best + score written
     achieved = bytes_per_launch / launch_s / 1e9
-    roof = {"bound": "hbm", "kernel": "k_topsis_tiles_wave<4,4>", "achieved": achieved,
+    roof = {"bound": "hbm", "kernel": "k_topsis_tiles_reg<4,4,4,1>", "achieved": achieved,
             "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": tile_traffic(),
             "avg_launch_us": launch_s * 1e6, "bytes_per_launch": bytes_per_launch}
     del x

@@ -327,12 +327,12 @@ int dc_last_timing(dc_ctx *ctx, float *ms, int64_t *launches, int64_t *steps);
  * T >= 2^31, C outside 1..DC_MAX_CRIT, N outside 1..2^20, a null x, best or
  * weight, or a weight that is not positive; DC_ENOMEM when the large-tile
  * path's partials cannot be allocated; DC_EDEVICE when the launch fails.
- * 16-byte aligned x and scores and N % 4 == 0 with a tile a wavefront's
- * registers hold take the fast path (one wavefront per tile); up to 1,024
- * tiles of at least 4,096 servers are split into slices of 2,048 servers
- * over several workgroups, with partials in device memory allocated on the
- * stream for the call (stream-ordered) and freed behind it; other shapes
- * take one workgroup per tile. */
+ * Tiles that fit the registers of one, four or sixteen wavefronts (up to
+ * 32,768 servers at C <= 2, 16,384 at C <= 4, 8,192 beyond) are read once,
+ * with 16-byte loads where x and scores are 16-byte aligned and N % 4 == 0.
+ * Larger tiles take one workgroup each or, from 1 MiB on, several, with
+ * partials in device memory allocated on the stream for the call
+ * (stream-ordered) and freed behind it. */
 int dc_topsis_tiles(int64_t T, int32_t C, int32_t N, const int32_t *x, const uint8_t *feasible,
                     const int32_t *cost, const float *weight, float *scores, int32_t *best, float *best_score,
                     void *stream);
@@ -347,7 +347,7 @@ int dc_topsis_tiles(int64_t T, int32_t C, int32_t N, const int32_t *x, const uin
  * library's code object): make one call, T = 0 will do, before capture.
  * A call whose large-tile partials need more than 4 MiB returns DC_ETOOBIG
  * (about T * ceil(N / 2048) * (16 C + 8) bytes: 1,024 tiles of 27,648
- * servers at C = 8 fit; other shapes use no scratch and have no limit).
+ * servers at C = 8 fit; other shapes have no limit).
  * Every call on one device shares its array: calls that overlap on one
  * device (several streams, several host threads) race and must be
  * serialised by the caller.  The caller passes and owns all inputs and

@@ -1127,13 +1127,22 @@ void cache_write(const char *path, const std::string &key, const Shape &sh, floa
 
 namespace {
 
-// Which kernels score a set of tiles: one wavefront per tile (matrices a
-// wavefront's registers hold), slices of one tile over several workgroups
-// with partials in scratch (few large tiles), or one workgroup per tile.
-enum { TILE_WAVE = 0, TILE_SPLIT = 1, TILE_GEN = 2 };
+// Which kernels score a set of tiles.
+//   REG    a tile in the registers of one, four or sixteen wavefronts;
+//   BIG    one workgroup per tile, reading it twice;
+//   SPLIT  slices over several workgroups, statistics and scores in two
+//          launches with partials in scratch.
+enum { TILE_REG = 0, TILE_BIG = 1, TILE_SPLIT = 2 };
 struct TilePath {
-    int kind = TILE_GEN, C = 0, V = 0;
+    int kind = TILE_BIG, C = 0, V = 0, W = 1, NW = 1;
+    size_t scratch = 0;     // device bytes the launches need
+    size_t refuse = 0;      // dc_topsis_tiles_noalloc: refused when above its static buffer
 };
+
+// Up to 1 MiB of criteria one workgroup per tile, beyond it (few tiles) the
+// split: a 27,648 x 4 tile alone took 31-35 us over seven workgroups behind
+// an allocation and a select launch, 17.7 us with one workgroup (41 us split).
+constexpr long long kBigTileInts = 1 << 18;
 
 int tiles_prepare(int64_t T, int32_t C, int32_t N, const int32_t *x, const uint8_t *feasible, const int32_t *cost,
                   const float *weight, float *scores, int32_t *best, float *best_score, TileArgs *a, TilePath *path) {
@@ -1155,71 +1164,115 @@ int tiles_prepare(int64_t T, int32_t C, int32_t N, const int32_t *x, const uint8
     }
     auto al = [](const void *p, uintptr_t m) { return (reinterpret_cast<uintptr_t>(p) & (m - 1)) == 0; };
     const bool vec = N % 4 == 0 && al(x, 16) && (!scores || al(scores, 16)) && (!feasible || al(feasible, 4));
-    // four-server groups per lane when one wavefront holds the tile
-    const int V = (N + 4 * kWave - 1) / (4 * kWave);
-    const int Vp = V <= 1 ? 1 : V <= 2 ? 2 : V <= 4 ? 4 : V <= 8 ? 8 : 16;   // 16: too large
     path->C = C;
-    path->V = Vp;
-    if (vec && Vp <= 8 && C * Vp <= 16) path->kind = TILE_WAVE;
-    else if (N >= 2 * kSplitSlice && T <= kSplitMaxTiles) path->kind = TILE_SPLIT;
-    else path->kind = TILE_GEN;
+    path->W = vec ? 4 : 1;
+    // fewest wavefronts whose registers hold the tile: 4V servers per thread
+    // and criterion, V a power of two with C * V <= 16 (V <= 8)
+    const int vmax = C <= 2 ? 8 : C <= 4 ? 4 : 2;
+    int nw = 0, v = 0;
+    for (int w : {1, 4, 16}) {
+        v = 1;
+        while (v < vmax && 256 * v * w < N) v *= 2;
+        if (256 * v * w >= N) { nw = w; break; }
+    }
+    // the scratch of the two-launch split, which the calls of its range are
+    // measured by against the static buffer whichever kernels they take
+    const bool in_regs1 = vec && nw == 1;
+    const bool splits = !in_regs1 && N >= 2 * kSplitSlice && T <= kSplitMaxTiles;
+    path->refuse = splits ? split_scratch_bytes(T, N, C) : 0;
+    if (nw) {
+        path->kind = TILE_REG;
+        path->V = v;
+        path->NW = nw;
+    } else if ((long long)C * N <= kBigTileInts || !splits) {
+        path->kind = TILE_BIG;
+    } else {
+        path->kind = TILE_SPLIT;
+        path->scratch = path->refuse;
+    }
     return DC_OK;
 }
 
-// work: split_scratch_bytes(T, N, C) device bytes for the split path
-// (unused otherwise).
-int tiles_launch(const TileArgs &a, int64_t T, const TilePath &path, void *work, hipStream_t st) {
-    if (path.kind == TILE_WAVE) {
+template <int C, int V, int W>
+int launch_tiles_reg(const TileArgs &a, int64_t T, int NW, hipStream_t st) {
+    if (NW == 1) {
         // persistent grid: as many workgroups as fit on the device at once,
         // never more than needed for one wavefront per tile
-        int dev = 0, cus = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-            return DC_EDEVICE;
-        const dim3 block(kTileBlock);
-        auto pgrid = [&](const void *k) {
-            int per = 0;
-            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k, kTileBlock, 0) != hipSuccess || per < 1) per = 1;
-            const long long need = (T + kTileWaves - 1) / kTileWaves;
-            return dim3(static_cast<unsigned>(std::min<long long>(need, (long long)per * cus)));
-        };
-#define DCS_TILES_LAUNCH(CC, VV)                                                                         \
-    hipLaunchKernelGGL((k_topsis_tiles_wave<CC, VV>),                                                    \
-                       pgrid(reinterpret_cast<const void *>(k_topsis_tiles_wave<CC, VV>)), block, 0, st, a, (long long)T)
-        switch (path.C * 100 + path.V) {
-        case 101: DCS_TILES_LAUNCH(1, 1); break;
-        case 102: DCS_TILES_LAUNCH(1, 2); break;
-        case 104: DCS_TILES_LAUNCH(1, 4); break;
-        case 108: DCS_TILES_LAUNCH(1, 8); break;
-        case 201: DCS_TILES_LAUNCH(2, 1); break;
-        case 202: DCS_TILES_LAUNCH(2, 2); break;
-        case 204: DCS_TILES_LAUNCH(2, 4); break;
-        case 208: DCS_TILES_LAUNCH(2, 8); break;
-        case 301: DCS_TILES_LAUNCH(3, 1); break;
-        case 302: DCS_TILES_LAUNCH(3, 2); break;
-        case 304: DCS_TILES_LAUNCH(3, 4); break;
-        case 401: DCS_TILES_LAUNCH(4, 1); break;
-        case 402: DCS_TILES_LAUNCH(4, 2); break;
-        case 404: DCS_TILES_LAUNCH(4, 4); break;
-        case 501: DCS_TILES_LAUNCH(5, 1); break;
-        case 502: DCS_TILES_LAUNCH(5, 2); break;
-        case 601: DCS_TILES_LAUNCH(6, 1); break;
-        case 602: DCS_TILES_LAUNCH(6, 2); break;
-        case 701: DCS_TILES_LAUNCH(7, 1); break;
-        case 702: DCS_TILES_LAUNCH(7, 2); break;
-        case 801: DCS_TILES_LAUNCH(8, 1); break;
-        case 802: DCS_TILES_LAUNCH(8, 2); break;
-        default: return DC_EINVAL;          // unreachable: V <= 8, C * V <= 16
+        long long blocks = (T + kTileWaves - 1) / kTileWaves;
+        if (blocks > 256) {
+            int dev = 0, cus = 0, per = 0;
+            if (hipGetDevice(&dev) != hipSuccess ||
+                hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+                return DC_EDEVICE;
+            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                    &per, reinterpret_cast<const void *>(k_topsis_tiles_reg<C, V, W, 1>), kTileBlock, 0) != hipSuccess ||
+                per < 1)
+                per = 1;
+            blocks = std::min<long long>(blocks, (long long)per * cus);
         }
-#undef DCS_TILES_LAUNCH
-    } else if (path.kind == TILE_SPLIT) {
+        hipLaunchKernelGGL((k_topsis_tiles_reg<C, V, W, 1>), dim3((unsigned)blocks), dim3(kTileBlock), 0, st, a,
+                           (long long)T);
+        return DC_OK;
+    }
+    // four wavefronts take what one cannot hold, sixteen what four cannot;
+    // a workgroup per tile, within the launch's limit on threads
+    const dim3 grid((unsigned)std::min<int64_t>(T, 1 << 20));
+    constexpr int vmax = C <= 2 ? 8 : C <= 4 ? 4 : 2;
+    if constexpr (4 * V > vmax)
+        if (NW == 4)
+            hipLaunchKernelGGL((k_topsis_tiles_reg<C, V, W, 4>), grid, dim3(4 * kWave), 0, st, a,
+                               (long long)T);
+    if constexpr (4 * V > vmax)
+        if (NW == 16)
+            hipLaunchKernelGGL((k_topsis_tiles_reg<C, V, W, 16>), grid, dim3(16 * kWave), 0, st, a,
+                               (long long)T);
+    return DC_OK;
+}
+
+template <int C, int W>
+int launch_tiles_reg_v(const TileArgs &a, int64_t T, const TilePath &p, hipStream_t st) {
+    switch (p.V) {
+    case 1: return launch_tiles_reg<C, 1, W>(a, T, p.NW, st);
+    case 2: return launch_tiles_reg<C, 2, W>(a, T, p.NW, st);
+    case 4:
+        if constexpr (C <= 4) return launch_tiles_reg<C, 4, W>(a, T, p.NW, st);
+        break;
+    case 8:
+        if constexpr (C <= 2) return launch_tiles_reg<C, 8, W>(a, T, p.NW, st);
+        break;
+    }
+    return DC_EINVAL;       // unreachable: V <= vmax of its C
+}
+
+template <int W>
+int launch_tiles_reg_c(const TileArgs &a, int64_t T, const TilePath &p, hipStream_t st) {
+    switch (p.C) {
+    case 1: return launch_tiles_reg_v<1, W>(a, T, p, st);
+    case 2: return launch_tiles_reg_v<2, W>(a, T, p, st);
+    case 3: return launch_tiles_reg_v<3, W>(a, T, p, st);
+    case 4: return launch_tiles_reg_v<4, W>(a, T, p, st);
+    case 5: return launch_tiles_reg_v<5, W>(a, T, p, st);
+    case 6: return launch_tiles_reg_v<6, W>(a, T, p, st);
+    case 7: return launch_tiles_reg_v<7, W>(a, T, p, st);
+    default: return launch_tiles_reg_v<8, W>(a, T, p, st);
+    }
+}
+
+// work: path.scratch device bytes (unused when 0).
+int tiles_launch(const TileArgs &a, int64_t T, const TilePath &path, void *work, hipStream_t st) {
+    if (path.kind == TILE_REG) {
+        const int rc = path.W == 4 ? launch_tiles_reg_c<4>(a, T, path, st) : launch_tiles_reg_c<1>(a, T, path, st);
+        if (rc) return rc;
+    } else if (path.kind == TILE_BIG) {
+        const dim3 grid(static_cast<unsigned>(T)), block(kBigTileBlock);
+        if (path.W == 4) hipLaunchKernelGGL(k_topsis_tiles_big<4>, grid, block, 0, st, a);
+        else hipLaunchKernelGGL(k_topsis_tiles_big<1>, grid, block, 0, st, a);
+    } else {
         const TileSplit sp = split_carve(work, T, a.N, a.C);
         const dim3 grid(static_cast<unsigned>(sp.S), static_cast<unsigned>(T));
         hipLaunchKernelGGL(k_tiles_split_stats, grid, dim3(kTileBlock), 0, st, a, sp);
         hipLaunchKernelGGL(k_tiles_split_score, grid, dim3(kTileBlock), 0, st, a, sp);
         hipLaunchKernelGGL(k_tiles_split_select, dim3(static_cast<unsigned>(T)), dim3(kWave), 0, st, a, sp);
-    } else {
-        hipLaunchKernelGGL(k_topsis_tiles_gen, dim3(static_cast<unsigned>(T)), dim3(kTileBlock), 0, st, a);
     }
     if (hipGetLastError() != hipSuccess) return DC_EDEVICE;
     return DC_OK;
@@ -1836,12 +1889,12 @@ int dc_topsis_tiles(int64_t T, int32_t C, int32_t N, const int32_t *x, const uin
     int rc = tiles_prepare(T, C, N, x, feasible, cost, weight, scores, best, best_score, &a, &path);
     if (rc || T == 0) return rc;
     const hipStream_t st = static_cast<hipStream_t>(stream);
-    if (path.kind != TILE_SPLIT) return tiles_launch(a, T, path, nullptr, st);
+    if (!path.scratch) return tiles_launch(a, T, path, nullptr, st);
     // the split path's partials: stream-ordered allocation, freed behind the
     // launches (or, where the device has no stream-ordered allocator,
     // allocated and freed around a synchronised launch)
     void *scr = nullptr;
-    const size_t bytes = split_scratch_bytes(T, N, C);
+    const size_t bytes = path.scratch;
     if (hipMallocAsync(&scr, bytes, st) == hipSuccess) {
         rc = tiles_launch(a, T, path, scr, st);
         if (hipFreeAsync(scr, st) != hipSuccess) return DC_EDEVICE;
@@ -1865,7 +1918,7 @@ int dc_topsis_tiles_noalloc(int64_t T, int32_t C, int32_t N, const int32_t *x, c
     void *work = nullptr;
     if ((rc = static_scratch(&work))) return rc;     // the first call on a device resolves the address
     if (T == 0) return DC_OK;
-    if (path.kind == TILE_SPLIT && split_scratch_bytes(T, N, C) > kStaticScratchBytes) return DC_ETOOBIG;
+    if (path.refuse > kStaticScratchBytes) return DC_ETOOBIG;
     return tiles_launch(a, T, path, work, static_cast<hipStream_t>(stream));
 }
 

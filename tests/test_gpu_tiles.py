@@ -165,3 +165,32 @@ def test_tiles_full_size_sampled():
         _check_tile(x[t], None, w, [0] * 4, None, best[t], bscore[t])
         ref = O.topsis(x[t].astype(np.float64), w, [0] * 4)
         assert abs(bscore[t] - ref[best[t]]) <= TOL * ref.max()
+
+
+EDGES = [
+    # T, C, N at the edges of the register paths: the most and least servers
+    # of one, four and sixteen wavefronts, odd counts (4-byte loads), and the
+    # first sizes beyond them (one workgroup per tile reading it twice, then the
+    # split behind a statistics launch)
+    (5, 2, 255), (3, 8, 512), (3, 5, 516), (4, 3, 1025), (3, 4, 1028), (3, 8, 2048), (3, 8, 2052), (2, 6, 4099),
+    (2, 8, 8192), (2, 8, 8196), (2, 4, 16384), (2, 4, 16386), (257, 4, 16640), (2, 1, 32768), (2, 1, 32769),
+    (2, 2, 131072), (1, 4, 65540),
+]
+
+
+@pytest.mark.parametrize("T,C,N", EDGES)
+def test_tiles_register_path_edges(T, C, N):
+    """Each edge against the oracle, and bit-identical to the same data at a
+    4-byte alignment (the other width of loads)."""
+    x, feas = make_tiles(seed=T * 31 + C * 7 + N, T=T, N=N, C=C, feasible_p=0.6)
+    w = np.arange(1, C + 1) / (C * (C + 1) / 2)
+    cost = [c % 3 == 1 for c in range(C)]
+    best, bscore, sc = _run(x, feas, w, cost)
+    for t in sorted({0, T // 2, T - 1}):
+        _check_tile(x[t], feas[t], w, cost, sc[t], best[t], bscore[t])
+    big = torch.zeros(T * C * N + 1, dtype=torch.int32, device="cuda")
+    big[1:] = _dev(x).reshape(-1)
+    b2, s2, sc2 = dc.topsis_tiles(big[1:].view(T, C, N), w, cost, _dev(feas), scores=True)
+    torch.cuda.synchronize()
+    assert np.array_equal(best, b2.cpu().numpy())
+    assert bscore.tobytes() == s2.cpu().numpy().tobytes() and sc.tobytes() == sc2.cpu().numpy().tobytes()
