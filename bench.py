@@ -259,11 +259,10 @@ def run_batch(args, wl, insts, reqs):
     if tune is not None:
         out["config"]["autotune"] = tune
     if wl["method"] == "topsis":
-        kname = ("k_topsis_batched" if mode == dc.DC_MODE_BATCHED else
-                 "k_topsis_grid" if args.grid == 2 else "k_topsis_plain")
+        kname = "k_topsis_grid" if mode == dc.DC_MODE_PLAIN and args.grid == 2 else "k_topsis_resident"
         bytes_per_launch = BYTES_PER_HOST_SCORE * hs / per_step_launches
         achieved = bytes_per_launch / avg_launch_s / 1e9
-        traffic = counter_traffic(BATCHED_TRAFFIC, shape) if kname == "k_topsis_batched" else None
+        traffic = counter_traffic(BATCHED_TRAFFIC, shape) if mode == dc.DC_MODE_BATCHED else None
         out["roofline"] = {"bound": "hbm", "kernel": kname, "achieved": achieved, "peak": HBM_PEAK_GBS,
                            "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
                            "avg_launch_us": avg_launch_s * 1e6, "launches_per_step": per_step_launches,

@@ -15,7 +15,9 @@ struct Params {
     int *xs;         // global per-server scratch [nc+6][N] of that instance
     int pc_cap;      // peers per path-table chunk
     int inst;
-    // batched form: state of instance i at state_base + i * state_stride
+    int xrows;       // resident kernel: rows of per-server scratch in LDS
+    int rq_pairs;    // and peer pairs of a request staged there at most
+    // resident kernel: state of instance i at state_base + i * state_stride
     int *state_base;
     long long state_stride;
     // AHP
@@ -77,7 +79,7 @@ __device__ __forceinline__ void stage_out(int *g, const int *lds, int n) {
 }
 
 // ---------------------------------------------------------------- plain form
-// The plain form passes the container's peer list in the kernel arguments,
+// A launch of one step passes the container's peer list in the kernel arguments,
 // so only the peers' servers are read from memory.
 //
 // The persistent kernels (batched, serving) read the Batch pointers from an
@@ -89,32 +91,14 @@ __device__ __forceinline__ ReqView plain_view(const Params &p) {
     return ReqView{p.pj, p.pbw, p.b.host + p.s.g0, nullptr, p.pbmax};
 }
 
-// One launch per container step, one workgroup.  With RES the instance's
-// state (6N int32) is staged into LDS for the step and written back, and
-// the criteria scratch lives in LDS too; otherwise both stay in HBM/L2.
-// K > 0: compiled for k = K fat-trees on the four default criteria (as the
-// batched kernel); K = 0: any.
-template <int BS, bool RES, int K = 0>
+// One launch per container step, one workgroup, for data centers whose
+// state and criteria do not fit the workgroup's LDS (both stay in HBM/L2).
+template <int BS>
 __global__ __launch_bounds__(BS) void k_topsis_plain(Params p) {
     extern __shared__ __align__(16) char dsm[];
     if (p.b.status[p.s.r] == 0) return;        // request already rejected
-    constexpr int CS = K ? 4 : 0;
-    const Topo t = topo_of<K>(p.t);
-    Smem sm = carve(dsm, p.pc_cap, t.nsw);
-    const ReqView rv = plain_view(p);
-    if (!RES) {
-        topsis_step<BS, host_group(BS), false, CS>(t, p.st, p.m, p.b, sm, p.xs, p.pc_cap, p.tr, p.inst, p.s, rv);
-        return;
-    }
-    const int N = t.N;
-    int *xs = lds_after_tables(dsm, p.pc_cap, t.nsw);
-    int *ls = xs + (size_t)xs_rows(crit_count<CS>(p.m)) * N;
-    stage_in<BS>(ls, p.st.cpu, 6 * N);        // the six arrays are contiguous
-    // (the barrier at the end of load_peers orders these writes before any read)
-    const State st{ls, ls + N, ls + 2 * N, ls + 3 * N, ls + 4 * N, ls + 5 * N};
-    topsis_step<BS, host_group(BS), true, CS>(t, st, p.m, p.b, sm, xs, p.pc_cap, p.tr, p.inst, p.s, rv);
-    __syncthreads();
-    stage_out<BS>(p.st.cpu, ls, 6 * N);
+    Smem sm = carve(dsm, p.pc_cap, p.t.nsw);
+    topsis_step<BS>(p.t, p.st, p.m, p.b, sm, p.xs, p.pc_cap, p.tr, p.inst, p.s, plain_view(p));
 }
 
 // AHP step, stage 1: criteria of every server into the global xs rows,
@@ -635,23 +619,41 @@ __global__ __launch_bounds__(BS) void k_ahp_select(Params p) {
 }
 
 // ---------------------------------------------------------------- batched form
-// LDS ints of the request prefetch of the batched form: hosts, cpu, ram
-// (kMaxN each), relative peer offsets (kMaxN + 4), peers, minimum and
-// maximum demands (kMaxPairs each), maximum cpu and ram (kMaxN each).
-__host__ __device__ inline size_t req_lds_ints() { return 6 * (size_t)kMaxN + 4 + 3 * (size_t)kMaxPairs; }
+// LDS ints of a request's header (servers, cpu, ram, relative peer offsets,
+// maximum cpu and ram) and of `pairs` of its peer pairs (peers, minimum and
+// maximum demands).
+constexpr int kReqHead = 6 * kMaxN + 4;
+__host__ __device__ inline size_t req_lds_ints(int pairs = kMaxPairs) { return kReqHead + 3 * (size_t)pairs; }
+
+// Dynamic LDS of the resident kernel: the step's region, the request
+// header, the state, `rows` rows of per-server scratch, then the pairs.
+inline size_t resident_lds_bytes(int pc, int nsw, int N, int rows, int pairs) {
+    return step_lds_bytes(pc, nsw, (size_t)rows * N, 6 * (size_t)N + req_lds_ints(pairs));
+}
 
 // One persistent workgroup per data-center instance: the instance's state,
 // the per-server scratch and the request being scheduled live in LDS for
 // the whole launch; the workgroup walks its requests in FCFS order and
-// their containers in index order.  Each thread scores G servers together
-// (the autotuner picks BS and G, and the peer chunk p.pc_cap).
+// their containers in index order.  Each thread scores G servers together.
+// The batched form runs it over its instances (the autotuner picks BS and
+// G, and the peer chunk p.pc_cap); the plain form runs it over a queue
+// wherever the state fits, p.xrows rows of scratch and p.rq_pairs staged
+// pairs (64 or more) sized for the queue; a request with more pairs has each
+// step's brought in as the step begins.  A step is a chain of LDS round trips and barriers, so
+// what counts is that nothing else sits between two steps: with one launch
+// per step instead, a queue of 500 requests at k = 16 took 44.4 ms, 5.2 us
+// per launch of the host's time, whether or not the request had been
+// rejected before; one launch takes 22 ms.
 // K > 0: the data centers are k = K fat-trees scored on the four default
 // criteria (CPU, RAM, active, path bandwidth; all benefits), so the
 // topology and the criterion list are compile-time constants: index
 // arithmetic becomes shifts and the per-criterion selection folds away.
 // Same arithmetic as K = 0 (any k and criteria), bit-identical results.
-template <int BS, int G, int K>
-__global__ __launch_bounds__(BS) void k_topsis_batched(Params p) {
+// QUEUE: the plain form, with p.xrows and p.rq_pairs; otherwise the batched
+// form's fixed layout (all rows, every pair), whose offsets are then
+// constants (as run-time values they cost its launches 1.3 %).
+template <int BS, int G, int K, bool QUEUE>
+__global__ __launch_bounds__(BS) void k_topsis_resident(Params p) {
     extern __shared__ __align__(16) char dsm[];
     const int inst = blockIdx.x;
     const Topo t = topo_of<K>(p.t);
@@ -659,12 +661,13 @@ __global__ __launch_bounds__(BS) void k_topsis_batched(Params p) {
     constexpr int CS = K ? 4 : 0;
     const int N = t.N;
     Smem sm = carve(dsm, p.pc_cap, t.nsw);
-    int *xs = lds_after_tables(dsm, p.pc_cap, t.nsw);
-    int *ls = xs + (size_t)xs_rows(crit_count<CS>(m)) * N;
-    int *rq_host = ls + 6 * (size_t)N;
+    int *rq_host = lds_after_tables(dsm, p.pc_cap, t.nsw);
     int *rq_cpu = rq_host + kMaxN, *rq_ram = rq_cpu + kMaxN, *rq_poff = rq_ram + kMaxN;
-    int *rq_pj = rq_poff + kMaxN + 4, *rq_pbw = rq_pj + kMaxPairs, *rq_pbmax = rq_pbw + kMaxPairs;
-    int *rq_cmax = rq_pbmax + kMaxPairs, *rq_rmax = rq_cmax + kMaxN;
+    int *rq_cmax = rq_poff + kMaxN + 4, *rq_rmax = rq_cmax + kMaxN;
+    int *ls = rq_host + kReqHead;
+    int *xs = ls + 6 * (size_t)N;
+    const int xrows = QUEUE ? p.xrows : xs_rows(crit_count<CS>(m)), rq_pairs = QUEUE ? p.rq_pairs : kMaxPairs;
+    int *rq_pj = xs + (size_t)xrows * N, *rq_pbw = rq_pj + rq_pairs, *rq_pbmax = rq_pbw + rq_pairs;
     const State gs = state_at(p.state_base, p.state_stride, inst, N);
     stage_in<BS>(ls, gs.cpu, 6 * N);
     const State st{ls, ls + N, ls + 2 * N, ls + 3 * N, ls + 4 * N, ls + 5 * N};
@@ -688,17 +691,26 @@ __global__ __launch_bounds__(BS) void k_topsis_batched(Params p) {
                 rq_host[x] = -1;
             }
         }
-        for (int x = threadIdx.x; x < npair; x += BS) {
-            rq_pj[x] = p.b.pj[pb + x];
-            rq_pbw[x] = p.b.pbw[pb + x];
-            rq_pbmax[x] = p.b.pbmax[pb + x];
-        }
+        const bool staged = !QUEUE || npair <= rq_pairs;
+        if (staged)
+            for (int x = threadIdx.x; x < npair; x += BS) {
+                rq_pj[x] = p.b.pj[pb + x];
+                rq_pbw[x] = p.b.pbw[pb + x];
+                rq_pbmax[x] = p.b.pbmax[pb + x];
+            }
         __syncthreads();
         for (int i = 0; i < n; ++i) {
-            const int q0 = rq_poff[i];
-            const StepIn s{r, i, n, g0, g0 + i, pb + q0, rq_poff[i + 1] - q0, rq_cpu[i], rq_ram[i],
-                           rq_cmax[i], rq_rmax[i]};
-            const ReqView rv{rq_pj + q0, rq_pbw + q0, rq_host, rq_host, rq_pbmax + q0, rq_poff, rq_pj};
+            const int q0 = rq_poff[i], P = rq_poff[i + 1] - q0, q = staged ? q0 : 0;
+            const StepIn s{r, i, n, g0, g0 + i, pb + q0, P, rq_cpu[i], rq_ram[i], rq_cmax[i], rq_rmax[i]};
+            if (!staged) {                     // only this step's pairs
+                for (int x = threadIdx.x; x < P; x += BS) {
+                    rq_pj[x] = p.b.pj[pb + q0 + x];
+                    rq_pbw[x] = p.b.pbw[pb + q0 + x];
+                    rq_pbmax[x] = p.b.pbmax[pb + q0 + x];
+                }
+                __syncthreads();
+            }
+            const ReqView rv{rq_pj + q, rq_pbw + q, rq_host, rq_host, rq_pbmax + q, rq_poff, rq_pj, staged};
             if (!topsis_step<BS, G, true, CS>(t, st, m, lb, sm, xs, p.pc_cap, p.tr, inst, s, rv)) break;
         }
         __syncthreads();

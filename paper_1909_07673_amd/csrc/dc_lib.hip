@@ -576,9 +576,6 @@ const void *grid_serve_kernel(const dc_ctx *ctx) {
                                     : reinterpret_cast<const void *>(k_serve_grid<kGridBlock, 0>);
 }
 
-// The plain kernel (state staged in LDS, 1,024 threads) compiled for k = 16
-// on the default criteria.
-constexpr int kPlainK = 16;
 // The AHP criteria kernel compiled for k = 32 (8,192 servers) on five criteria.
 constexpr int kAhpK = 32;
 
@@ -596,14 +593,7 @@ void launch_plain_step(dc_ctx *ctx, const Params &p) {
         return;
     }
     if (ctx->m.method == DC_TOPSIS) {
-        if (ctx->plain_res)
-            if (BS == 1024 && specialised(ctx, kPlainK))
-                hipLaunchKernelGGL((k_topsis_plain<1024, true, kPlainK>), dim3(1), dim3(1024), ctx->lds_plain,
-                                   ctx->stream, p);
-            else
-                hipLaunchKernelGGL((k_topsis_plain<BS, true>), dim3(1), dim3(BS), ctx->lds_plain, ctx->stream, p);
-        else
-            hipLaunchKernelGGL((k_topsis_plain<BS, false>), dim3(1), dim3(BS), ctx->lds_plain, ctx->stream, p);
+        hipLaunchKernelGGL((k_topsis_plain<BS>), dim3(1), dim3(BS), ctx->lds_plain, ctx->stream, p);
         ctx->last_launches += 1;
     } else {
         const int bx = (ctx->N + kAhpBlock - 1) / kAhpBlock;
@@ -638,7 +628,10 @@ void launch_plain_step(dc_ctx *ctx, const Params &p) {
     }
 }
 
+int run_resident(dc_ctx *ctx, DevBatch &b);
+
 int run_plain(dc_ctx *ctx, DevBatch &b) {
+    if (ctx->plain_res && ctx->m.method == DC_TOPSIS && !ctx->use_grid) return run_resident(ctx, b);
     ctx->launch_err = hipSuccess;
     for (int r = 0; r < b.R; ++r) {
         Params p = base_params(ctx, b, b.inst[r]);
@@ -666,10 +659,10 @@ int run_plain(dc_ctx *ctx, DevBatch &b) {
 }
 
 size_t batched_lds(const dc_ctx *ctx, int pc) {
-    return step_lds_bytes(pc, ctx->t.nsw, (size_t)xs_rows(ctx->m.nc) * ctx->N, 6 * (size_t)ctx->N + req_lds_ints());
+    return resident_lds_bytes(pc, ctx->t.nsw, ctx->N, xs_rows(ctx->m.nc), kMaxPairs);
 }
 
-// The batched kernel compiled for k = 16 fat-trees scored on the four
+// The resident kernel compiled for k = 16 fat-trees scored on the four
 // default criteria (the constants fold into the kernel), or for any case.
 constexpr int kBatchedK = 16;
 bool batched_specialised(const dc_ctx *ctx) { return specialised(ctx, kBatchedK); }
@@ -677,21 +670,23 @@ bool batched_specialised(const dc_ctx *ctx) { return specialised(ctx, kBatchedK)
 template <int BS, int G>
 void launch_batched_k(dc_ctx *ctx, const Params &p, size_t lds, hipStream_t stream) {
     if (batched_specialised(ctx))
-        hipLaunchKernelGGL((k_topsis_batched<BS, G, kBatchedK>), dim3(ctx->I), dim3(BS), lds, stream, p);
+        hipLaunchKernelGGL((k_topsis_resident<BS, G, kBatchedK, false>), dim3(ctx->I), dim3(BS), lds, stream, p);
     else
-        hipLaunchKernelGGL((k_topsis_batched<BS, G, 0>), dim3(ctx->I), dim3(BS), lds, stream, p);
+        hipLaunchKernelGGL((k_topsis_resident<BS, G, 0, false>), dim3(ctx->I), dim3(BS), lds, stream, p);
 }
 
 template <int BS, int G>
 int set_lds_batched(dc_ctx *ctx, size_t lds) {
-    return batched_specialised(ctx) ? set_lds(ctx, k_topsis_batched<BS, G, kBatchedK>, lds)
-                                    : set_lds(ctx, k_topsis_batched<BS, G, 0>, lds);
+    return batched_specialised(ctx) ? set_lds(ctx, k_topsis_resident<BS, G, kBatchedK, false>, lds)
+                                    : set_lds(ctx, k_topsis_resident<BS, G, 0, false>, lds);
 }
 
 // sh must be a built shape with 1 <= sh.pc <= ctx->pc_batched (callers check)
 void launch_batched(dc_ctx *ctx, DevBatch &b, const Shape &sh, hipStream_t stream) {
     Params p = base_params(ctx, b, 0);
     p.pc_cap = sh.pc;
+    p.xrows = xs_rows(ctx->m.nc);
+    p.rq_pairs = kMaxPairs;
     const size_t lds = batched_lds(ctx, sh.pc);
     switch (sh.bs * 10 + sh.g) {
     case 2561: launch_batched_k<256, 1>(ctx, p, lds, stream); break;
@@ -703,6 +698,60 @@ void launch_batched(dc_ctx *ctx, DevBatch &b, const Shape &sh, hipStream_t strea
     case 10242: launch_batched_k<1024, 2>(ctx, p, lds, stream); break;
     default: launch_batched_k<1024, 1>(ctx, p, lds, stream); break;
     }
+}
+
+// Plain form with the state in LDS: the whole queue in one launch of the
+// resident kernel, one workgroup per instance.  Its LDS is cut to the queue:
+// the accumulator rows only where a container has more peers than a chunk of
+// path tables, and as many of them and of the request's pairs as fit.
+constexpr size_t kLdsMax = 159 * 1024;   // 160 KiB of LDS, 1 KiB left for static shared memory
+
+struct Resident {
+    int pc = 0, rows = 0, pairs = 0;
+    size_t lds = 0;
+};
+
+Resident resident_layout(const dc_ctx *ctx, int max_peers, int max_pairs) {
+    const int nsw = ctx->t.nsw, nc = ctx->m.nc, need = std::max(max_peers, 1);
+    Resident L;
+    auto fits = [&](int pc, int rows, int pairs) { return resident_lds_bytes(pc, nsw, ctx->N, rows, pairs) <= kLdsMax; };
+    L.pairs = std::min(kMaxPairs, std::max(kMaxN, max_pairs));
+    if (!fits(1, nc + 1, L.pairs)) L.pairs = kMaxN;
+    L.rows = fits(need, nc + 1, L.pairs) || fits(need, nc + 1, kMaxN) ? nc + 1 : xs_rows(nc);
+    if (!fits(L.rows == nc + 1 ? need : std::min(need, 4), L.rows, L.pairs)) L.pairs = kMaxN;
+    for (L.pc = need; L.pc > 1 && !fits(L.pc, L.rows, L.pairs);) --L.pc;
+    L.lds = resident_lds_bytes(L.pc, nsw, ctx->N, L.rows, L.pairs);
+    return L;
+}
+
+// The resident kernel for a queue at BS threads: one server per thread where
+// that covers them, otherwise several; at the automatic size the one
+// compiled for k = 16.
+using ResidentFn = void (*)(Params);
+template <int BS>
+ResidentFn resident_fn(const dc_ctx *ctx) {
+    if (BS == 1024 && batched_specialised(ctx)) return k_topsis_resident<1024, 1, kBatchedK, true>;
+    return ctx->N <= BS ? k_topsis_resident<BS, 1, 0, true> : k_topsis_resident<BS, host_group(BS), 0, true>;
+}
+ResidentFn resident_fn_at(const dc_ctx *ctx, int bs) {
+    return bs == 64 ? resident_fn<64>(ctx) : bs == 256 ? resident_fn<256>(ctx)
+         : bs == 512 ? resident_fn<512>(ctx) : resident_fn<1024>(ctx);
+}
+
+int run_resident(dc_ctx *ctx, DevBatch &b) {
+    int max_pairs = 0, max_peers = 0;
+    for (int r = 0; r < b.R; ++r) max_pairs = std::max(max_pairs, b.poff[b.coff[r + 1]] - b.poff[b.coff[r]]);
+    for (int g = 0; g < b.Ct; ++g) max_peers = std::max(max_peers, b.poff[g + 1] - b.poff[g]);
+    const Resident L = resident_layout(ctx, max_peers, max_pairs);
+    Params p = base_params(ctx, b, 0);
+    p.pc_cap = L.pc;
+    p.xrows = L.rows;
+    p.rq_pairs = L.pairs;
+    hipLaunchKernelGGL(resident_fn_at(ctx, ctx->plain_bs), dim3(ctx->I), dim3(ctx->plain_bs), L.lds, ctx->stream, p);
+    HIPCHK(hipGetLastError());
+    ctx->last_launches += 1;
+    ctx->last_steps += b.Ct;
+    return DC_OK;
 }
 
 // Captures the batch's launch into a graph on a private stream (capture is
@@ -859,7 +908,7 @@ int serve_init(dc_ctx *ctx) {
     sv->free_list[0] = sv->arena_ints & ~size_t(3);
     HIPCHK(hipStreamCreateWithFlags(&sv->aux, hipStreamNonBlocking));
     sv->bs = ctx->N <= 256 ? 256 : 512;
-    const size_t lds_max = 159 * 1024;   // 160 KiB of LDS, 1 KiB left for static shared memory
+    const size_t lds_max = kLdsMax;
     const size_t base = step_lds_bytes(0, ctx->t.nsw, req_lds_ints(), 0);
     sv->pc = (int)std::max<size_t>(1, std::min<size_t>(kMaxN, (lds_max - base) / (8 * (size_t)ctx->t.nsw)));
     sv->lds = step_lds_bytes(sv->pc, ctx->t.nsw, req_lds_ints(), 0);
@@ -1400,7 +1449,7 @@ int dc_create(const dc_config *cfg, dc_ctx **out) {
     c->plain_bs = cfg->block ? cfg->block : (N <= 64 ? 64 : N <= 256 ? 256 : 1024);
     c->bshape.bs = cfg->block ? std::max(256, cfg->block) : 1024;
     c->bshape.g = c->bshape.bs >= 1024 ? 1 : host_group(c->bshape.bs);
-    const size_t lds_max = 159 * 1024;   // 160 KiB of LDS, 1 KiB left for static shared memory
+    const size_t lds_max = kLdsMax;
     {
         // plain: state + scratch in LDS when they fit with at least 8 peer tables
         const size_t res_fixed = step_lds_bytes(0, c->t.nsw, (size_t)xs_rows(nc) * N, 6 * (size_t)N);
@@ -1416,7 +1465,7 @@ int dc_create(const dc_config *cfg, dc_ctx **out) {
     }
     c->lds_select = step_lds_bytes(0, c->t.nsw, 0, 0);
     if (cfg->mode == DC_MODE_BATCHED) {
-        const size_t fixed = step_lds_bytes(0, c->t.nsw, (size_t)xs_rows(nc) * N, 6 * (size_t)N + req_lds_ints());
+        const size_t fixed = batched_lds(c, 0);
         if (fixed + 8 * (size_t)c->t.nsw > lds_max) { dc_destroy(ctx.release()); return DC_EINVAL; }
         c->pc_batched = (int)std::min<size_t>(kMaxN, (lds_max - fixed) / (8 * (size_t)c->t.nsw));
         c->bshape.pc = c->pc_batched;
@@ -1428,11 +1477,12 @@ int dc_create(const dc_config *cfg, dc_ctx **out) {
             return DC_EDEVICE;
         }
     }
-    if (set_lds(c, k_topsis_plain<64, true>, c->lds_plain) || set_lds(c, k_topsis_plain<64, false>, c->lds_plain) ||
-        set_lds(c, k_topsis_plain<256, true>, c->lds_plain) || set_lds(c, k_topsis_plain<256, false>, c->lds_plain) ||
-        set_lds(c, k_topsis_plain<512, true>, c->lds_plain) || set_lds(c, k_topsis_plain<512, false>, c->lds_plain) ||
-        set_lds(c, k_topsis_plain<1024, true>, c->lds_plain) || set_lds(c, k_topsis_plain<1024, false>, c->lds_plain) ||
-        set_lds(c, k_topsis_plain<1024, true, kPlainK>, c->lds_plain)) {
+    if (cfg->method == DC_TOPSIS && cfg->mode == DC_MODE_PLAIN &&
+        (c->plain_res
+             ? set_lds(c, resident_fn<64>(c), lds_max) || set_lds(c, resident_fn<256>(c), lds_max) ||
+                   set_lds(c, resident_fn<512>(c), lds_max) || set_lds(c, resident_fn<1024>(c), lds_max)
+             : set_lds(c, k_topsis_plain<64>, c->lds_plain) || set_lds(c, k_topsis_plain<256>, c->lds_plain) ||
+                   set_lds(c, k_topsis_plain<512>, c->lds_plain) || set_lds(c, k_topsis_plain<1024>, c->lds_plain))) {
         dc_destroy(ctx.release());
         return DC_EDEVICE;
     }

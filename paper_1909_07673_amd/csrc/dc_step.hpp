@@ -141,10 +141,11 @@ struct ReqView {
     const int *pj, *pbw, *hosts;
     int *hosts_out;    // LDS copy of hosts to update (batched form), or nullptr
     const int *pbmax;  // the peers' maximum demands
-    // the whole request in LDS (forms that stage it there), else nullptr:
-    // rpoff[x] the first pair of container x relative to the request's
-    // first pair (x <= n), rpj the pairs' peer containers
+    // where `whole`, the whole request in LDS: rpoff[x] the first pair of
+    // container x relative to the request's first pair (x <= n), rpj the
+    // pairs' peer containers
     const int *rpoff = nullptr, *rpj = nullptr;
+    bool whole = false;
 };
 
 // Waits for this wave's outstanding global loads and stores (s_waitcnt
@@ -545,7 +546,7 @@ __device__ __forceinline__ void give_back(const Topo &t, const State &st, const 
 // Request r found no server for container `upto`: undo containers
 // [0, upto) (all or nothing) and mark the request rejected.  host[] keeps
 // the servers the undone containers had been given (attempt record).
-// The same from the LDS copy of the request (ReqView::rpoff, rpj, hosts):
+// The same from the LDS copy of the request (ReqView::whole):
 // the pair owners are found in LDS, not by a search through global memory.
 // g0 and pb: the request's first container and first pair in the batch.
 template <int BS>
@@ -573,7 +574,7 @@ __device__ __forceinline__ void give_back_lds(const Topo &t, const State &st, co
 template <int BS>
 __device__ __forceinline__ void rollback_request(const Topo &t, const State &st, const Batch &b, int r, int upto,
                                                  const ReqView *rv = nullptr, const StepIn *s = nullptr) {
-    if (rv && rv->rpoff)
+    if (rv && rv->whole)
         give_back_lds<BS>(t, st, b, s->g0, s->p0 - rv->rpoff[s->i], upto, *rv);
     else
         give_back<BS>(t, st, b, r, upto);
