@@ -27,6 +27,7 @@ struct GridCtl {
     unsigned long long *rec;      // [G][kRecWords] per-workgroup records of a step, tagged (below)
     unsigned *round;              // selection rounds so far (kept across launches)
     int *flag;                    // [kGridFlags]: command buffers
+    unsigned *join;               // [2] entry of the queue kernels: arrivals, decision
 };
 
 // Selection rounds.  Round r of the argmax and commit needs no grid barrier:
@@ -249,23 +250,15 @@ __device__ __forceinline__ int block_sum(int v, int *slot) {
     return r;
 }
 
-// One container step on the pod of this workgroup (w = blockIdx.x).
-// rv.hosts_out, when given, is this workgroup's LDS copy of the request's
-// servers.  Returns false when the request was rejected at this container.
-template <int BS, int CS = 0>
-__device__ __forceinline__ bool grid_topsis_step(const Topo &t, const State &st, const Method &m, const Batch &b,
-                                                 const GSmem &sm, const GridCtl &g, long long timeout, const StepIn &s,
-                                                 const ReqView &rv, const Trace &tr, unsigned &rnd) {
-    const int w = blockIdx.x, G = gridDim.x, h = t.h, hh = t.hh, nc = crit_count<CS>(m);
-    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-    const int P = s.P, ubase = w * hh;
-    int *xs = sm.xs;
-    const unsigned long long stag = rec_tag(rnd);     // this step's records
-    int my_slot = -1;                                   // trace slot (workgroup 0, thread 0)
-    if (w == 0 && threadIdx.x == 0) {
-        if (s.i == 0) b.tsb[s.r] = dev_clock();
-        if (tr.stride > 0) my_slot = trace_slot(tr, 0, b.rid[s.r], s.i);
-    }
+// Peers, own capacities, path tables and criteria of a container step, for
+// the servers of this workgroup's pod (w = blockIdx.x < k).  emit(x, f, get)
+// receives server x of the pod, its feasibility and its criteria get(c), in
+// one thread per server.  The deficit slots and M_OK are reset here, before
+// the first barrier.  Returns the pod's summed aggregation-core residual.
+template <int BS, int CS, class Emit>
+__device__ __forceinline__ int grid_criteria(const Topo &t, const State &st, const Method &m, const GSmem &sm,
+                                             const StepIn &s, const ReqView &rv, Emit emit) {
+    const int w = blockIdx.x, h = t.h, hh = t.hh, P = s.P, ubase = w * hh;
     // ---- A: peers, own capacities
     for (int p = threadIdx.x; p < P; p += BS) {
         const int v = rv.hosts[rv.pj[p]];
@@ -278,8 +271,6 @@ __device__ __forceinline__ bool grid_topsis_step(const Topo &t, const State &st,
     }
     int cp = 0;
     for (int x = threadIdx.x; x < hh; x += BS) cp += st.ac[w * hh + x];
-    // the deficit slots and the error flag of phase D, reset here so that
-    // the barriers below order them before their use
     if (threadIdx.x < 6) sm.misc[M_DH0 + threadIdx.x] = (threadIdx.x & 1) ? -1 : kBig;
     if (threadIdx.x == 6) sm.misc[M_OK] = 0;
     const int capP_own = block_sum<BS>(cp, sm.misc + M_MISC - 1);   // ends with barriers
@@ -307,11 +298,7 @@ __device__ __forceinline__ bool grid_topsis_step(const Topo &t, const State &st,
         sm.tabE[pc * h + e] = val;
     }
     __syncthreads();
-    // ---- C: criteria of the pod's servers, partial column statistics
-    unsigned long long s2[kMaxCrit];
-    int mx[kMaxCrit], mn[kMaxCrit];
-#pragma unroll
-    for (int c = 0; c < kMaxCrit; ++c) { s2[c] = 0; mx[c] = -kBig - 1; mn[c] = kBig; }
+    // ---- C: criteria of the pod's servers
     for (int x = threadIdx.x; x < hh; x += BS) {
         const int u = ubase + x;
         const int up_u = st.up[u], el = edge_of(t, x), eu = w * h + el;
@@ -332,25 +319,200 @@ __device__ __forceinline__ bool grid_topsis_step(const Topo &t, const State &st,
         }
         feas &= (up_u >= up_acc);
         if (P > 0 && !m.route_end) feas &= (sm.capE[el] >= oute) & (capP_own >= outp);
-        xs[nc * hh + x] = feas;
+        emit(x, feas, [&](int c) -> int {
+            switch (crit_at<CS>(m, c)) {
+            case CRIT_CPU: return st.cpu[u];
+            case CRIT_RAM: return st.ram[u];
+            case CRIT_ACTIVE: return st.npl[u] > 0 ? 1 : 0;
+            case CRIT_PATHBW: return pbw_acc;
+            case CRIT_UPLINK: return up_u;
+            default: return hop_acc;
+            }
+        });
+    }
+    return capP_own;
+}
+
+// Peer-side deficits (server uplink, edge switch, pod) as in the
+// single-workgroup step, by thread p for peer p (me its packed record, capE
+// and capP its edge switch's and pod's summed residuals); they only narrow
+// the candidates.  The slots were reset by grid_criteria.
+__device__ __forceinline__ void grid_deficits(const GSmem &sm, int P, const int4 &me, int capE, int capP) {
+    const int v = me.x, e = me.y & 0xffff, d = me.y >> 16;
+    int sh = 0, se = 0, sp = 0;
+    for (int q = 0; q < P; ++q) {
+        const int4 o = sm.pk[q];
+        sh += o.x == v ? o.z : 0;
+        se += (o.y & 0xffff) == e ? o.z : 0;
+        sp += (o.y >> 16) == d ? o.z : 0;
+    }
+    if (me.w < sh) { atomicMin(sm.misc + M_DH0, v); atomicMax(sm.misc + M_DH1, v); }
+    if (capE < se) {
+        atomicMin(sm.misc + M_DE0, e);
+        atomicMax(sm.misc + M_DE1, e);
+    }
+    if (capP < sp) {
+        atomicMin(sm.misc + M_DP0, d);
+        atomicMax(sm.misc + M_DP1, d);
+    }
+}
+
+// Whether the deficits leave server x of pod w a candidate.
+struct Deficits {
+    int dh0, dh1, de0, de1, dp0, dp1;
+};
+__device__ __forceinline__ Deficits read_deficits(const GSmem &sm) {
+    return Deficits{sm.misc[M_DH0], sm.misc[M_DH1], sm.misc[M_DE0], sm.misc[M_DE1], sm.misc[M_DP0], sm.misc[M_DP1]};
+}
+__device__ __forceinline__ bool deficits_allow(const Topo &t, const Deficits &d, int w, int x) {
+    int f = (d.dh1 < 0) | ((d.dh0 == d.dh1) & (w * t.hh + x == d.dh0));
+    f &= (d.de1 < 0) | ((d.de0 == d.de1) & (w * t.h + edge_of(t, x) == d.de0));
+    f &= (d.dp1 < 0) | ((d.dp0 == d.dp1) & (w == d.dp0));
+    return f;
+}
+
+// Selection rounds of a step (global argmax, commit by workgroup 0,
+// retries).  key_of(x): the score key of the pod's server x, 0 when it is
+// no candidate (feas[x] == 0 masks it); a workgroup without a pod (nx = 0)
+// only follows.  Returns false when the request was rejected at this
+// container, or a wait failed.
+template <int BS, class KeyFn>
+__device__ __forceinline__ bool grid_select(const Topo &t, const State &st, const Method &m, const Batch &b,
+                                            const GSmem &sm, const GridCtl &g, long long timeout, const StepIn &s,
+                                            const ReqView &rv, unsigned &rnd, int nx, int *feas, KeyFn key_of) {
+    const int w = blockIdx.x, G = gridDim.x, ubase = w * t.hh, P = s.P;
+    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+    // the workgroup's best key (largest packed key) into LDS slot 0..1
+    auto wg_best = [&]() {
+        unsigned long long kb = 0;
+        for (int x = threadIdx.x; x < nx; x += BS) {
+            const unsigned long long k = key_of(x);
+            kb = k > kb ? k : kb;
+        }
+        unsigned hiw = wave_umax(static_cast<unsigned>(kb >> 32));
+        unsigned low = wave_umax(static_cast<unsigned>(kb >> 32) == hiw ? static_cast<unsigned>(kb) : 0u);
+        if (lane == 0) {
+            sm.wst[wid] = static_cast<int>(hiw);
+            sm.wst[kMaxWaves + wid] = static_cast<int>(low);
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            unsigned long long best = 0;
+            for (int x = 0; x < BS / kWave; ++x) {
+                const unsigned long long k = (static_cast<unsigned long long>(static_cast<unsigned>(sm.wst[x])) << 32) |
+                                             static_cast<unsigned>(sm.wst[kMaxWaves + x]);
+                best = k > best ? k : best;
+            }
+            *reinterpret_cast<unsigned long long *>(sm.misc + M_KEY) = round_key(best);
+        }
+    };
+    wg_best();
+    for (;;) {
+        const unsigned r = rnd++;
+        if (threadIdx.x == 0)
+            __hip_atomic_store(g.kslot + (r & 1) * G + w,
+                               round_tag(r) | *reinterpret_cast<const unsigned long long *>(sm.misc + M_KEY),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (threadIdx.x < kWave) {
+            bool bad = false;
+            const unsigned long long kb = round_max(g, r, timeout, bad);
+            if (lane == 0) {
+                *reinterpret_cast<unsigned long long *>(sm.wst + 2 * kMaxWaves) = kb;
+                sm.misc[M_OK] = bad;
+            }
+        }
+        __syncthreads();
+        if (sm.misc[M_OK]) return false;
+        const unsigned long long kb = *reinterpret_cast<const unsigned long long *>(sm.wst + 2 * kMaxWaves);
+        if (kb == 0) {                                                        // no server left
+            if (w == 0) rollback_request<BS>(t, st, b, s.r, s.i);
+            grid_sync(g, sm.misc + M_OK, timeout);
+            return false;
+        }
+        const int u = static_cast<int>(0x1ffffu - static_cast<unsigned>(kb & 0x1ffffu));
+        if (w == 0) {
+            // workgroup 0 commits: 1 placed, 0 retry with the next server,
+            // 2 request rejected when its links were routed at its end
+            if (threadIdx.x < kWave) {
+                // commit_wave reads the peer servers from LDS; its routing
+                // uses the global state
+                Smem cs;
+                cs.pk = sm.pk;
+                const bool ok = commit_wave(t, st, b, u, s, m.route_end ? 0 : P, cs, b.pbmax + s.p0, lane);
+                if (lane == 0) {
+                    sm.misc[M_ROUTE + 1] = ok;
+                    if (ok) {
+                        b.host[s.g] = u;
+                        b.score[s.g] = __uint_as_float(static_cast<unsigned>(kb >> 17) - 1u);
+                        if (s.i == s.n - 1) b.tse[s.r] = dev_clock();
+                    }
+                }
+            }
+            __syncthreads();
+            int res = sm.misc[M_ROUTE + 1];
+            if (res && m.route_end && s.i == s.n - 1)
+                res = route_request_end<BS>(t, st, b, sm.misc + M_ROUTE, s,
+                                            [&](int q) { return q == s.i ? u : rv.hosts[q]; }) ? 1 : 2;
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                __hip_atomic_store(g.rflag, round_tag(r) | static_cast<unsigned>(res), __ATOMIC_RELEASE,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+                sm.misc[M_RES] = res;
+            }
+        } else if (threadIdx.x == 0) {
+            sm.misc[M_RES] = round_outcome(g, r, timeout);
+        }
+        __syncthreads();
+        const int ok = sm.misc[M_RES];
+        if (ok < 0 || ok == 2) return false;
+        if (ok) {
+            if (rv.hosts_out && threadIdx.x == 0) rv.hosts_out[s.i] = u;
+            __syncthreads();
+            return true;
+        }
+        if (u - ubase >= 0 && u - ubase < nx) {                               // owner masks it and rescans
+            if (threadIdx.x == 0) feas[u - ubase] = 0;
+            __syncthreads();
+            wg_best();
+        }
+        __syncthreads();
+    }
+}
+
+// One container step on the pod of this workgroup (w = blockIdx.x).
+// rv.hosts_out, when given, is this workgroup's LDS copy of the request's
+// servers.  Returns false when the request was rejected at this container.
+template <int BS, int CS = 0>
+__device__ __forceinline__ bool grid_topsis_step(const Topo &t, const State &st, const Method &m, const Batch &b,
+                                                 const GSmem &sm, const GridCtl &g, long long timeout, const StepIn &s,
+                                                 const ReqView &rv, const Trace &tr, unsigned &rnd) {
+    const int w = blockIdx.x, G = gridDim.x, h = t.h, hh = t.hh, nc = crit_count<CS>(m);
+    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+    const int P = s.P, ubase = w * hh;
+    int *xs = sm.xs;
+    const unsigned long long stag = rec_tag(rnd);     // this step's records
+    int my_slot = -1;                                   // trace slot (workgroup 0, thread 0)
+    if (w == 0 && threadIdx.x == 0) {
+        if (s.i == 0) b.tsb[s.r] = dev_clock();
+        if (tr.stride > 0) my_slot = trace_slot(tr, 0, b.rid[s.r], s.i);
+    }
+    // partial column statistics of the pod's servers
+    unsigned long long s2[kMaxCrit];
+    int mx[kMaxCrit], mn[kMaxCrit];
+#pragma unroll
+    for (int c = 0; c < kMaxCrit; ++c) { s2[c] = 0; mx[c] = -kBig - 1; mn[c] = kBig; }
+    const int capP_own = grid_criteria<BS, CS>(t, st, m, sm, s, rv, [&](int x, int f, auto get) {
+        xs[nc * hh + x] = f;
 #pragma unroll
         for (int c = 0; c < kMaxCrit; ++c) {
             if (c >= nc) break;
-            int v;
-            switch (crit_at<CS>(m, c)) {
-            case CRIT_CPU: v = st.cpu[u]; break;
-            case CRIT_RAM: v = st.ram[u]; break;
-            case CRIT_ACTIVE: v = st.npl[u] > 0 ? 1 : 0; break;
-            case CRIT_PATHBW: v = pbw_acc; break;
-            case CRIT_UPLINK: v = up_u; break;
-            default: v = hop_acc; break;
-            }
+            const int v = get(c);
             xs[c * hh + x] = v;
             s2[c] += static_cast<unsigned long long>(static_cast<long long>(v) * v);
             mx[c] = max(mx[c], v);
             mn[c] = min(mn[c], v);
         }
-    }
+    });
 #pragma unroll
     for (int c = 0; c < kMaxCrit; ++c) {
         if (c >= nc) break;
@@ -425,28 +587,7 @@ __device__ __forceinline__ bool grid_topsis_step(const Topo &t, const State &st,
         MX[c] = wave_max(hi);
         MN[c] = -wave_max(nlo);
     }
-    // peer-side deficits (server uplink, edge switch, pod) as in the
-    // single-workgroup step; they only narrow the candidates (slots reset
-    // in phase A)
-    if (hp) {
-        const int v = me.x, e = me.y & 0xffff, d = me.y >> 16;
-        int sh = 0, se = 0, sp = 0;
-        for (int q = 0; q < P; ++q) {
-            const int4 o = sm.pk[q];
-            sh += o.x == v ? o.z : 0;
-            se += (o.y & 0xffff) == e ? o.z : 0;
-            sp += (o.y >> 16) == d ? o.z : 0;
-        }
-        if (me.w < sh) { atomicMin(sm.misc + M_DH0, v); atomicMax(sm.misc + M_DH1, v); }
-        if (cv[0] < se) {
-            atomicMin(sm.misc + M_DE0, e);
-            atomicMax(sm.misc + M_DE1, e);
-        }
-        if (cv[1] < sp) {
-            atomicMin(sm.misc + M_DP0, d);
-            atomicMax(sm.misc + M_DP1, d);
-        }
-    }
+    if (hp) grid_deficits(sm, P, me, cv[0], cv[1]);
     int slot = -1;
     if (tr.stride > 0) {
         const int zw[1] = {0}, zx[1] = {kRecTrace};
@@ -457,8 +598,7 @@ __device__ __forceinline__ bool grid_topsis_step(const Topo &t, const State &st,
     if (bad) sm.misc[M_OK] = 1;
     __syncthreads();
     if (sm.misc[M_OK]) return false;
-    const int dh0 = sm.misc[M_DH0], dh1 = sm.misc[M_DH1], de0 = sm.misc[M_DE0], de1 = sm.misc[M_DE1];
-    const int dp0 = sm.misc[M_DP0], dp1 = sm.misc[M_DP1];
+    const Deficits df = read_deficits(sm);
     float q[kMaxCrit], ap[kMaxCrit], am[kMaxCrit];
 #pragma unroll
     for (int c = 0; c < kMaxCrit; ++c) {
@@ -469,116 +609,14 @@ __device__ __forceinline__ bool grid_topsis_step(const Topo &t, const State &st,
         am[c] = static_cast<float>(crit_cost<CS>(m, c) ? MX[c] : MN[c]);
     }
     auto key_of = [&](int x) -> unsigned long long {
-        const int u = ubase + x;
-        int f = xs[nc * hh + x];
-        if (!m.route_end) {
-            f &= (dh1 < 0) | ((dh0 == dh1) & (u == dh0));
-            f &= (de1 < 0) | ((de0 == de1) & (w * h + edge_of(t, x) == de0));
-            f &= (dp1 < 0) | ((dp0 == dp1) & (w == dp0));
-        }
-        if (!f) return 0ull;
-        return score_key(topsis_close(nc, [&](int c) { return xs[c * hh + x]; }, q, ap, am), u);
-    };
-    // the workgroup's best key (largest packed key) into LDS slot 0..1
-    auto wg_best = [&]() {
-        unsigned long long kb = 0;
-        for (int x = threadIdx.x; x < hh; x += BS) {
-            const unsigned long long k = key_of(x);
-            kb = k > kb ? k : kb;
-        }
-        unsigned hiw = wave_umax(static_cast<unsigned>(kb >> 32));
-        unsigned low = wave_umax(static_cast<unsigned>(kb >> 32) == hiw ? static_cast<unsigned>(kb) : 0u);
-        if (lane == 0) {
-            sm.wst[wid] = static_cast<int>(hiw);
-            sm.wst[kMaxWaves + wid] = static_cast<int>(low);
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            unsigned long long best = 0;
-            for (int x = 0; x < BS / kWave; ++x) {
-                const unsigned long long k = (static_cast<unsigned long long>(static_cast<unsigned>(sm.wst[x])) << 32) |
-                                             static_cast<unsigned>(sm.wst[kMaxWaves + x]);
-                best = k > best ? k : best;
-            }
-            *reinterpret_cast<unsigned long long *>(sm.misc + M_KEY) = round_key(best);
-        }
+        if (!xs[nc * hh + x] || !(m.route_end || deficits_allow(t, df, w, x))) return 0ull;
+        return score_key(topsis_close(nc, [&](int c) { return xs[c * hh + x]; }, q, ap, am), ubase + x);
     };
     if (slot >= 0)
         for (int x = threadIdx.x; x < hh; x += BS)
             tr.scores[static_cast<size_t>(slot) * t.N + ubase + x] =
                 topsis_close(nc, [&](int c) { return xs[c * hh + x]; }, q, ap, am);
-    wg_best();
-    // ---- E: selection rounds (global argmax, commit by workgroup 0, retries)
-    for (;;) {
-        const unsigned r = rnd++;
-        if (threadIdx.x == 0)
-            __hip_atomic_store(g.kslot + (r & 1) * G + w,
-                               round_tag(r) | *reinterpret_cast<const unsigned long long *>(sm.misc + M_KEY),
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (threadIdx.x < kWave) {
-            bool bad = false;
-            const unsigned long long kb = round_max(g, r, timeout, bad);
-            if (lane == 0) {
-                *reinterpret_cast<unsigned long long *>(sm.wst + 2 * kMaxWaves) = kb;
-                sm.misc[M_OK] = bad;
-            }
-        }
-        __syncthreads();
-        if (sm.misc[M_OK]) return false;
-        const unsigned long long kb = *reinterpret_cast<const unsigned long long *>(sm.wst + 2 * kMaxWaves);
-        if (kb == 0) {                                                        // no server left
-            if (w == 0) rollback_request<BS>(t, st, b, s.r, s.i);
-            grid_sync(g, sm.misc + M_OK, timeout);
-            return false;
-        }
-        const int u = static_cast<int>(0x1ffffu - static_cast<unsigned>(kb & 0x1ffffu));
-        if (w == 0) {
-            // workgroup 0 commits: 1 placed, 0 retry with the next server,
-            // 2 request rejected when its links were routed at its end
-            if (threadIdx.x < kWave) {
-                // commit_wave reads the peer servers from LDS; its routing
-                // uses the global state
-                Smem cs;
-                cs.pk = sm.pk;
-                const bool ok = commit_wave(t, st, b, u, s, m.route_end ? 0 : P, cs, b.pbmax + s.p0, lane);
-                if (lane == 0) {
-                    sm.misc[M_ROUTE + 1] = ok;
-                    if (ok) {
-                        b.host[s.g] = u;
-                        b.score[s.g] = __uint_as_float(static_cast<unsigned>(kb >> 17) - 1u);
-                        if (s.i == s.n - 1) b.tse[s.r] = dev_clock();
-                    }
-                }
-            }
-            __syncthreads();
-            int res = sm.misc[M_ROUTE + 1];
-            if (res && m.route_end && s.i == s.n - 1)
-                res = route_request_end<BS>(t, st, b, sm.misc + M_ROUTE, s,
-                                            [&](int q) { return q == s.i ? u : rv.hosts[q]; }) ? 1 : 2;
-            __syncthreads();
-            if (threadIdx.x == 0) {
-                __hip_atomic_store(g.rflag, round_tag(r) | static_cast<unsigned>(res), __ATOMIC_RELEASE,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-                sm.misc[M_RES] = res;
-            }
-        } else if (threadIdx.x == 0) {
-            sm.misc[M_RES] = round_outcome(g, r, timeout);
-        }
-        __syncthreads();
-        const int ok = sm.misc[M_RES];
-        if (ok < 0 || ok == 2) return false;
-        if (ok) {
-            if (rv.hosts_out && threadIdx.x == 0) rv.hosts_out[s.i] = u;
-            __syncthreads();
-            return true;
-        }
-        if (u / hh == w) {                                                    // owner masks it and rescans
-            if (threadIdx.x == 0) xs[nc * hh + (u - ubase)] = 0;
-            __syncthreads();
-            wg_best();
-        }
-        __syncthreads();
-    }
+    return grid_select<BS>(t, st, m, b, sm, g, timeout, s, rv, rnd, hh, xs + nc * hh, key_of);
 }
 
 }  // namespace dcs

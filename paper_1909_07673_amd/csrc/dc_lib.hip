@@ -5,6 +5,7 @@
 #include "../../include/dcsched.h"
 #include "dc_kernels.hpp"
 #include "dc_grid.hpp"
+#include "dc_queue.hpp"
 #include "dc_tiles.hpp"
 
 #include <algorithm>
@@ -325,6 +326,16 @@ struct dc_ctx {
     int *d_grid = nullptr;         // backing allocation of grid
     size_t lds_grid = 0;
     long long grid_timeout = 10000000LL;   // 100 ms of device clock per barrier wait
+    // plain form: a queue in one launch over several workgroups
+    enum { QUEUE_NONE, QUEUE_TOPSIS, QUEUE_AHP };
+    int queue = QUEUE_NONE;
+    int queue_wgs = 0;
+    size_t lds_queue = 0;
+    unsigned epoch = 0;            // launches of the queue kernel
+    long long patience = 2000000LL;        // 20 ms of device clock for its workgroups to meet
+    AhpGrid ahp{};
+    unsigned long long *d_words = nullptr; // its value and rank words
+    int *h_ctl = nullptr;          // pinned: err, round, join[2] after a launch
     hipError_t launch_err = hipSuccess;    // first failed cooperative launch of a run
     hipStream_t cap_stream = nullptr;      // graph capture (batched form)
 };
@@ -629,9 +640,15 @@ void launch_plain_step(dc_ctx *ctx, const Params &p) {
 }
 
 int run_resident(dc_ctx *ctx, DevBatch &b);
+int run_queue(dc_ctx *ctx, DevBatch &b, bool *ran);
 
 int run_plain(dc_ctx *ctx, DevBatch &b) {
     if (ctx->plain_res && ctx->m.method == DC_TOPSIS && !ctx->use_grid) return run_resident(ctx, b);
+    if (ctx->queue != dc_ctx::QUEUE_NONE) {
+        bool ran = false;
+        const int rc = run_queue(ctx, b, &ran);
+        if (rc || ran) return rc;
+    }
     ctx->launch_err = hipSuccess;
     for (int r = 0; r < b.R; ++r) {
         Params p = base_params(ctx, b, b.inst[r]);
@@ -845,11 +862,9 @@ int collect(dc_ctx *ctx, DevBatch &b) {
 }
 
 // ---------------------------------------------------------------- cooperative step
-int grid_init(dc_ctx *ctx) {
-    const int G = ctx->t.k, h = ctx->t.h;
-    if (h > kRecCapP - kRecCapE || G > kWave) return DC_EINVAL;
-    // count, gen, err, round, flag[kGridFlags], then 8-byte aligned: kslot[2][G], rflag, rec[G][kRecWords]
-    const size_t ints = 4 + kGridFlags + 2 + 2 * (2 * (size_t)G + 1 + (size_t)G * kRecWords);
+int grid_alloc(dc_ctx *ctx, int G) {
+    // count, gen, err, round, join[2], flag[kGridFlags], then 8-byte aligned: kslot[2][G], rflag, rec[k][kRecWords]
+    const size_t ints = 6 + kGridFlags + 2 + 2 * (2 * (size_t)G + 1 + (size_t)ctx->t.k * kRecWords);
     HIPCHK(hipMalloc(&ctx->d_grid, ints * sizeof(int)));
     hipLaunchKernelGGL(k_fill_i32, dim3(16), dim3(256), 0, ctx->stream, ctx->d_grid, 0, (long long)ints);
     HIPCHK(hipGetLastError());
@@ -859,12 +874,21 @@ int grid_init(dc_ctx *ctx) {
     g.gen = reinterpret_cast<unsigned *>(p + 1);
     g.err = p + 2;
     g.round = reinterpret_cast<unsigned *>(p + 3);
-    g.flag = p + 4;
+    g.join = reinterpret_cast<unsigned *>(p + 4);
+    g.flag = p + 6;
     int *k = g.flag + kGridFlags;
     k += (reinterpret_cast<uintptr_t>(k) & 7) ? 1 : 0;
     g.kslot = reinterpret_cast<unsigned long long *>(k);
     g.rflag = g.kslot + 2 * G;
     g.rec = g.rflag + 1;
+    return DC_OK;
+}
+
+int grid_init(dc_ctx *ctx) {
+    const int G = ctx->t.k, h = ctx->t.h;
+    if (h > kRecCapP - kRecCapE || G > kWave) return DC_EINVAL;
+    const int rc = grid_alloc(ctx, G);
+    if (rc) return rc;
     ctx->lds_grid = gsmem_bytes(h, ctx->t.hh, ctx->m.nc);
     const size_t serve_lds = align4(ctx->lds_grid / sizeof(int)) * sizeof(int) + req_lds_ints() * sizeof(int);
     if (serve_lds > 159 * 1024) return DC_EINVAL;
@@ -874,6 +898,86 @@ int grid_init(dc_ctx *ctx) {
             hipSuccess)
         return DC_EDEVICE;
     ctx->use_grid = true;
+    return DC_OK;
+}
+
+// ---------------------------------------------------------------- queue kernels
+using TopsisQueueFn = void (*)(Params, GridCtl, unsigned, long long, long long);
+TopsisQueueFn topsis_queue_fn(const dc_ctx *ctx) {
+    return specialised(ctx, kGridK) ? k_topsis_queue<kGridBlock, kGridK> : k_topsis_queue<kGridBlock, 0>;
+}
+
+// Which plain contexts run their queue in one launch over several
+// workgroups: one data center, left to the automatic choice (grid = 0 and no
+// block size asked for).  TOPSIS where the state does not fit one workgroup
+// (from k = 22 on): a step over one workgroup per pod.  AHP on the 1-9 scale
+// up to 8,192 servers, where the position table of every criterion fits LDS
+// beside the prefix sums.
+int queue_init(dc_ctx *ctx) {
+    const dc_config &cfg = ctx->cfg;
+    if (cfg.mode != DC_MODE_PLAIN || ctx->I != 1 || cfg.grid != 0 || cfg.block != 0) return DC_OK;
+    const int k = ctx->t.k, h = ctx->t.h, hh = ctx->t.hh, nc = ctx->m.nc;
+    if (ctx->m.method == DC_TOPSIS) {
+        if (ctx->plain_res) return DC_OK;
+        ctx->queue_wgs = k;
+        ctx->lds_queue = align4(gsmem_bytes(h, hh, nc) / sizeof(int)) * sizeof(int) + kQueueReqInts * sizeof(int);
+        if (set_lds(ctx, topsis_queue_fn(ctx), ctx->lds_queue)) return DC_EDEVICE;
+        ctx->queue = dc_ctx::QUEUE_TOPSIS;
+    } else {
+        if (!ctx->ahp_sorted) return DC_OK;
+        int vmax = 0;
+        for (int c = 0; c < nc; ++c) {
+            const int id = ctx->m.crit[c];
+            int &v = ctx->ahp.vmax[c];
+            v = id == CRIT_CPU ? cfg.host_cpu : id == CRIT_RAM ? cfg.host_ram : id == CRIT_ACTIVE ? 1
+              : id == CRIT_HOPS ? 6 * (kMaxN - 1) : cfg.bw_host_edge;
+            vmax = std::max(vmax, v);
+        }
+        ctx->ahp.fbytes = ((vmax + 3) / 2 * 4 + 15) & ~15;
+        ctx->lds_queue = ahp_queue_lds(h, hh, ctx->N, ctx->ahp.fbytes);
+        if (vmax >= 1 << 17 || ctx->lds_queue > kLdsMax) return DC_OK;
+        // a workgroup per pod, and enough of them that a slice of a
+        // criterion's ranks is one row per thread
+        ctx->queue_wgs = std::max(k, nc * ((ctx->N + kAhpQueueBlock - 1) / kAhpQueueBlock));
+        if (ctx->queue_wgs > kWave) return DC_OK;
+        if (set_lds(ctx, k_ahp_queue<kAhpQueueBlock>, ctx->lds_queue)) return DC_EDEVICE;
+        const size_t words = 2 * (size_t)nc * ctx->N;
+        HIPCHK(hipMalloc(&ctx->d_words, words * sizeof(unsigned long long)));
+        hipLaunchKernelGGL(k_fill_i32, dim3(64), dim3(256), 0, ctx->stream, reinterpret_cast<int *>(ctx->d_words), 0,
+                           2 * (long long)words);
+        ctx->ahp.xw = ctx->d_words;
+        ctx->ahp.lw = ctx->d_words + (size_t)nc * ctx->N;
+        ctx->queue = dc_ctx::QUEUE_AHP;
+    }
+    HIPCHK(hipHostMalloc(reinterpret_cast<void **>(&ctx->h_ctl), 4 * sizeof(int), 0));
+    if (cfg.grid_timeout_us > 0) ctx->patience = 100LL * cfg.grid_timeout_us;
+    return grid_alloc(ctx, ctx->queue_wgs);
+}
+
+// Runs a batch in one launch; *ran is false when its workgroups did not
+// meet in time and nothing was done.  Once they have met, a wait inside is
+// bounded by two seconds: far above any step, and only a fault reaches it.
+int run_queue(dc_ctx *ctx, DevBatch &b, bool *ran) {
+    constexpr long long kWait = 200000000LL;
+    const Params p = base_params(ctx, b, 0);
+    const unsigned epoch = ++ctx->epoch;
+    if (ctx->queue == dc_ctx::QUEUE_TOPSIS)
+        hipLaunchKernelGGL(topsis_queue_fn(ctx), dim3(ctx->queue_wgs), dim3(kGridBlock), ctx->lds_queue, ctx->stream, p,
+                           ctx->grid, epoch, ctx->patience, kWait);
+    else
+        hipLaunchKernelGGL((k_ahp_queue<kAhpQueueBlock>), dim3(ctx->queue_wgs), dim3(kAhpQueueBlock), ctx->lds_queue,
+                           ctx->stream, p, ctx->grid, ctx->ahp, epoch, ctx->patience, kWait);
+    HIPCHK(hipGetLastError());
+    HIPCHK(hipMemcpyAsync(ctx->h_ctl, ctx->grid.err, 4 * sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
+    HIPCHK(hipStreamSynchronize(ctx->stream));
+    if (ctx->h_ctl[0]) {
+        ctx->poisoned = true;
+        std::fprintf(stderr, "libdcsched: a wait inside a queue kernel timed out\n");
+        return DC_EDEVICE;
+    }
+    *ran = static_cast<unsigned>(ctx->h_ctl[3]) == 2 * epoch;
+    ctx->last_launches += 1;
+    if (*ran) ctx->last_steps += b.Ct;
     return DC_OK;
 }
 
@@ -1527,6 +1631,7 @@ int dc_create(const dc_config *cfg, dc_ctx **out) {
         const int grc = grid_init(c);
         if (grc) { dc_destroy(ctx.release()); return grc; }
     }
+    if (const int qrc = queue_init(c)) { dc_destroy(ctx.release()); return qrc; }
     if (cfg->mode == DC_MODE_SERVING) {
         if (I != 1) { dc_destroy(ctx.release()); return DC_EINVAL; }
         const int src = serve_init(c);
@@ -2008,6 +2113,8 @@ void dc_destroy(dc_ctx *ctx) {
             if (p) (void)hipFree(p);
         if (ctx->d_rowpart) (void)hipFree(ctx->d_rowpart);
         if (ctx->d_wsort) (void)hipFree(ctx->d_wsort);
+        if (ctx->d_words) (void)hipFree(ctx->d_words);
+        if (ctx->h_ctl) (void)hipHostFree(ctx->h_ctl);
         if (ctx->d_tscore) (void)hipFree(ctx->d_tscore);
     } else {
         std::fprintf(stderr, "libdcsched: the device did not finish this context's work; its memory is left allocated\n");

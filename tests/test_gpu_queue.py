@@ -83,3 +83,83 @@ def test_queue_several_instances():
         np.testing.assert_array_equal(mine["score"].view(np.uint32), one["score"].view(np.uint32))
         np.testing.assert_array_equal(s.state(x), one["state"])
     s.close()
+
+
+def _ahp(inst, reqs, crit=None, cost=None, **kw):
+    if crit is not None:
+        kw.update(crit=crit, cost=cost)
+    return _schedule(inst, reqs, method=dc.DC_AHP, **kw)
+
+
+C8 = (0, 1, 2, 3, 4, 5, 0, 4)
+
+
+@pytest.mark.parametrize("k,n_lo,n_hi,count,crit,cost", [
+    (4, 2, 6, 40, None, None),
+    (4, 2, 6, 20, C8, (0, 0, 0, 0, 0, 1, 1, 1)),    # more workgroups than pods
+    (6, 60, 64, 6, C5, (0, 0, 0, 0, 1)),
+    (16, 2, 24, 20, None, None),                     # 1,024 servers: one per thread
+    (18, 2, 24, 12, C5, (1, 0, 1, 0, 1)),
+    (20, 4, 4, 24, None, None),
+    (30, 2, 32, 6, (4,), (0,)),                      # one criterion, 30 slices
+    (32, 8, 64, 6, C5, (0, 0, 0, 0, 1)),             # the largest
+])
+@pytest.mark.parametrize("routing", [0, 1])
+def test_ahp_queue_matches_launches(k, n_lo, n_hi, count, crit, cost, routing):
+    """One launch, its column sums from counts, against the sorted passes of
+    one launch per stage (grid = 1): the same sums up to FP64 rounding, so
+    the same FP32 scores."""
+    inst, reqs = _queue(k, n_lo, n_hi, count, seed=3)
+    _same(_ahp(inst, reqs, crit, cost, routing=routing), _ahp(inst, reqs, crit, cost, routing=routing, grid=1))
+
+
+@pytest.mark.parametrize("cap", [0, 1, 43000, 100000])
+def test_ahp_queue_capacities(cap):
+    """Capacities at the ends of the position table's range, and past it."""
+    rng = np.random.default_rng(cap)
+    inst = make_instance(16, 32, 256, cap, 100000, 100000, background=0.7, rng=rng)
+    reqs = make_requests(12, rng, 1, 12, bw_lo=1, bw_hi=max(1, cap // 20))
+    _same(_ahp(inst, reqs, C5, (0, 0, 0, 0, 1)), _ahp(inst, reqs, C5, (0, 0, 0, 0, 1), grid=1))
+
+
+@pytest.mark.parametrize("k,method", [(16, dc.DC_AHP), (24, dc.DC_TOPSIS)])
+def test_queue_that_cannot_start_runs_step_by_step(k, method):
+    """With 1 us for its workgroups to meet, a queue kernel that finds them
+    late leaves everything alone, and the queue runs launch by launch: the
+    same results either way, again and again."""
+    inst, reqs = _queue(k, 2, 12, 8, seed=9)
+    want = _schedule(inst, reqs, method=method, grid=1)
+    s = dc.Scheduler([inst], method=method, grid_timeout_us=1)
+    for r in reqs:
+        s.submit(r)
+    for _ in range(3):
+        s.rewind()
+        res = s.schedule_array()
+        for f in ("status", "n", "failed_at", "host"):
+            np.testing.assert_array_equal(res[f], want[f])
+        np.testing.assert_array_equal(res["score"].view(np.uint32), want["score"].view(np.uint32))
+        np.testing.assert_array_equal(s.state(0), want["state"])
+    s.close()
+
+
+def test_topsis_queue_two_calls_and_releases():
+    """Several schedule calls with departures between them on one context:
+    rounds and tags go on from one launch to the next."""
+    inst, reqs = _queue(24, 2, 16, 16, seed=21)
+    out = []
+    for grid in (0, 2):
+        s = dc.Scheduler([inst], grid=grid)
+        got = []
+        for lo in range(0, 16, 4):
+            ids = [s.submit(r) for r in reqs[lo:lo + 4]]
+            res = s.schedule_array()
+            got.append(res.copy())
+            for i, ok in zip(ids, res["status"]):
+                if ok and i % 2 == 0:
+                    assert s.release(i) == dc.DC_OK
+        out.append((got, s.state(0)))
+        s.close()
+    for a, b in zip(out[0][0], out[1][0]):
+        for f in ("status", "failed_at", "host"):
+            np.testing.assert_array_equal(a[f], b[f])
+    np.testing.assert_array_equal(out[0][1], out[1][1])
