@@ -24,7 +24,8 @@ struct GridCtl {
     int *err;                     // set when a barrier wait timed out
     unsigned long long *kslot;    // [2][G] per-workgroup best key of a selection round, tagged
     unsigned long long *rflag;    // outcome of a selection round's commit, tagged
-    unsigned long long *rec;      // [G][kRecWords] per-workgroup records of a step, tagged (below)
+    unsigned long long *rec;      // [kRecWords][pods] per-workgroup records of a step, tagged (below)
+    int pods;                     // workgroups that own a pod (the first k)
     unsigned *round;              // selection rounds so far (kept across launches)
     int *flag;                    // [kGridFlags]: command buffers
     unsigned *join;               // [2] entry of the queue kernels: arrivals, decision
@@ -158,7 +159,9 @@ __device__ __forceinline__ bool grid_sync(const GridCtl &g, int *lds_flag, long 
 // 2^31 rounds, so a word read with the current tag was written in this step.
 // A workgroup writes the next step's record only after this step's last
 // selection round, whose outcome needs every workgroup's key, which each
-// publishes after it has read the records.
+// publishes after it has read the records.  A wave reads one word of every
+// workgroup at once, so the words are laid out by word, then workgroup: one
+// poll then takes a few cache lines a word instead of one per workgroup.
 __device__ __forceinline__ unsigned long long rec_tag(unsigned r) {
     return static_cast<unsigned long long>(r | 0x80000000u) << 32;
 }
@@ -169,13 +172,12 @@ constexpr int kRecTrace = kRecCapP + 1;
 static_assert(kRecTrace < kRecWords, "record layout");
 
 __device__ __forceinline__ void rec_put(const GridCtl &g, int w, int x, unsigned long long tag, int v) {
-    __hip_atomic_store(g.rec + static_cast<size_t>(w) * kRecWords + x, tag | static_cast<unsigned>(v),
-                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(g.rec + x * g.pods + w, tag | static_cast<unsigned>(v), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
 }
 
 __device__ __forceinline__ unsigned long long rec_load(const GridCtl &g, int w, int x) {
-    return __hip_atomic_load(g.rec + static_cast<size_t>(w) * kRecWords + x, __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_AGENT);
+    return __hip_atomic_load(g.rec + x * g.pods + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ bool rec_has(unsigned long long v, unsigned long long tag) { return (v >> 32) == (tag >> 32); }
 
@@ -204,22 +206,31 @@ __device__ __forceinline__ bool rec_get(const GridCtl &g, int n, const int (&ws)
     }
 }
 
-// LDS of the cooperative step (per workgroup): peers, own-pod tables and
-// capacities, per-server scratch of the pod, statistics slots.
+// LDS of the cooperative step (per workgroup): peers, the own pod's state,
+// tables and capacities, per-server scratch of the pod, statistics slots.
 struct GSmem {
     int4 *pk;                     // [kMaxN] packed peers (as in Smem)
     int *wst;                     // [kStatFields][kMaxWaves]
     int *misc;                    // [M_MISC]
-    int *capE;                    // [h] own edge switches
-    int *tabT, *tabE;             // [kMaxN][h]
+    int *own;                     // [6][hh] the own pod's residuals, as in State
+    int *capE;                    // [h] own edge switches, summed
+    int *tabT, *tabE, *peerE;     // [kMaxN][h] path tables; the peers' edge-aggregation residuals
     int *xs;                      // [nc+6][hh]
-    int *pcap;                    // [2][kMaxN] peers' edge-switch and pod capacities
 };
 
+// Residuals of the own pod kept in LDS, and the tables of a step.
+__host__ __device__ inline size_t own_ints(int h, int hh) { return align4(6 * (size_t)hh) + align4(h); }
+__host__ __device__ inline size_t tab_ints(int h) { return 3 * align4((size_t)kMaxN * h); }
+__device__ inline int *carve_tabs(GSmem &s, int *p, int h) {
+    s.tabT = p; p += align4((size_t)kMaxN * h);
+    s.tabE = p; p += align4((size_t)kMaxN * h);
+    s.peerE = p; p += align4((size_t)kMaxN * h);
+    return p;
+}
+
 __host__ __device__ inline size_t gsmem_bytes(int h, int hh, int nc) {
-    return sizeof(int4) * kMaxN + sizeof(int) * (kStatFields * kMaxWaves + M_MISC + align4(h) +
-                                                 2 * align4((size_t)kMaxN * h) + (size_t)(nc + 6) * hh +
-                                                 2 * kMaxN);
+    return sizeof(int4) * kMaxN +
+           sizeof(int) * (kStatFields * kMaxWaves + M_MISC + own_ints(h, hh) + tab_ints(h) + (size_t)(nc + 6) * hh);
 }
 
 __device__ inline GSmem gcarve(char *base, int h, int hh, int nc) {
@@ -228,82 +239,111 @@ __device__ inline GSmem gcarve(char *base, int h, int hh, int nc) {
     int *p = reinterpret_cast<int *>(base + sizeof(int4) * kMaxN);
     s.wst = p; p += kStatFields * kMaxWaves;
     s.misc = p; p += M_MISC;
+    s.own = p; p += align4(6 * (size_t)hh);
     s.capE = p; p += align4(h);
-    s.tabT = p; p += align4((size_t)kMaxN * h);
-    s.tabE = p; p += align4((size_t)kMaxN * h);
-    s.xs = p; p += (size_t)(nc + 6) * hh;
-    s.pcap = p;
+    s.xs = carve_tabs(s, p, h);
     return s;
 }
 
-// Sum of v over the block; the result is valid in every thread after the
-// call (uses misc[M_MISC-1] and one LDS barrier pair).
-template <int BS>
-__device__ __forceinline__ int block_sum(int v, int *slot) {
-    v = wave_sum(v);
-    if (threadIdx.x == 0) *slot = 0;
-    __syncthreads();
-    if ((threadIdx.x & (kWave - 1)) == 0) atomicAdd(slot, v);
-    __syncthreads();
-    const int r = *slot;
-    __syncthreads();
-    return r;
+// max_j min(x[j], y[j]) over n entries (n % 4 == 0: 16-byte aligned rows)
+template <class X, class Y>
+__device__ __forceinline__ int max_min(X x, Y y, int n) {
+    int val = 0;
+    if ((n & 3) == 0) {
+#pragma unroll 4
+        for (int j = 0; j < n; j += 4) {
+            const int4 a = *reinterpret_cast<const int4 *>(x + j), b = *reinterpret_cast<const int4 *>(y + j);
+            val = max(val, max(max(min(a.x, b.x), min(a.y, b.y)), max(min(a.z, b.z), min(a.w, b.w))));
+        }
+    } else {
+#pragma unroll 8
+        for (int j = 0; j < n; ++j) val = max(val, min(x[j], y[j]));
+    }
+    return val;
 }
 
 // Peers, own capacities, path tables and criteria of a container step, for
 // the servers of this workgroup's pod (w = blockIdx.x < k).  emit(x, f, get)
 // receives server x of the pod, its feasibility and its criteria get(c), in
 // one thread per server.  The deficit slots and M_OK are reset here, before
-// the first barrier.  Returns the pod's summed aggregation-core residual.
+// the first barrier.  The pod's residuals stay in LDS from step to step and
+// are read again only where a commit may have changed them (`stale`), so a
+// step waits for memory once, for the peers' residuals, instead of once per
+// stage: see grid_select for who sets stale.  misc[M_CAPP] keeps the pod's
+// summed aggregation-core residual.
 template <int BS, int CS, class Emit>
-__device__ __forceinline__ int grid_criteria(const Topo &t, const State &st, const Method &m, const GSmem &sm,
-                                             const StepIn &s, const ReqView &rv, Emit emit) {
+__device__ __forceinline__ void grid_criteria(const Topo &t, const State &st, const Method &m, const GSmem &sm,
+                                              const StepIn &s, const ReqView &rv, bool stale, Emit emit) {
     const int w = blockIdx.x, h = t.h, hh = t.hh, P = s.P, ubase = w * hh;
-    // ---- A: peers, own capacities
+    int *own_up = sm.own + 3 * hh, *own_ea = sm.own + 4 * hh, *own_ac = sm.own + 5 * hh;
+    // ---- A: everything a step reads from memory.  Peers, their edge
+    // switches' rows, table T (against the peers' aggregation-core rows)
     for (int p = threadIdx.x; p < P; p += BS) {
         const int v = rv.hosts[rv.pj[p]];
         sm.pk[p] = make_int4(v, edge_of(t, v) | (pod_of(t, v) << 16), rv.pbw[p], st.up[v]);
     }
-    for (int e = threadIdx.x; e < h; e += BS) {
-        int se = 0;
-        for (int a = 0; a < h; ++a) se += st.ea[(w * h + e) * h + a];
-        sm.capE[e] = se;
-    }
-    int cp = 0;
-    for (int x = threadIdx.x; x < hh; x += BS) cp += st.ac[w * hh + x];
     if (threadIdx.x < 6) sm.misc[M_DH0 + threadIdx.x] = (threadIdx.x & 1) ? -1 : kBig;
     if (threadIdx.x == 6) sm.misc[M_OK] = 0;
-    const int capP_own = block_sum<BS>(cp, sm.misc + M_MISC - 1);   // ends with barriers
-    // ---- B: path tables for this pod (T: its aggregation switches, E: its edge switches)
+    if (stale) {
+        // the six arrays are contiguous, N entries each
+        const int n = 6 * hh;
+        if ((hh & 3) == 0) {
+            for (int x = 4 * threadIdx.x; x < n; x += 4 * BS) {
+                const int f = x / hh;
+                *reinterpret_cast<int4 *>(sm.own + x) =
+                    *reinterpret_cast<const int4 *>(st.cpu + (size_t)f * t.N + ubase + (x - f * hh));
+            }
+        } else {
+            for (int x = threadIdx.x; x < n; x += BS) {
+                const int f = x / hh;
+                sm.own[x] = st.cpu[(size_t)f * t.N + ubase + (x - f * hh)];
+            }
+        }
+    }
     for (int it = threadIdx.x; it < P * h; it += BS) {
         const int pc = it / h, a = it - pc * h;
-        const int pv = sm.pk[pc].y >> 16;
+        const int v = rv.hosts[rv.pj[pc]], pv = pod_of(t, v);
+        sm.peerE[it] = st.ea[edge_of(t, v) * h + a];
+        const int *y = st.ac + (pv * h + a) * h;
         int val = 0;
-        if (pv != w) {
-            const int *x = st.ac + (w * h + a) * h, *y = st.ac + (pv * h + a) * h;
-            for (int j = 0; j < h; ++j) val = max(val, min(x[j], y[j]));
-        }
-        sm.tabT[pc * h + a] = val;
+        if (pv != w) val = stale ? max_min(st.ac + (w * h + a) * h, y, h) : max_min(own_ac + a * h, y, h);
+        sm.tabT[it] = val;
     }
     __syncthreads();
+    // ---- B: table E of the pod's edge switches, own capacities
+    if (stale) {
+        for (int e = BS - 1 - static_cast<int>(threadIdx.x); e < h; e += BS) {
+            int se = 0;
+            for (int a = 0; a < h; ++a) se += own_ea[e * h + a];
+            sm.capE[e] = se;
+        }
+        if (threadIdx.x < kWave) {
+            int cp = 0;
+            for (int x = threadIdx.x; x < hh; x += kWave) cp += own_ac[x];
+            cp = wave_sum(cp);
+            if (threadIdx.x == 0) sm.misc[M_CAPP] = cp;
+        }
+    }
     for (int it = threadIdx.x; it < P * h; it += BS) {
         const int pc = it / h, e = it - pc * h;
         const int ed = sm.pk[pc].y, ev = ed & 0xffff, pv = ed >> 16, eg = w * h + e;
         int val = 0;
         if (eg != ev) {
-            const int *x = st.ea + eg * h, *y = st.ea + ev * h, *T = sm.tabT + pc * h;
+            const int *x = own_ea + e * h, *y = sm.peerE + pc * h, *T = sm.tabT + pc * h;
             const int lim = pv != w ? 0 : kBig;
             for (int a = 0; a < h; ++a) val = max(val, min(min(x[a], y[a]), max(T[a], lim)));
         }
-        sm.tabE[pc * h + e] = val;
+        sm.tabE[it] = val;
     }
     __syncthreads();
     // ---- C: criteria of the pod's servers
+    const int capP_own = sm.misc[M_CAPP];
     for (int x = threadIdx.x; x < hh; x += BS) {
         const int u = ubase + x;
-        const int up_u = st.up[u], el = edge_of(t, x), eu = w * h + el;
+        const int up_u = own_up[x], el = edge_of(t, x), eu = w * h + el;
+        const int cpu_u = sm.own[x], ram_u = sm.own[hh + x];
         int pbw_acc = up_u, up_acc = 0, hop_acc = 0, oute = 0, outp = 0;
-        int feas = (st.cpu[u] >= s.cpu) & (st.ram[u] >= s.ram);
+        int feas = (cpu_u >= s.cpu) & (ram_u >= s.ram);
         for (int pc = 0; pc < P; ++pc) {
             const int4 pk = sm.pk[pc];
             const int v = pk.x, bw = pk.z, ev = pk.y & 0xffff, pv = pk.y >> 16;
@@ -321,16 +361,15 @@ __device__ __forceinline__ int grid_criteria(const Topo &t, const State &st, con
         if (P > 0 && !m.route_end) feas &= (sm.capE[el] >= oute) & (capP_own >= outp);
         emit(x, feas, [&](int c) -> int {
             switch (crit_at<CS>(m, c)) {
-            case CRIT_CPU: return st.cpu[u];
-            case CRIT_RAM: return st.ram[u];
-            case CRIT_ACTIVE: return st.npl[u] > 0 ? 1 : 0;
+            case CRIT_CPU: return cpu_u;
+            case CRIT_RAM: return ram_u;
+            case CRIT_ACTIVE: return sm.own[2 * hh + x] > 0 ? 1 : 0;
             case CRIT_PATHBW: return pbw_acc;
             case CRIT_UPLINK: return up_u;
             default: return hop_acc;
             }
         });
     }
-    return capP_own;
 }
 
 // Peer-side deficits (server uplink, edge switch, pod) as in the
@@ -375,11 +414,13 @@ __device__ __forceinline__ bool deficits_allow(const Topo &t, const Deficits &d,
 // retries).  key_of(x): the score key of the pod's server x, 0 when it is
 // no candidate (feas[x] == 0 masks it); a workgroup without a pod (nx = 0)
 // only follows.  Returns false when the request was rejected at this
-// container, or a wait failed.
+// container, or a wait failed.  stale: whether this pod's residuals may have
+// changed.  A commit changes those of the chosen server's pod and of the
+// peers' pods, a rollback or the routing at a request's end any.
 template <int BS, class KeyFn>
 __device__ __forceinline__ bool grid_select(const Topo &t, const State &st, const Method &m, const Batch &b,
                                             const GSmem &sm, const GridCtl &g, long long timeout, const StepIn &s,
-                                            const ReqView &rv, unsigned &rnd, int nx, int *feas, KeyFn key_of) {
+                                            const ReqView &rv, unsigned &rnd, bool &stale, int nx, int *feas, KeyFn key_of) {
     const int w = blockIdx.x, G = gridDim.x, ubase = w * t.hh, P = s.P;
     const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
     // the workgroup's best key (largest packed key) into LDS slot 0..1
@@ -396,17 +437,18 @@ __device__ __forceinline__ bool grid_select(const Topo &t, const State &st, cons
             sm.wst[kMaxWaves + wid] = static_cast<int>(low);
         }
         __syncthreads();
-        if (threadIdx.x == 0) {
-            unsigned long long best = 0;
-            for (int x = 0; x < BS / kWave; ++x) {
-                const unsigned long long k = (static_cast<unsigned long long>(static_cast<unsigned>(sm.wst[x])) << 32) |
-                                             static_cast<unsigned>(sm.wst[kMaxWaves + x]);
-                best = k > best ? k : best;
-            }
-            *reinterpret_cast<unsigned long long *>(sm.misc + M_KEY) = round_key(best);
+        if (threadIdx.x < kWave) {
+            const unsigned hi = lane < BS / kWave ? static_cast<unsigned>(sm.wst[lane]) : 0u;
+            const unsigned lo = lane < BS / kWave ? static_cast<unsigned>(sm.wst[kMaxWaves + lane]) : 0u;
+            hiw = wave_umax(hi);
+            low = wave_umax(hi == hiw ? lo : 0u);
+            if (lane == 0)
+                *reinterpret_cast<unsigned long long *>(sm.misc + M_KEY) =
+                    round_key((static_cast<unsigned long long>(hiw) << 32) | low);
         }
     };
     wg_best();
+    stale = true;                              // until the container is placed
     for (;;) {
         const unsigned r = rnd++;
         if (threadIdx.x == 0)
@@ -467,6 +509,8 @@ __device__ __forceinline__ bool grid_select(const Topo &t, const State &st, cons
         if (ok < 0 || ok == 2) return false;
         if (ok) {
             if (rv.hosts_out && threadIdx.x == 0) rv.hosts_out[s.i] = u;
+            stale = (m.route_end && s.i == s.n - 1) || pod_of(t, u) == w ||
+                    __any(lane < P && (sm.pk[lane].y >> 16) == w);
             __syncthreads();
             return true;
         }
@@ -485,7 +529,7 @@ __device__ __forceinline__ bool grid_select(const Topo &t, const State &st, cons
 template <int BS, int CS = 0>
 __device__ __forceinline__ bool grid_topsis_step(const Topo &t, const State &st, const Method &m, const Batch &b,
                                                  const GSmem &sm, const GridCtl &g, long long timeout, const StepIn &s,
-                                                 const ReqView &rv, const Trace &tr, unsigned &rnd) {
+                                                 const ReqView &rv, const Trace &tr, unsigned &rnd, bool &stale) {
     const int w = blockIdx.x, G = gridDim.x, h = t.h, hh = t.hh, nc = crit_count<CS>(m);
     const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
     const int P = s.P, ubase = w * hh;
@@ -501,7 +545,7 @@ __device__ __forceinline__ bool grid_topsis_step(const Topo &t, const State &st,
     int mx[kMaxCrit], mn[kMaxCrit];
 #pragma unroll
     for (int c = 0; c < kMaxCrit; ++c) { s2[c] = 0; mx[c] = -kBig - 1; mn[c] = kBig; }
-    const int capP_own = grid_criteria<BS, CS>(t, st, m, sm, s, rv, [&](int x, int f, auto get) {
+    grid_criteria<BS, CS>(t, st, m, sm, s, rv, stale, [&](int x, int f, auto get) {
         xs[nc * hh + x] = f;
 #pragma unroll
         for (int c = 0; c < kMaxCrit; ++c) {
@@ -536,7 +580,7 @@ __device__ __forceinline__ bool grid_topsis_step(const Topo &t, const State &st,
     }
     for (int e = threadIdx.x; e < h; e += BS) rec_put(g, w, kRecCapE + e, stag, sm.capE[e]);
     if (threadIdx.x == 0) {
-        rec_put(g, w, kRecCapP, stag, capP_own);
+        rec_put(g, w, kRecCapP, stag, sm.misc[M_CAPP]);
         if (w == 0) rec_put(g, 0, kRecTrace, stag, my_slot);
     }
     // ---- D: block totals, peer-side deficits, scores, workgroup best
@@ -616,7 +660,7 @@ __device__ __forceinline__ bool grid_topsis_step(const Topo &t, const State &st,
         for (int x = threadIdx.x; x < hh; x += BS)
             tr.scores[static_cast<size_t>(slot) * t.N + ubase + x] =
                 topsis_close(nc, [&](int c) { return xs[c * hh + x]; }, q, ap, am);
-    return grid_select<BS>(t, st, m, b, sm, g, timeout, s, rv, rnd, hh, xs + nc * hh, key_of);
+    return grid_select<BS>(t, st, m, b, sm, g, timeout, s, rv, rnd, stale, hh, xs + nc * hh, key_of);
 }
 
 }  // namespace dcs
@@ -643,7 +687,8 @@ __global__ __launch_bounds__(BS) void k_topsis_grid(Params p, GridCtl g, long lo
     const Topo t = topo_of<K>(p.t);
     const GSmem sm = gcarve(dsm, t.h, t.hh, crit_count<CS>(p.m));
     unsigned rnd = __hip_atomic_load(g.round, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    grid_topsis_step<BS, CS>(t, p.st, p.m, p.b, sm, g, timeout, p.s, plain_view(p), p.tr, rnd);
+    bool stale = true;
+    grid_topsis_step<BS, CS>(t, p.st, p.m, p.b, sm, g, timeout, p.s, plain_view(p), p.tr, rnd, stale);
     if (blockIdx.x == 0 && threadIdx.x == 0) __hip_atomic_store(g.round, rnd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -664,6 +709,7 @@ __global__ __launch_bounds__(BS) void k_serve_grid(Params p, ServeArgs a, GridCt
     const bool lead = blockIdx.x == 0;
     int pos = a.start;
     unsigned rnd = __hip_atomic_load(g.round, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // selection rounds
+    bool stale = true;
     long long idle0 = dev_clock();
     for (;;) {
         if (lead && threadIdx.x == 0) {
@@ -734,13 +780,14 @@ __global__ __launch_bounds__(BS) void k_serve_grid(Params p, ServeArgs a, GridCt
                 const int q0 = rq_poff[i];
                 const StepIn s{0, i, n, 0, i, q0, rq_poff[i + 1] - q0, rq_cpu[i], rq_ram[i], rq_cmax[i], rq_rmax[i]};
                 const ReqView rv{rq_pj + q0, rq_pbw + q0, rq_host, rq_host, rq_pbmax + q0, rq_poff, rq_pj, true};
-                if (!grid_topsis_step<BS, CS>(t, p.st, p.m, b, sm, g, timeout, s, rv, p.tr, rnd)) {
+                if (!grid_topsis_step<BS, CS>(t, p.st, p.m, b, sm, g, timeout, s, rv, p.tr, rnd, stale)) {
                     fault = __hip_atomic_load(g.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
                     break;
                 }
             }
-        } else if (lead) {
-            give_back<BS>(t, p.st, b, 0, n);         // departure of an accepted request
+        } else {
+            if (lead) give_back<BS>(t, p.st, b, 0, n);         // departure of an accepted request
+            stale = true;
         }
         if (fault) break;
         if (lead) {

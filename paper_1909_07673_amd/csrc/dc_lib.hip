@@ -334,7 +334,7 @@ struct dc_ctx {
     unsigned epoch = 0;            // launches of the queue kernel
     long long patience = 2000000LL;        // 20 ms of device clock for its workgroups to meet
     AhpGrid ahp{};
-    unsigned long long *d_words = nullptr; // its value and rank words
+    unsigned long long *d_words = nullptr; // its value, column and rank words
     int *h_ctl = nullptr;          // pinned: err, round, join[2] after a launch
     hipError_t launch_err = hipSuccess;    // first failed cooperative launch of a run
     hipStream_t cap_stream = nullptr;      // graph capture (batched form)
@@ -863,7 +863,7 @@ int collect(dc_ctx *ctx, DevBatch &b) {
 
 // ---------------------------------------------------------------- cooperative step
 int grid_alloc(dc_ctx *ctx, int G) {
-    // count, gen, err, round, join[2], flag[kGridFlags], then 8-byte aligned: kslot[2][G], rflag, rec[k][kRecWords]
+    // count, gen, err, round, join[2], flag[kGridFlags], then 8-byte aligned: kslot[2][G], rflag, rec[kRecWords][k]
     const size_t ints = 6 + kGridFlags + 2 + 2 * (2 * (size_t)G + 1 + (size_t)ctx->t.k * kRecWords);
     HIPCHK(hipMalloc(&ctx->d_grid, ints * sizeof(int)));
     hipLaunchKernelGGL(k_fill_i32, dim3(16), dim3(256), 0, ctx->stream, ctx->d_grid, 0, (long long)ints);
@@ -881,6 +881,7 @@ int grid_alloc(dc_ctx *ctx, int G) {
     g.kslot = reinterpret_cast<unsigned long long *>(k);
     g.rflag = g.kslot + 2 * G;
     g.rec = g.rflag + 1;
+    g.pods = ctx->t.k;
     return DC_OK;
 }
 
@@ -941,12 +942,13 @@ int queue_init(dc_ctx *ctx) {
         ctx->queue_wgs = std::max(k, nc * ((ctx->N + kAhpQueueBlock - 1) / kAhpQueueBlock));
         if (ctx->queue_wgs > kWave) return DC_OK;
         if (set_lds(ctx, k_ahp_queue<kAhpQueueBlock>, ctx->lds_queue)) return DC_EDEVICE;
-        const size_t words = 2 * (size_t)nc * ctx->N;
+        const size_t words = 3 * (size_t)nc * ctx->N;
         HIPCHK(hipMalloc(&ctx->d_words, words * sizeof(unsigned long long)));
         hipLaunchKernelGGL(k_fill_i32, dim3(64), dim3(256), 0, ctx->stream, reinterpret_cast<int *>(ctx->d_words), 0,
                            2 * (long long)words);
         ctx->ahp.xw = ctx->d_words;
-        ctx->ahp.lw = ctx->d_words + (size_t)nc * ctx->N;
+        ctx->ahp.zw = ctx->d_words + (size_t)nc * ctx->N;
+        ctx->ahp.lw = ctx->d_words + 2 * (size_t)nc * ctx->N;
         ctx->queue = dc_ctx::QUEUE_AHP;
     }
     HIPCHK(hipHostMalloc(reinterpret_cast<void **>(&ctx->h_ctl), 4 * sizeof(int), 0));

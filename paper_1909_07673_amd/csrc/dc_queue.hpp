@@ -128,8 +128,9 @@ __global__ __launch_bounds__(BS) void k_topsis_queue(Params p, GridCtl g, unsign
     if (!queue_join(g.join, epoch, patience, sm.misc + M_OK)) return;
     const QueueReq q = queue_req(grid_req_lds(dsm, t.h, t.hh, crit_count<CS>(p.m)));
     unsigned rnd = __hip_atomic_load(g.round, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    bool stale = true;
     walk_queue<BS>(p.b, q, g, sm.misc + M_OK, [&](const StepIn &s, const ReqView &rv) {
-        return grid_topsis_step<BS, CS>(t, p.st, p.m, p.b, sm, g, timeout, s, rv, p.tr, rnd);
+        return grid_topsis_step<BS, CS>(t, p.st, p.m, p.b, sm, g, timeout, s, rv, p.tr, rnd, stale);
     });
     if (blockIdx.x == 0 && threadIdx.x == 0) __hip_atomic_store(g.round, rnd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -139,13 +140,14 @@ __global__ __launch_bounds__(BS) void k_topsis_queue(Params p, GridCtl g, unsign
 // its servers' criteria; C * S of them, S per criterion, turn a criterion's
 // values over all servers into its local ranks (section V-B); the pods then
 // sum their servers' global priorities, and the selection rounds follow.
-// The values and the ranks travel as 64-bit words, the 32-bit value under
+// The values, column sums and ranks travel as 64-bit words, the 32-bit value under
 // the step's tag (rec_tag), each waited for by whoever needs it.  A word of
 // the next step is written only after this step's last selection round,
 // whose outcome needs every pod's key, which needs every rank word, which
 // needs every value word; so none is overwritten before it is read.
 struct AhpGrid {
     unsigned long long *xw;   // [C][N] criterion values
+    unsigned long long *zw;   // [C][N] column sums (x 2520)
     unsigned long long *lw;   // [C][N] row sums of the column-normalised matrix (FP32)
     int vmax[kMaxCrit];       // largest value of each criterion, from the capacities
     int fbytes;               // LDS of the position table, 16-byte multiple
@@ -160,7 +162,7 @@ __device__ __forceinline__ int swz(int q) { return q ^ ((q >> 3) & 7); }
 __host__ __device__ inline int ahp_p_slots(int N) { return (N + 8) & ~7; }
 
 struct AhpSmem {
-    GSmem g;              // pk, wst, misc, capE, tabT, tabE (over F), xs: feasibility row, then global priorities
+    GSmem g;              // tables over F; xs: feasibility row, then global priorities
     QueueReq q;
     double *scan;         // [kMaxWaves]
     unsigned *F;          // [(V + 3) / 2] positions, 16 bits each
@@ -168,11 +170,11 @@ struct AhpSmem {
 };
 
 __host__ __device__ inline size_t ahp_fixed_ints(int h, int hh) {
-    return 4 * (size_t)kMaxN + kStatFields * kMaxWaves + M_MISC + align4(h) + align4(2 * (size_t)hh) + kQueueReqInts +
+    return 4 * (size_t)kMaxN + kStatFields * kMaxWaves + M_MISC + own_ints(h, hh) + align4(2 * (size_t)hh) + kQueueReqInts +
            2 * kMaxWaves;
 }
 inline size_t ahp_queue_lds(int h, int hh, int N, int fbytes) {
-    const size_t tables = 2 * align4((size_t)kMaxN * h) * sizeof(int);
+    const size_t tables = tab_ints(h) * sizeof(int);
     return ahp_fixed_ints(h, hh) * sizeof(int) + std::max<size_t>(tables, (size_t)fbytes + sizeof(double) * ahp_p_slots(N));
 }
 __device__ inline AhpSmem ahp_carve(char *base, int h, int hh, int fbytes) {
@@ -181,41 +183,65 @@ __device__ inline AhpSmem ahp_carve(char *base, int h, int hh, int fbytes) {
     int *p = reinterpret_cast<int *>(base) + 4 * kMaxN;
     s.g.wst = p; p += kStatFields * kMaxWaves;
     s.g.misc = p; p += M_MISC;
+    s.g.own = p; p += align4(6 * (size_t)hh);
     s.g.capE = p; p += align4(h);
     s.g.xs = p; p += align4(2 * (size_t)hh);
     s.q = queue_req(p); p += kQueueReqInts;
     s.scan = reinterpret_cast<double *>(p); p += 2 * kMaxWaves;
-    s.g.tabT = p;
-    s.g.tabE = p + align4((size_t)kMaxN * h);
-    s.g.pcap = nullptr;
+    (void)carve_tabs(s.g, p, h);
     s.F = reinterpret_cast<unsigned *>(p);
     s.P = reinterpret_cast<double *>(reinterpret_cast<char *>(p) + fbytes);
     return s;
 }
 
-// Exclusive scan of one value per thread over the block; ends with a
-// barrier.  total: the block's sum.
+// DPP moves and lane reads of a 32- or 64-bit value.
+template <int CTRL, int ROWS, class T>
+__device__ __forceinline__ T dpp_zero(T v) {
+    if constexpr (sizeof(T) == 4) {
+        return __builtin_bit_cast(T, dpp<CTRL, ROWS>(0, __builtin_bit_cast(int, v)));
+    } else {
+        const long long x = __builtin_bit_cast(long long, v);
+        const unsigned lo = dpp<CTRL, ROWS>(0, static_cast<int>(x)), hi = dpp<CTRL, ROWS>(0, static_cast<int>(x >> 32));
+        return __builtin_bit_cast(T, static_cast<long long>((static_cast<unsigned long long>(hi) << 32) | lo));
+    }
+}
+template <class T>
+__device__ __forceinline__ T read_lane(T v, int lane) {
+    if constexpr (sizeof(T) == 4) {
+        return __builtin_bit_cast(T, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
+    } else {
+        const long long x = __builtin_bit_cast(long long, v);
+        const unsigned lo = __builtin_amdgcn_readlane(static_cast<int>(x), lane);
+        const unsigned hi = __builtin_amdgcn_readlane(static_cast<int>(x >> 32), lane);
+        return __builtin_bit_cast(T, static_cast<long long>((static_cast<unsigned long long>(hi) << 32) | lo));
+    }
+}
+
+// Exclusive scan of one value per thread over the block, total its sum: a
+// DPP scan of each wave, the wave sums through LDS (slots: one per wave) and
+// one more DPP scan of them in every wave.  One barrier; slots must not be
+// written again before another.
 template <int BS, class T>
 __device__ __forceinline__ T block_scan(T v, T *slots, T &total) {
-    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+    static_assert(BS / kWave <= 16, "the wave sums are scanned within one DPP row");
+    const int lane = threadIdx.x & (kWave - 1), wid = uniform(threadIdx.x / kWave);
     T inc = v;
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const T o = __shfl_up(inc, d);
-        if (lane >= d) inc += o;
-    }
+    inc += dpp_zero<0x111, 0xf>(inc);
+    inc += dpp_zero<0x112, 0xf>(inc);
+    inc += dpp_zero<0x114, 0xf>(inc);
+    inc += dpp_zero<0x118, 0xf>(inc);
+    inc += dpp_zero<0x142, 0xa>(inc);
+    inc += dpp_zero<0x143, 0xc>(inc);
     if (lane == kWave - 1) slots[wid] = inc;
     __syncthreads();
-    T before = 0;
-    total = 0;
-#pragma unroll
-    for (int x = 0; x < BS / kWave; ++x) {
-        const T o = slots[x];
-        before += x < wid ? o : T(0);
-        total += o;
-    }
-    __syncthreads();
-    return before + inc - v;
+    T w = lane < BS / kWave ? slots[lane] : T(0);
+    w += dpp_zero<0x111, 0xf>(w);
+    w += dpp_zero<0x112, 0xf>(w);
+    w += dpp_zero<0x114, 0xf>(w);
+    w += dpp_zero<0x118, 0xf>(w);
+    total = read_lane(w, BS / kWave - 1);
+    const T before = wid ? read_lane(w, wid - 1) : T(0);
+    return before + (inc - v);
 }
 
 // The bounds of saaty_buckets for a value v, looked up: at(t) is the number
@@ -238,6 +264,40 @@ __device__ __forceinline__ SaatyBuckets saaty_positions(int v, int V, int n, At 
     return b;
 }
 
+// Thread: the 32-bit values of the tagged words at(e) for every e of the bits
+// of todo, once each carries the tag; only the words still missing are read
+// again.  False when the wait timed out or a workgroup reported an error.
+template <int E, class At>
+__device__ __forceinline__ bool words_get(const GridCtl &g, unsigned todo, At at, unsigned long long tag,
+                                          long long timeout, int (&v)[E]) {
+    const long long t0 = dev_clock();
+    while (todo) {
+        unsigned long long w[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            if (todo >> e & 1) w[e] = __hip_atomic_load(at(e), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            if ((todo >> e & 1) && rec_has(w[e], tag)) {
+                v[e] = static_cast<int>(static_cast<unsigned>(w[e]));
+                todo &= ~(1u << e);
+            }
+        if (!todo) break;
+        if (__hip_atomic_load(g.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) || dev_clock() - t0 > timeout) {
+            __hip_atomic_store(g.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return false;
+        }
+        __builtin_amdgcn_s_sleep(1);
+    }
+    return true;
+}
+
+// Servers from which a criterion's column sums are shared out over its
+// slices: each thread then computes one and reads the others' from their
+// words, which costs one more exchange (about 2 us) and saves 1.1 us per
+// column the thread would take otherwise.
+constexpr int kAhpSplitColumns = 3 * kAhpQueueBlock;
+
 // Local ranks of criterion c for slice s of S (servers [s R, (s + 1) R)).
 // A criterion's values are bounded by its capacity, so counting takes the
 // place of a sort: F[t], the number of servers with a value below t, from a
@@ -257,7 +317,7 @@ __device__ __forceinline__ bool ahp_local_rank(const AhpSmem &sm, const AhpGrid 
     // few values would meet on few LDS words: their histogram takes several
     // copies, in the space of P
     const int slots = 2 * ahp_p_slots(N);
-    int lg = 5;
+    int lg = 3;
     while (lg > 0 && ((V + 1) << lg) > slots) --lg;
     const bool copies = lg >= 2;
     // clear, while the values come in
@@ -267,55 +327,41 @@ __device__ __forceinline__ bool ahp_local_rank(const AhpSmem &sm, const AhpGrid 
     } else {
         for (int x = tid; x < fw; x += BS) sm.F[x] = 0;
     }
-    // the values: server e * BS + tid in v[e], this slice's row in mine
+    // the values: server e * BS + tid in v[e], this slice's row in v[E]
     const int R = (N + S - 1) / S, row = s * R + tid;
     const bool has_row = tid < R && row < N;
-    int v[E], mine = 0;
-    unsigned todo = has_row ? 1u << E : 0u;
+    int v[E + 1] = {};
+    unsigned mine = 0;
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-        v[e] = 0;
-        if (e * BS + tid < N) todo |= 1u << e;
-    }
-    const long long t0 = dev_clock();
-    bool bad = false;
-    while (todo) {
-        unsigned long long w[E + 1];
-#pragma unroll
-        for (int e = 0; e <= E; ++e)
-            if (todo >> e & 1)
-                w[e] = __hip_atomic_load(xw + (e < E ? e * BS + tid : row), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-        for (int e = 0; e <= E; ++e)
-            if ((todo >> e & 1) && rec_has(w[e], tag)) {
-                if (e < E) v[e] = static_cast<int>(static_cast<unsigned>(w[e]));
-                else mine = static_cast<int>(static_cast<unsigned>(w[e]));
-                todo &= ~(1u << e);
-            }
-        if (!todo) break;
-        if (__hip_atomic_load(g.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) || dev_clock() - t0 > timeout) {
-            __hip_atomic_store(g.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            bad = true;
-            break;
-        }
-        __builtin_amdgcn_s_sleep(1);
-    }
+    for (int e = 0; e < E; ++e) mine |= e * BS + tid < N ? 1u << e : 0u;
+    bool bad = !words_get<E + 1>(g, mine | (has_row ? 1u << E : 0u),
+                                 [&](int e) { return xw + (e < E ? e * BS + tid : row); }, tag, timeout, v);
     if (bad) sm.g.misc[M_OK] = 1;
     __syncthreads();
     if (sm.g.misc[M_OK]) return false;
-    // histogram
+    // histogram; where a wave's values repeat (path bandwidths capped by one
+    // peer's uplink), the servers with its first lane's value count as one
 #pragma unroll
-    for (int e = 0; e < E; ++e)
-        if (e * BS + tid < N) {
-            if (copies) atomicAdd(H + (v[e] << lg) + (tid & ((1 << lg) - 1)), 1u);
-            else atomicAdd(sm.F + (v[e] >> 1), 1u << (16 * (v[e] & 1)));
+    for (int e = 0; e < E; ++e) {
+        if (e * BS >= N) break;
+        const bool in = e * BS + tid < N;
+        if (copies) {
+            if (in) atomicAdd(H + (v[e] << lg) + (tid & ((1 << lg) - 1)), 1u);
+        } else {
+            const int v0 = uniform(v[e]);
+            const bool same = in && v[e] == v0;
+            const unsigned long long m = __ballot(same);
+            const bool first = same && (tid & (kWave - 1)) == __builtin_ctzll(m);
+            const unsigned cnt = first ? static_cast<unsigned>(__builtin_popcountll(m)) : 1u;
+            if (in && (!same || first)) atomicAdd(sm.F + (v[e] >> 1), cnt << (16 * (v[e] & 1)));
         }
+    }
     __syncthreads();
     if (copies) {
         for (int x = tid; x < 2 * fw; x += BS) {
             unsigned cnt = 0;
             if (x <= V)
-                for (int y = 0; y < 1 << lg; ++y) cnt += H[(x << lg) + y];
+                for (int y = 0; y < 1 << lg; ++y) cnt += H[(x << lg) + ((y + tid) & ((1 << lg) - 1))];
             F16[x] = static_cast<unsigned short>(cnt);
         }
         __syncthreads();
@@ -325,50 +371,81 @@ __device__ __forceinline__ bool ahp_local_rank(const AhpSmem &sm, const AhpGrid 
     // threads' runs start in different banks
     {
         const int per = ((fw + BS - 1) / BS) | 1, w0 = min(fw, tid * per), w1 = min(fw, w0 + per);
+        constexpr int U = 8;                           // words in flight
         int sum = 0;
-        for (int x = w0; x < w1; ++x) {
-            const unsigned o = sm.F[x];
-            sum += static_cast<int>((o & 0xffffu) + (o >> 16));
+        for (int x = w0; x < w1; x += U) {
+            unsigned o[U];
+#pragma unroll
+            for (int j = 0; j < U; ++j) o[j] = x + j < w1 ? sm.F[x + j] : 0u;
+#pragma unroll
+            for (int j = 0; j < U; ++j) sum += static_cast<int>((o[j] & 0xffffu) + (o[j] >> 16));
         }
         int total;
-        int at = block_scan<BS>(sum, reinterpret_cast<int *>(sm.scan), total);
-        for (int x = w0; x < w1; ++x) {
-            const unsigned o = sm.F[x];
-            const unsigned lo = at, hi = at + (o & 0xffffu);
-            sm.F[x] = lo | hi << 16;
-            at = static_cast<int>(hi + (o >> 16));
+        unsigned at = block_scan<BS>(sum, reinterpret_cast<int *>(sm.scan), total);
+        for (int x = w0; x < w1; x += U) {
+            unsigned o[U];
+#pragma unroll
+            for (int j = 0; j < U; ++j) o[j] = x + j < w1 ? sm.F[x + j] : 0u;
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                const unsigned hi = at + (o[j] & 0xffffu);
+                if (x + j < w1) sm.F[x + j] = at | hi << 16;
+                at = hi + (o[j] >> 16);
+            }
         }
     }
     __syncthreads();
     auto F = [&](int t) { return static_cast<int>(F16[t]); };
     // 1 / column sum, times the number of servers with the value, at the
     // value's first position (servers of equal value write the same)
-#pragma unroll
-    for (int e = 0; e < E; ++e)
-        if (e * BS + tid < N) {
-            const SaatyBuckets b = saaty_positions(v[e], V, N, F);
-            const int cs = saaty_sum<int>(b, N, cost, [](int lo, int hi) { return hi - lo; });
-            sm.P[swz(b.lv)] = static_cast<double>(b.uv - b.lv) / static_cast<double>(cs);
+    SaatyBuckets rb;
+    if (N > kAhpSplitColumns) {
+        unsigned long long *zw = a.zw + static_cast<size_t>(c) * N;
+        if (has_row) {
+            rb = saaty_positions(v[E], V, N, F);
+            const int cs = saaty_sum<int>(rb, N, cost, [](int lo, int hi) { return hi - lo; });
+            __hip_atomic_store(zw + row, tag | static_cast<unsigned>(cs), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
+        int z[E];
+        bad = !words_get<E>(g, mine, [&](int e) { return zw + e * BS + tid; }, tag, timeout, z);
+        if (bad) sm.g.misc[M_OK] = 1;
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            if (!bad && e * BS + tid < N) {
+                const int lv = F(v[e]);
+                sm.P[swz(lv)] = static_cast<double>(F(v[e] + 1) - lv) / static_cast<double>(z[e]);
+            }
+    } else {
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            if (e * BS + tid < N) {
+                const SaatyBuckets b = saaty_positions(v[e], V, N, F);
+                const int cs = saaty_sum<int>(b, N, cost, [](int lo, int hi) { return hi - lo; });
+                sm.P[swz(b.lv)] = static_cast<double>(b.uv - b.lv) / static_cast<double>(cs);
+            }
+        rb = saaty_positions(v[E], V, N, F);
+    }
     __syncthreads();
+    if (sm.g.misc[M_OK]) return false;
     // prefix sums
     {
         const int per = (N + BS - 1) / BS, q0 = min(N, tid * per), q1 = min(N, q0 + per);
-        double sum = 0.0;
-        for (int x = q0; x < q1; ++x) sum += sm.P[swz(x)];
-        double total;
+        double d[E], sum = 0.0, total;
+#pragma unroll
+        for (int j = 0; j < E; ++j) d[j] = q0 + j < q1 ? sm.P[swz(q0 + j)] : 0.0;
+#pragma unroll
+        for (int j = 0; j < E; ++j) sum += d[j];
         double at = block_scan<BS>(sum, sm.scan, total);
-        for (int x = q0; x < q1; ++x) {
-            const double d = sm.P[swz(x)];
-            sm.P[swz(x)] = at;
-            at += d;
+#pragma unroll
+        for (int j = 0; j < E; ++j) {
+            if (q0 + j < q1) sm.P[swz(q0 + j)] = at;
+            at += d[j];
         }
         if (tid == 0) sm.P[swz(N)] = total;
     }
     __syncthreads();
     if (has_row) {
-        const SaatyBuckets b = saaty_positions(mine, V, N, F);
-        const double r = saaty_sum<double>(b, N, !cost, [&](int lo, int hi) { return sm.P[swz(hi)] - sm.P[swz(lo)]; });
+        const double r = saaty_sum<double>(rb, N, !cost, [&](int lo, int hi) { return sm.P[swz(hi)] - sm.P[swz(lo)]; });
         __hip_atomic_store(a.lw + static_cast<size_t>(c) * N + row, tag | __float_as_uint(static_cast<float>(r)),
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -378,7 +455,7 @@ __device__ __forceinline__ bool ahp_local_rank(const AhpSmem &sm, const AhpGrid 
 template <int BS>
 __device__ __forceinline__ bool grid_ahp_step(const Params &p, const Topo &t, const AhpSmem &sm, const AhpGrid &a,
                                               const GridCtl &g, long long timeout, const StepIn &s, const ReqView &rv,
-                                              unsigned &rnd) {
+                                              unsigned &rnd, bool &stale) {
     const int w = blockIdx.x, h = t.h, hh = t.hh, nc = p.m.nc, N = t.N, ubase = w * hh, P = s.P;
     const bool pod = w < t.k;
     const unsigned long long tag = rec_tag(rnd);
@@ -390,7 +467,7 @@ __device__ __forceinline__ bool grid_ahp_step(const Params &p, const Topo &t, co
             if (s.i == 0) p.b.tsb[s.r] = dev_clock();
             if (p.tr.stride > 0) slot = trace_slot(p.tr, 0, p.b.rid[s.r], s.i);
         }
-        const int capP = grid_criteria<BS, 0>(t, p.st, p.m, sm.g, s, rv, [&](int x, int f, auto get) {
+        grid_criteria<BS, 0>(t, p.st, p.m, sm.g, s, rv, stale, [&](int x, int f, auto get) {
             feas[x] = f;
 #pragma unroll
             for (int c = 0; c < kMaxCrit; ++c) {
@@ -401,7 +478,7 @@ __device__ __forceinline__ bool grid_ahp_step(const Params &p, const Topo &t, co
         });
         for (int e = threadIdx.x; e < h; e += BS) rec_put(g, w, kRecCapE + e, tag, sm.g.capE[e]);
         if (threadIdx.x == 0) {
-            rec_put(g, w, kRecCapP, tag, capP);
+            rec_put(g, w, kRecCapP, tag, sm.g.misc[M_CAPP]);
             if (w == 0) rec_put(g, 0, kRecTrace, tag, slot);
         }
         __syncthreads();                                  // the tables make room for F
@@ -431,29 +508,13 @@ __device__ __forceinline__ bool grid_ahp_step(const Params &p, const Topo &t, co
         // global priorities of the pod's servers, as k_ahp_pg sums them
         const double invN = 1.0 / N;
         for (int x = threadIdx.x; x < hh; x += BS) {
-            unsigned long long l[kMaxCrit];
-            const long long t0 = dev_clock();
-            for (;;) {
-                bool ok = true;
-#pragma unroll
-                for (int q = 0; q < kMaxCrit; ++q)
-                    if (q < nc) {
-                        l[q] = __hip_atomic_load(a.lw + static_cast<size_t>(q) * N + ubase + x, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT);
-                        ok &= rec_has(l[q], tag);
-                    }
-                if (ok) break;
-                if (__hip_atomic_load(g.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) || dev_clock() - t0 > timeout) {
-                    __hip_atomic_store(g.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    bad = true;
-                    break;
-                }
-                __builtin_amdgcn_s_sleep(1);
-            }
+            int l[kMaxCrit] = {};
+            bad |= !words_get<kMaxCrit>(g, (1u << nc) - 1, [&](int q) { return a.lw + static_cast<size_t>(q) * N + ubase + x; },
+                                        tag, timeout, l);
             double sum = 0.0;
 #pragma unroll
             for (int q = 0; q < kMaxCrit; ++q)
-                if (q < nc) sum += p.p1[q] * (static_cast<double>(__uint_as_float(static_cast<unsigned>(l[q]))) * invN);
+                if (q < nc) sum += p.p1[q] * (static_cast<double>(__int_as_float(l[q])) * invN);
             pg[x] = static_cast<float>(sum);
             if (slot >= 0) p.tr.scores[static_cast<size_t>(slot) * N + ubase + x] = pg[x];
         }
@@ -462,7 +523,7 @@ __device__ __forceinline__ bool grid_ahp_step(const Params &p, const Topo &t, co
         if (sm.g.misc[M_OK]) return false;
     }
     const Deficits df = read_deficits(sm.g);
-    return grid_select<BS>(t, p.st, p.m, p.b, sm.g, g, timeout, s, rv, rnd, pod ? hh : 0, feas,
+    return grid_select<BS>(t, p.st, p.m, p.b, sm.g, g, timeout, s, rv, rnd, stale, pod ? hh : 0, feas,
                            [&](int x) -> unsigned long long {
                                if (!feas[x] || !(p.m.route_end || deficits_allow(t, df, w, x))) return 0ull;
                                return score_key(pg[x], ubase + x);
@@ -477,8 +538,9 @@ __global__ __launch_bounds__(BS) void k_ahp_queue(Params p, GridCtl g, AhpGrid a
     const AhpSmem sm = ahp_carve(dsm, t.h, t.hh, a.fbytes);
     if (!queue_join(g.join, epoch, patience, sm.g.misc + M_OK)) return;
     unsigned rnd = __hip_atomic_load(g.round, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    bool stale = true;
     walk_queue<BS>(p.b, sm.q, g, sm.g.misc + M_OK, [&](const StepIn &s, const ReqView &rv) {
-        return grid_ahp_step<BS>(p, t, sm, a, g, timeout, s, rv, rnd);
+        return grid_ahp_step<BS>(p, t, sm, a, g, timeout, s, rv, rnd, stale);
     });
     if (blockIdx.x == 0 && threadIdx.x == 0) __hip_atomic_store(g.round, rnd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
