@@ -16,7 +16,7 @@ namespace dcs {
 // Threads per pod workgroup.  The step is bound by memory latency and the
 // waits between workgroups, not by threads: 1024 threads measured no faster
 // than 256.
-constexpr int kGridBlock = 256;
+constexpr int kGridBlock = 512;
 
 // Cross-workgroup state, in device memory.
 struct GridCtl {
@@ -584,54 +584,49 @@ __device__ __forceinline__ bool grid_topsis_step(const Topo &t, const State &st,
         if (w == 0) rec_put(g, 0, kRecTrace, stag, my_slot);
     }
     // ---- D: block totals, peer-side deficits, scores, workgroup best
-    // One poll per thread of all it needs from the records, waiting until
-    // every word carries this step's tag: in every wave, lane x the
-    // statistics words of workgroup x (G <= 64; the lanes past G read
-    // workgroup 0's and count identities instead), and thread p < P (P <=
-    // 63) the capacity words of peer p's edge switch and pod (the other
-    // threads read their own pod's word in their place).
+    // One poll for all a wave needs from the records, until every word
+    // carries this step's tag: wave 0 takes the statistics, lane x those of
+    // workgroup x (G <= 64; the lanes past G read workgroup 0's and count
+    // identities instead), wave 1 the capacities of peer x's edge switch and
+    // pod (P <= 63).  The other waves wait at the barrier: with every wave
+    // polling, the polls of 48 workgroups held one another up (a step at
+    // 1,024 threads took 1.4 times as long as at 256).
     constexpr int NF = 5 * (CS ? CS : kMaxCrit);
-    const bool hp = static_cast<int>(threadIdx.x) < P;
-    const int4 me = hp ? sm.pk[threadIdx.x] : make_int4(-1, 0, 0, 0);
+    static_assert(BS >= 2 * kWave, "statistics and capacities are waited for by two waves");
+    float *fac = reinterpret_cast<float *>(sm.wst) + 4 * kMaxWaves;
     bool bad = false;
-    int fv[NF];
-    int cv[2];
-    {
-        int ww[NF + 2], wx[NF + 2], wv[NF + 2];
-        const int e = me.y & 0xffff, d = me.y >> 16;
-        ww[0] = hp ? e / h : w;
-        wx[0] = hp ? kRecCapE + e % h : kRecCapP;
-        ww[1] = hp ? d : w;
-        wx[1] = kRecCapP;
+    if (wid == 0) {
+        int ww[NF], wx[NF], fv[NF];
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
-            ww[2 + f] = lane < G ? lane : 0;
-            wx[2 + f] = f;
+            ww[f] = lane < G ? lane : 0;
+            wx[f] = f;
         }
-        bad = !rec_get(g, 2 + 5 * nc, ww, wx, stag, timeout, wv);
-        cv[0] = wv[0];
-        cv[1] = wv[1];
+        bad = !rec_get(g, 5 * nc, ww, wx, stag, timeout, fv);
 #pragma unroll
-        for (int f = 0; f < NF; ++f) fv[f] = lane < G ? wv[2 + f] : ((f % 5) < 3 ? 0 : -kBig - 1);
-    }
-    unsigned long long S2[kMaxCrit];
-    int MX[kMaxCrit], MN[kMaxCrit];
+        for (int c = 0; c < kMaxCrit; ++c) {
+            if (c >= nc || 5 * c >= NF) continue;
 #pragma unroll
-    for (int c = 0; c < kMaxCrit; ++c) {
-        S2[c] = 0;
-        MX[c] = MN[c] = 0;
-        if (c >= nc || 5 * c >= NF) continue;
-        int a0 = fv[5 * c], a1 = fv[5 * c + 1], a2 = fv[5 * c + 2], hi = fv[5 * c + 3], nlo = fv[5 * c + 4];
-        a0 = wave_sum(a0);
-        a1 = wave_sum(a1);
-        a2 = wave_sum(a2);
-        S2[c] = static_cast<unsigned long long>(static_cast<unsigned>(a0)) +
-                (static_cast<unsigned long long>(static_cast<unsigned>(a1)) << 17) +
-                (static_cast<unsigned long long>(static_cast<unsigned>(a2)) << 34);
-        MX[c] = wave_max(hi);
-        MN[c] = -wave_max(nlo);
+            for (int j = 0; j < 5; ++j) fv[5 * c + j] = lane < G ? fv[5 * c + j] : (j < 3 ? 0 : -kBig - 1);
+            const int a0 = wave_sum(fv[5 * c]), a1 = wave_sum(fv[5 * c + 1]), a2 = wave_sum(fv[5 * c + 2]);
+            const unsigned long long S2 = static_cast<unsigned long long>(static_cast<unsigned>(a0)) +
+                                          (static_cast<unsigned long long>(static_cast<unsigned>(a1)) << 17) +
+                                          (static_cast<unsigned long long>(static_cast<unsigned>(a2)) << 34);
+            const int hi = wave_max(fv[5 * c + 3]), lo = -wave_max(fv[5 * c + 4]);
+            if (lane == 0) {
+                fac[c] = S2 ? (m.w[c] * m.w[c]) / static_cast<float>(S2) : 0.0f;
+                fac[kMaxCrit + c] = static_cast<float>(crit_cost<CS>(m, c) ? lo : hi);
+                fac[2 * kMaxCrit + c] = static_cast<float>(crit_cost<CS>(m, c) ? hi : lo);
+            }
+        }
+    } else if (wid == 1 && lane < P) {
+        const int4 me = sm.pk[lane];
+        const int e = me.y & 0xffff, d = me.y >> 16;
+        const int ww[2] = {e / h, d}, wx[2] = {kRecCapE + e % h, kRecCapP};
+        int cv[2];
+        bad = !rec_get(g, 2, ww, wx, stag, timeout, cv);
+        grid_deficits(sm, P, me, cv[0], cv[1]);
     }
-    if (hp) grid_deficits(sm, P, me, cv[0], cv[1]);
     int slot = -1;
     if (tr.stride > 0) {
         const int zw[1] = {0}, zx[1] = {kRecTrace};
@@ -648,9 +643,9 @@ __device__ __forceinline__ bool grid_topsis_step(const Topo &t, const State &st,
     for (int c = 0; c < kMaxCrit; ++c) {
         q[c] = ap[c] = am[c] = 0.f;
         if (c >= nc) continue;
-        q[c] = S2[c] ? (m.w[c] * m.w[c]) / static_cast<float>(S2[c]) : 0.0f;
-        ap[c] = static_cast<float>(crit_cost<CS>(m, c) ? MN[c] : MX[c]);
-        am[c] = static_cast<float>(crit_cost<CS>(m, c) ? MX[c] : MN[c]);
+        q[c] = fac[c];
+        ap[c] = fac[kMaxCrit + c];
+        am[c] = fac[2 * kMaxCrit + c];
     }
     auto key_of = [&](int x) -> unsigned long long {
         if (!xs[nc * hh + x] || !(m.route_end || deficits_allow(t, df, w, x))) return 0ull;
