@@ -580,7 +580,9 @@ __host__ __device__ inline void ahp_p1(const Method &m, double *p1) {
 // L2_c[u], summing the row partials in fixed order.  Written as FP32 into
 // xs row nc + 1 (free once the criteria stage is done), and into the trace
 // when this step is recorded.
-__global__ __launch_bounds__(kAhpBlock) void k_ahp_pg(Params p) {
+// lsum, didx: the row sums by distinct value and each server's value's index,
+// instead of row partials (nullptr: none).
+__global__ __launch_bounds__(kAhpBlock) void k_ahp_pg(Params p, const double *lsum, const int *didx) {
     if (p.b.status[p.s.r] == 0) return;
     const int N = p.t.N, nc = p.m.nc;
     const int u = blockIdx.x * kAhpBlock + threadIdx.x;
@@ -589,7 +591,11 @@ __global__ __launch_bounds__(kAhpBlock) void k_ahp_pg(Params p) {
     double s = 0.0;
     for (int c = 0; c < nc; ++c) {
         double l = 0.0;
-        for (int jb = 0; jb < p.nJ; ++jb) l += p.rowpart[((size_t)c * p.nJ + jb) * N + u];
+        if (lsum) {
+            l = lsum[(size_t)c * N + didx[(size_t)c * N + u]];
+        } else {
+            for (int jb = 0; jb < p.nJ; ++jb) l += p.rowpart[((size_t)c * p.nJ + jb) * N + u];
+        }
         s += p.p1[c] * (l * invN);
     }
     const float v = static_cast<float>(s);

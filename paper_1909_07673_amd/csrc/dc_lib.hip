@@ -6,6 +6,7 @@
 #include "dc_kernels.hpp"
 #include "dc_grid.hpp"
 #include "dc_queue.hpp"
+#include "dc_ahp_large.hpp"
 #include "dc_tiles.hpp"
 
 #include <algorithm>
@@ -334,6 +335,10 @@ struct dc_ctx {
     unsigned epoch = 0;            // launches of the queue kernel
     long long patience = 2000000LL;        // 20 ms of device clock for its workgroups to meet
     AhpGrid ahp{};
+    bool ahp_large = false;        // AHP on the 1-9 scale past the sorted passes, by distinct value
+    AhpLarge large{};
+    void *d_large = nullptr;
+    size_t lds_count = 0;
     unsigned long long *d_words = nullptr; // its value, column and rank words
     int *h_ctl = nullptr;          // pinned: err, round, join[2] after a launch
     hipError_t launch_err = hipSuccess;    // first failed cooperative launch of a run
@@ -626,13 +631,22 @@ void launch_plain_step(dc_ctx *ctx, const Params &p) {
             }
             hipLaunchKernelGGL(k_ahp_sort_col, dim3(bx, 1, ctx->m.nc), dim3(kAhpBlock), 0, ctx->stream, q);
             hipLaunchKernelGGL(k_ahp_sort_row, dim3(bx, 1, ctx->m.nc), dim3(kAhpBlock), 0, ctx->stream, q);
-            hipLaunchKernelGGL(k_ahp_pg, dim3(bx), dim3(kAhpBlock), 0, ctx->stream, q);
+            hipLaunchKernelGGL(k_ahp_pg, dim3(bx), dim3(kAhpBlock), 0, ctx->stream, q, nullptr, nullptr);
             hipLaunchKernelGGL((k_ahp_select<BS>), dim3(1), dim3(BS), ctx->lds_select, ctx->stream, q);
+            ctx->last_launches += 6;
+        } else if (ctx->ahp_large) {
+            const AhpLarge &a = ctx->large;
+            hipLaunchKernelGGL(k_ahp_count, dim3((ctx->N + kAhpQueueBlock - 1) / kAhpQueueBlock, ctx->m.nc),
+                               dim3(kAhpQueueBlock), ctx->lds_count, ctx->stream, p, a);
+            hipLaunchKernelGGL(k_ahp_rows, dim3(a.first[ctx->m.nc]), dim3(kRowWaves * kWave), 0, ctx->stream, p, a);
+            hipLaunchKernelGGL(k_ahp_row_total, dim3(bx, ctx->m.nc), dim3(kAhpBlock), 0, ctx->stream, p, a);
+            hipLaunchKernelGGL(k_ahp_pg, dim3(bx), dim3(kAhpBlock), 0, ctx->stream, p, a.lsum, a.didx);
+            hipLaunchKernelGGL((k_ahp_select<BS>), dim3(1), dim3(BS), ctx->lds_select, ctx->stream, p);
             ctx->last_launches += 6;
         } else {
             hipLaunchKernelGGL(k_ahp_colsum, dim3(bx, ctx->nI, ctx->m.nc), dim3(kAhpBlock), 0, ctx->stream, p);
             hipLaunchKernelGGL(k_ahp_rowsum, dim3(bx, ctx->nJ, ctx->m.nc), dim3(kAhpBlock), 0, ctx->stream, p);
-            hipLaunchKernelGGL(k_ahp_pg, dim3(bx), dim3(kAhpBlock), 0, ctx->stream, p);
+            hipLaunchKernelGGL(k_ahp_pg, dim3(bx), dim3(kAhpBlock), 0, ctx->stream, p, nullptr, nullptr);
             hipLaunchKernelGGL((k_ahp_select<BS>), dim3(1), dim3(BS), ctx->lds_select, ctx->stream, p);
             ctx->last_launches += 5;
         }
@@ -908,6 +922,49 @@ TopsisQueueFn topsis_queue_fn(const dc_ctx *ctx) {
     return specialised(ctx, kGridK) ? k_topsis_queue<kGridBlock, kGridK> : k_topsis_queue<kGridBlock, 0>;
 }
 
+// Largest value criterion c can take: residuals stay within the capacities,
+// path bandwidth within the server's uplink, hops within six per peer.
+int crit_max(const dc_ctx *ctx, int c) {
+    const dc_config &cfg = ctx->cfg;
+    switch (ctx->m.crit[c]) {
+    case CRIT_CPU: return cfg.host_cpu;
+    case CRIT_RAM: return cfg.host_ram;
+    case CRIT_ACTIVE: return 1;
+    case CRIT_HOPS: return 6 * (kMaxN - 1);
+    default: return cfg.bw_host_edge;
+    }
+}
+
+// AHP on the 1-9 scale by distinct value, where the counts of a criterion's
+// values fit one workgroup's LDS (capacities up to some 75,000) and a count
+// 16 bits; otherwise the pairwise passes remain.
+int large_init(dc_ctx *ctx) {
+    const int N = ctx->N, nc = ctx->m.nc;
+    if (ctx->m.scale != DC_AHP_SAATY9 || ctx->ahp_sorted || N >= 1 << 16) return DC_OK;
+    AhpLarge &a = ctx->large;
+    int vmax = 0;
+    a.groups = (ctx->nJ + kRowWaves * kRowChunks - 1) / (kRowWaves * kRowChunks);
+    for (int c = 0; c < nc; ++c) {
+        a.vmax[c] = crit_max(ctx, c);
+        vmax = std::max(vmax, a.vmax[c]);
+        const int distinct = std::min(N, a.vmax[c] + 1);
+        const int block = a.vmax[c] < kRowFew ? kRowBlockFew : kRowBlock;
+        a.first[c + 1] = a.first[c] + (distinct + block - 1) / block * a.groups;
+    }
+    ctx->lds_count = large_count_lds(vmax);
+    if (vmax >= 1 << 17 || ctx->lds_count > kLdsMax) return DC_OK;
+    if (set_lds(ctx, k_ahp_count, ctx->lds_count)) return DC_EDEVICE;
+    const size_t n = (size_t)nc * N;
+    HIPCHK(hipMalloc(&ctx->d_large, n * (sizeof(double) + 3 * sizeof(int)) + kMaxCrit * sizeof(int)));
+    a.lsum = static_cast<double *>(ctx->d_large);
+    a.sinv = reinterpret_cast<float *>(a.lsum + n);
+    a.didx = reinterpret_cast<int *>(a.sinv + n);
+    a.dist = a.didx + n;
+    a.count = a.dist + n;
+    ctx->ahp_large = true;
+    return DC_OK;
+}
+
 // Which plain contexts run their queue in one launch over several
 // workgroups: one data center, left to the automatic choice (grid = 0 and no
 // block size asked for).  TOPSIS where the state does not fit one workgroup
@@ -928,11 +985,8 @@ int queue_init(dc_ctx *ctx) {
         if (!ctx->ahp_sorted) return DC_OK;
         int vmax = 0;
         for (int c = 0; c < nc; ++c) {
-            const int id = ctx->m.crit[c];
-            int &v = ctx->ahp.vmax[c];
-            v = id == CRIT_CPU ? cfg.host_cpu : id == CRIT_RAM ? cfg.host_ram : id == CRIT_ACTIVE ? 1
-              : id == CRIT_HOPS ? 6 * (kMaxN - 1) : cfg.bw_host_edge;
-            vmax = std::max(vmax, v);
+            ctx->ahp.vmax[c] = crit_max(ctx, c);
+            vmax = std::max(vmax, ctx->ahp.vmax[c]);
         }
         ctx->ahp.fbytes = ((vmax + 3) / 2 * 4 + 15) & ~15;
         ctx->lds_queue = ahp_queue_lds(h, hh, ctx->N, ctx->ahp.fbytes);
@@ -1633,6 +1687,10 @@ int dc_create(const dc_config *cfg, dc_ctx **out) {
         const int grc = grid_init(c);
         if (grc) { dc_destroy(ctx.release()); return grc; }
     }
+    if (cfg->method == DC_AHP && cfg->grid != 1) {
+        const int lrc = large_init(c);
+        if (lrc) { dc_destroy(ctx.release()); return lrc; }
+    }
     if (const int qrc = queue_init(c)) { dc_destroy(ctx.release()); return qrc; }
     if (cfg->mode == DC_MODE_SERVING) {
         if (I != 1) { dc_destroy(ctx.release()); return DC_EINVAL; }
@@ -2116,6 +2174,7 @@ void dc_destroy(dc_ctx *ctx) {
         if (ctx->d_rowpart) (void)hipFree(ctx->d_rowpart);
         if (ctx->d_wsort) (void)hipFree(ctx->d_wsort);
         if (ctx->d_words) (void)hipFree(ctx->d_words);
+        if (ctx->d_large) (void)hipFree(ctx->d_large);
         if (ctx->h_ctl) (void)hipHostFree(ctx->h_ctl);
         if (ctx->d_tscore) (void)hipFree(ctx->d_tscore);
     } else {

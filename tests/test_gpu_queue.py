@@ -163,3 +163,34 @@ def test_topsis_queue_two_calls_and_releases():
         for f in ("status", "failed_at", "host"):
             np.testing.assert_array_equal(a[f], b[f])
     np.testing.assert_array_equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("k,up,cost", [
+    (34, 40000, (0, 0, 0, 0, 1)),      # 9,826 servers: a chunk of 98 columns with a tail of two
+    (36, 1000, (1, 1, 1, 1, 0)),       # 11,664: few distinct values, other directions
+    (48, 40000, (0, 0, 0, 0, 1)),      # 27,648
+    (34, 90000, (0, 0, 0, 0, 1)),      # past the counting kernel: the pairwise passes on both sides
+])
+def test_ahp_large_matches_pairwise(k, up, cost):
+    """Row sums by distinct value against the pairwise passes (grid = 1): the
+    same FP32 terms in the same order, so every score vector is the same bit
+    for bit."""
+    rng = np.random.default_rng([k, up])
+    inst = make_instance(k, 32, 256, up, 100000, 100000, background=0.99 if up == 1000 else 0.7, rng=rng)
+    reqs = make_requests(2, rng, 4, 8, bw_lo=1, bw_hi=up // 20)
+    out = []
+    for grid in (0, 1):
+        s = dc.Scheduler([inst], method=dc.DC_AHP, crit=C5, cost=cost, grid=grid, trace_stride=1, trace_cap=16)
+        for r in reqs:
+            s.submit(r)
+        res = s.schedule_array()
+        meta, scores = s.trace()
+        out.append((res.copy(), meta, scores.view(np.uint32).copy(), s.state(0)))
+        s.close()
+    (a, ma, sa, ta), (b, mb, sb, tb) = out
+    np.testing.assert_array_equal(ma, mb)
+    assert len(ma) >= 4
+    np.testing.assert_array_equal(sa, sb)
+    for f in ("status", "failed_at", "host"):
+        np.testing.assert_array_equal(a[f], b[f])
+    np.testing.assert_array_equal(ta, tb)
