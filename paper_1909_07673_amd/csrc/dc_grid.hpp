@@ -417,7 +417,8 @@ __device__ __forceinline__ bool deficits_allow(const Topo &t, const Deficits &d,
 // container, or a wait failed.  stale: whether this pod's residuals may have
 // changed.  A commit changes those of the chosen server's pod and of the
 // peers' pods, a rollback or the routing at a request's end any.
-template <int BS, class KeyFn>
+// TOGETHER: see commit_wave.
+template <int BS, bool TOGETHER, class KeyFn>
 __device__ __forceinline__ bool grid_select(const Topo &t, const State &st, const Method &m, const Batch &b,
                                             const GSmem &sm, const GridCtl &g, long long timeout, const StepIn &s,
                                             const ReqView &rv, unsigned &rnd, bool &stale, int nx, int *feas, KeyFn key_of) {
@@ -480,7 +481,7 @@ __device__ __forceinline__ bool grid_select(const Topo &t, const State &st, cons
                 // uses the global state
                 Smem cs;
                 cs.pk = sm.pk;
-                const bool ok = commit_wave(t, st, b, u, s, m.route_end ? 0 : P, cs, b.pbmax + s.p0, lane);
+                const bool ok = commit_wave<TOGETHER>(t, st, b, u, s, m.route_end ? 0 : P, cs, b.pbmax + s.p0, lane);
                 if (lane == 0) {
                     sm.misc[M_ROUTE + 1] = ok;
                     if (ok) {
@@ -493,7 +494,7 @@ __device__ __forceinline__ bool grid_select(const Topo &t, const State &st, cons
             __syncthreads();
             int res = sm.misc[M_ROUTE + 1];
             if (res && m.route_end && s.i == s.n - 1)
-                res = route_request_end<BS>(t, st, b, sm.misc + M_ROUTE, s,
+                res = route_request_end<BS>(t, st, b, sm.misc + M_ROUTE, s, rv,
                                             [&](int q) { return q == s.i ? u : rv.hosts[q]; }) ? 1 : 2;
             __syncthreads();
             if (threadIdx.x == 0) {
@@ -655,7 +656,7 @@ __device__ __forceinline__ bool grid_topsis_step(const Topo &t, const State &st,
         for (int x = threadIdx.x; x < hh; x += BS)
             tr.scores[static_cast<size_t>(slot) * t.N + ubase + x] =
                 topsis_close(nc, [&](int c) { return xs[c * hh + x]; }, q, ap, am);
-    return grid_select<BS>(t, st, m, b, sm, g, timeout, s, rv, rnd, stale, hh, xs + nc * hh, key_of);
+    return grid_select<BS, CS != 0>(t, st, m, b, sm, g, timeout, s, rv, rnd, stale, hh, xs + nc * hh, key_of);
 }
 
 }  // namespace dcs
@@ -669,8 +670,9 @@ __device__ __forceinline__ int *grid_req_lds(char *dsm, int h, int hh, int nc) {
 
 // Plain form, large data centers: one cooperative launch per container step.
 // K > 0: k = K fat-trees on the four default criteria, as compile-time
-// constants (as in the batched kernel); K = 0: any.
-template <int BS, int K>
+// constants (as in the resident kernel); K = 0: any k, on those criteria
+// (CS = 4) or any (CS = 0).
+template <int BS, int K, int CS>
 __global__ __launch_bounds__(BS) void k_topsis_grid(Params p, GridCtl g, long long timeout) {
     extern __shared__ __align__(16) char dsm[];
     // every workgroup leaves before any wait: the request was rejected at an
@@ -678,7 +680,6 @@ __global__ __launch_bounds__(BS) void k_topsis_grid(Params p, GridCtl g, long lo
     // a batch's steps are queued together, and a step after a failed one
     // would read the missing peer's server as -1)
     if (p.b.status[p.s.r] == 0 || __hip_atomic_load(g.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
-    constexpr int CS = K ? 4 : 0;
     const Topo t = topo_of<K>(p.t);
     const GSmem sm = gcarve(dsm, t.h, t.hh, crit_count<CS>(p.m));
     unsigned rnd = __hip_atomic_load(g.round, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -691,10 +692,9 @@ __global__ __launch_bounds__(BS) void k_topsis_grid(Params p, GridCtl g, long lo
 // one cooperative workgroup per pod.  Workgroup 0 polls the command ring
 // and publishes each command to the others through a grid barrier; every
 // workgroup keeps its own LDS copy of the request.
-template <int BS, int K>
+template <int BS, int K, int CS>
 __global__ __launch_bounds__(BS) void k_serve_grid(Params p, ServeArgs a, GridCtl g, long long timeout) {
     extern __shared__ __align__(16) char dsm[];
-    constexpr int CS = K ? 4 : 0;
     const Topo t = topo_of<K>(p.t);
     const GSmem sm = gcarve(dsm, t.h, t.hh, crit_count<CS>(p.m));
     int *rq_host = grid_req_lds(dsm, t.h, t.hh, crit_count<CS>(p.m));

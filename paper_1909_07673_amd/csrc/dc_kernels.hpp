@@ -654,17 +654,17 @@ inline size_t resident_lds_bytes(int pc, int nsw, int N, int rows, int pairs) {
 // criteria (CPU, RAM, active, path bandwidth; all benefits), so the
 // topology and the criterion list are compile-time constants: index
 // arithmetic becomes shifts and the per-criterion selection folds away.
-// Same arithmetic as K = 0 (any k and criteria), bit-identical results.
+// K = 0: any k, on those criteria (CS = 4) or any (CS = 0).  Same arithmetic
+// everywhere, bit-identical results.
 // QUEUE: the plain form, with p.xrows and p.rq_pairs; otherwise the batched
 // form's fixed layout (all rows, every pair), whose offsets are then
 // constants (as run-time values they cost its launches 1.3 %).
-template <int BS, int G, int K, bool QUEUE>
+template <int BS, int G, int K, int CS, bool QUEUE>
 __global__ __launch_bounds__(BS) void k_topsis_resident(Params p) {
     extern __shared__ __align__(16) char dsm[];
     const int inst = blockIdx.x;
     const Topo t = topo_of<K>(p.t);
     const Method &m = p.m;
-    constexpr int CS = K ? 4 : 0;
     const int N = t.N;
     Smem sm = carve(dsm, p.pc_cap, t.nsw);
     int *rq_host = lds_after_tables(dsm, p.pc_cap, t.nsw);

@@ -570,26 +570,33 @@ bool specialised_ahp5(const dc_ctx *ctx, int K) {
     return true;
 }
 
-// Whether the context runs k = K fat-trees on the four default criteria
-// (CPU, RAM, active, path bandwidth; all benefits, TOPSIS), for which
-// kernels are also compiled with these as compile-time constants.
-bool specialised(const dc_ctx *ctx, int K) {
-    if (ctx->t.k != K || ctx->m.method != DC_TOPSIS || ctx->m.nc != 4) return false;
+// Whether the context runs TOPSIS on the four default criteria (CPU, RAM,
+// active, path bandwidth; all benefits), the list kernels are also compiled
+// for; and on k = K fat-trees, for which some are compiled too.
+bool default_criteria(const dc_ctx *ctx) {
+    if (ctx->m.method != DC_TOPSIS || ctx->m.nc != 4) return false;
     for (int c = 0; c < 4; ++c)
         if (ctx->m.crit[c] != c || ctx->m.cost[c] != 0) return false;
     return true;
+}
+bool specialised(const dc_ctx *ctx, int K) { return ctx->t.k == K && default_criteria(ctx); }
+
+// The kernel compiled for k = K, for the default criteria, or for any case.
+template <class F>
+F by_case(const dc_ctx *ctx, int K, F at_k, F at_list, F any) {
+    return specialised(ctx, K) ? at_k : default_criteria(ctx) ? at_list : any;
 }
 
 // The cooperative kernels compiled for k = 48 (the large data center of the
 // serving form) on the default criteria, or for any case.
 constexpr int kGridK = 48;
 const void *grid_step_kernel(const dc_ctx *ctx) {
-    return specialised(ctx, kGridK) ? reinterpret_cast<const void *>(k_topsis_grid<kGridBlock, kGridK>)
-                                    : reinterpret_cast<const void *>(k_topsis_grid<kGridBlock, 0>);
+    return reinterpret_cast<const void *>(by_case(ctx, kGridK, k_topsis_grid<kGridBlock, kGridK, 4>,
+                                                  k_topsis_grid<kGridBlock, 0, 4>, k_topsis_grid<kGridBlock, 0, 0>));
 }
 const void *grid_serve_kernel(const dc_ctx *ctx) {
-    return specialised(ctx, kGridK) ? reinterpret_cast<const void *>(k_serve_grid<kGridBlock, kGridK>)
-                                    : reinterpret_cast<const void *>(k_serve_grid<kGridBlock, 0>);
+    return reinterpret_cast<const void *>(by_case(ctx, kGridK, k_serve_grid<kGridBlock, kGridK, 4>,
+                                                  k_serve_grid<kGridBlock, 0, 4>, k_serve_grid<kGridBlock, 0, 0>));
 }
 
 // The AHP criteria kernel compiled for k = 32 (8,192 servers) on five criteria.
@@ -696,20 +703,21 @@ size_t batched_lds(const dc_ctx *ctx, int pc) {
 // The resident kernel compiled for k = 16 fat-trees scored on the four
 // default criteria (the constants fold into the kernel), or for any case.
 constexpr int kBatchedK = 16;
-bool batched_specialised(const dc_ctx *ctx) { return specialised(ctx, kBatchedK); }
+using ResidentFn = void (*)(Params);
+template <int BS, int G, bool QUEUE>
+ResidentFn resident_case(const dc_ctx *ctx) {
+    return by_case<ResidentFn>(ctx, kBatchedK, k_topsis_resident<BS, G, kBatchedK, 4, QUEUE>,
+                               k_topsis_resident<BS, G, 0, 4, QUEUE>, k_topsis_resident<BS, G, 0, 0, QUEUE>);
+}
 
 template <int BS, int G>
 void launch_batched_k(dc_ctx *ctx, const Params &p, size_t lds, hipStream_t stream) {
-    if (batched_specialised(ctx))
-        hipLaunchKernelGGL((k_topsis_resident<BS, G, kBatchedK, false>), dim3(ctx->I), dim3(BS), lds, stream, p);
-    else
-        hipLaunchKernelGGL((k_topsis_resident<BS, G, 0, false>), dim3(ctx->I), dim3(BS), lds, stream, p);
+    hipLaunchKernelGGL((resident_case<BS, G, false>(ctx)), dim3(ctx->I), dim3(BS), lds, stream, p);
 }
 
 template <int BS, int G>
 int set_lds_batched(dc_ctx *ctx, size_t lds) {
-    return batched_specialised(ctx) ? set_lds(ctx, k_topsis_resident<BS, G, kBatchedK, false>, lds)
-                                    : set_lds(ctx, k_topsis_resident<BS, G, 0, false>, lds);
+    return set_lds(ctx, resident_case<BS, G, false>(ctx), lds);
 }
 
 // sh must be a built shape with 1 <= sh.pc <= ctx->pc_batched (callers check)
@@ -758,11 +766,12 @@ Resident resident_layout(const dc_ctx *ctx, int max_peers, int max_pairs) {
 // The resident kernel for a queue at BS threads: one server per thread where
 // that covers them, otherwise several; at the automatic size the one
 // compiled for k = 16.
-using ResidentFn = void (*)(Params);
 template <int BS>
 ResidentFn resident_fn(const dc_ctx *ctx) {
-    if (BS == 1024 && batched_specialised(ctx)) return k_topsis_resident<1024, 1, kBatchedK, true>;
-    return ctx->N <= BS ? k_topsis_resident<BS, 1, 0, true> : k_topsis_resident<BS, host_group(BS), 0, true>;
+    if (BS == 1024 && ctx->N <= BS) return resident_case<BS, 1, true>(ctx);
+    return default_criteria(ctx)
+               ? (ctx->N <= BS ? k_topsis_resident<BS, 1, 0, 4, true> : k_topsis_resident<BS, host_group(BS), 0, 4, true>)
+               : (ctx->N <= BS ? k_topsis_resident<BS, 1, 0, 0, true> : k_topsis_resident<BS, host_group(BS), 0, 0, true>);
 }
 ResidentFn resident_fn_at(const dc_ctx *ctx, int bs) {
     return bs == 64 ? resident_fn<64>(ctx) : bs == 256 ? resident_fn<256>(ctx)
@@ -919,7 +928,8 @@ int grid_init(dc_ctx *ctx) {
 // ---------------------------------------------------------------- queue kernels
 using TopsisQueueFn = void (*)(Params, GridCtl, unsigned, long long, long long);
 TopsisQueueFn topsis_queue_fn(const dc_ctx *ctx) {
-    return specialised(ctx, kGridK) ? k_topsis_queue<kGridBlock, kGridK> : k_topsis_queue<kGridBlock, 0>;
+    return by_case<TopsisQueueFn>(ctx, kGridK, k_topsis_queue<kGridBlock, kGridK, 4>, k_topsis_queue<kGridBlock, 0, 4>,
+                                  k_topsis_queue<kGridBlock, 0, 0>);
 }
 
 // Largest value criterion c can take: residuals stay within the capacities,

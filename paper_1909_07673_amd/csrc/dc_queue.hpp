@@ -100,7 +100,7 @@ __device__ __forceinline__ void walk_queue(const Batch &b, const QueueReq &q, co
                 nx = b.pbmax[at];
             }
             const StepIn s{r, i, n, g0, g0 + i, pb + q0, P, q.cpu[i], q.ram[i], q.cmax[i], q.rmax[i]};
-            const ReqView rv{q.pj, q.pbw, q.host, q.host, q.pbmax};
+            const ReqView rv{q.pj, q.pbw, q.host, q.host, q.pbmax, q.poff};
             __syncthreads();
             if (!step(s, rv)) {
                 // rejected, or a wait failed: one thread asks, so that the
@@ -116,13 +116,11 @@ __device__ __forceinline__ void walk_queue(const Batch &b, const QueueReq &q, co
 }
 
 // ---------------------------------------------------------------- TOPSIS
-// One workgroup per pod, k workgroups.  K > 0: compiled for k = K on the
-// four default criteria.
-template <int BS, int K>
+// One workgroup per pod, k workgroups.  K and CS as in k_topsis_grid.
+template <int BS, int K, int CS>
 __global__ __launch_bounds__(BS) void k_topsis_queue(Params p, GridCtl g, unsigned epoch, long long patience,
                                                      long long timeout) {
     extern __shared__ __align__(16) char dsm[];
-    constexpr int CS = K ? 4 : 0;
     const Topo t = topo_of<K>(p.t);
     const GSmem sm = gcarve(dsm, t.h, t.hh, crit_count<CS>(p.m));
     if (!queue_join(g.join, epoch, patience, sm.misc + M_OK)) return;
@@ -523,7 +521,7 @@ __device__ __forceinline__ bool grid_ahp_step(const Params &p, const Topo &t, co
         if (sm.g.misc[M_OK]) return false;
     }
     const Deficits df = read_deficits(sm.g);
-    return grid_select<BS>(t, p.st, p.m, p.b, sm.g, g, timeout, s, rv, rnd, stale, pod ? hh : 0, feas,
+    return grid_select<BS, false>(t, p.st, p.m, p.b, sm.g, g, timeout, s, rv, rnd, stale, pod ? hh : 0, feas,
                            [&](int x) -> unsigned long long {
                                if (!feas[x] || !(p.m.route_end || deficits_allow(t, df, w, x))) return 0ull;
                                return score_key(pg[x], ubase + x);

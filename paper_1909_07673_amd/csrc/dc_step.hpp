@@ -141,9 +141,9 @@ struct ReqView {
     const int *pj, *pbw, *hosts;
     int *hosts_out;    // LDS copy of hosts to update (batched form), or nullptr
     const int *pbmax;  // the peers' maximum demands
-    // where `whole`, the whole request in LDS: rpoff[x] the first pair of
-    // container x relative to the request's first pair (x <= n), rpj the
-    // pairs' peer containers
+    // in LDS where not nullptr: rpoff[x] the first pair of container x
+    // relative to the request's first pair (x <= n); where `whole`, rpj the
+    // peer containers of all the request's pairs
     const int *rpoff = nullptr, *rpj = nullptr;
     bool whole = false;
 };
@@ -421,6 +421,146 @@ __device__ __forceinline__ void path_apply_lanes(const Topo &t, const State &st,
     }
 }
 
+// Routing state of a commit: lane p holds peer p's packed record, path choice
+// and allocation.
+struct Routing {
+    int4 pk;
+    int code, got;
+    int routed;          // peers [0, routed) are routed or on the server itself
+};
+
+// Routes the remote peers of container s from server u in order, I candidate
+// paths per lane, D peers' candidate links read together: the chain of a
+// commit is then one memory or LDS round trip per D peers, and per peer a
+// wave maximum over registers.  The server's own links stay in registers
+// throughout, less what each route takes; a peer read before another's route
+// was taken has the links they share (same server, edge switch or pod)
+// lowered in its registers too.  For states in memory, in the kernels that
+// have the registers: a serving session at k = 48 took 60.2 ms routing one
+// peer at a time, 56.8 ms so; the 1,024-thread AHP kernel spilled (a queue at
+// k = 32: 31.7 and 33.8 ms), and with the state in LDS the round trip is no
+// longer than the extra work (a queue at k = 16: 22.0 and 23.8 ms).  False
+// when a bottleneck is below the demand.
+template <int I, int D>
+__device__ __forceinline__ bool route_peers(const Topo &t, const State &st, int u, int P, Routing &rt, int lane) {
+    const int eu = edge_of(t, u), pu = pod_of(t, u);
+    int c[I], ca[I], x2[I], x4[I];                       // candidate, its aggregation index, the server's links
+#pragma unroll
+    for (int i = 0; i < I; ++i) {
+        c[i] = lane + i * kWave;
+        const int cs = min(c[i], t.hh - 1);
+        ca[i] = div_floor(cs, t.h, t.rh);
+        x2[i] = st.ea[eu * t.h + ca[i]];
+        x4[i] = st.ac[pu * t.hh + cs];
+    }
+    int upu = st.up[u];
+    unsigned long long todo = __ballot(lane < P && rt.pk.x != u);
+    while (todo) {
+        int pp[D], v[D], ev[D], pv[D], dm[D], upv[D], x3[D][I], x5[D][I];
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            pp[d] = -1;
+            v[d] = ev[d] = pv[d] = -1;
+            if (!todo) continue;
+            pp[d] = __builtin_ctzll(todo);
+            todo &= todo - 1;
+            v[d] = __builtin_amdgcn_readlane(rt.pk.x, pp[d]);
+            const int ed = __builtin_amdgcn_readlane(rt.pk.y, pp[d]);
+            ev[d] = ed & 0xffff;
+            pv[d] = ed >> 16;
+            dm[d] = __builtin_amdgcn_readlane(rt.pk.z, pp[d]);
+            upv[d] = st.up[v[d]];
+#pragma unroll
+            for (int i = 0; i < I; ++i) {
+                x3[d][i] = st.ea[ev[d] * t.h + ca[i]];
+                x5[d][i] = st.ac[pv[d] * t.hh + min(c[i], t.hh - 1)];
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            if (pp[d] < 0) break;
+            const bool near = ev[d] == eu, pod = pv[d] == pu;
+            const int base = min(upu, upv[d]);
+            unsigned best = 0;
+            int b2 = 0, b3 = 0, b4 = 0, b5 = 0;
+            if (near) {
+                best = lane == 0 ? (static_cast<unsigned>(base) << 10) | 1023u : 0u;
+            } else {
+#pragma unroll
+                for (int i = 0; i < I; ++i) {
+                    // within a pod a candidate is an aggregation switch: the
+                    // lane of its first core stands for it
+                    const int code = pod ? ca[i] : c[i];
+                    const bool is = c[i] < t.hh && !(pod && c[i] != ca[i] * t.h);
+                    const int low = min(base, min(x2[i], x3[d][i]));
+                    const int b = pod ? low : min(low, min(x4[i], x5[d][i]));
+                    const unsigned key = is ? (static_cast<unsigned>(b) << 10) | static_cast<unsigned>(1023 - code) : 0u;
+                    if (key > best) { best = key; b2 = x2[i]; b3 = x3[d][i]; b4 = x4[i]; b5 = x5[d][i]; }
+                }
+            }
+            const unsigned key = wave_umax(best);
+            const int cc = 1023 - static_cast<int>(key & 1023u);
+            if (static_cast<int>(key >> 10) < dm[d]) return false;
+            // lane x writes link x of the path with its residual less the
+            // demand (no other wave writes them meanwhile)
+            const int src = __builtin_ctzll(__ballot(best == key));
+            const int l2 = __builtin_amdgcn_readlane(b2, src), l3 = __builtin_amdgcn_readlane(b3, src);
+            const int l4 = __builtin_amdgcn_readlane(b4, src), l5 = __builtin_amdgcn_readlane(b5, src);
+            {
+                int *l = path_link_lane(t, st, u, v[d], cc, lane);
+                int cur = lane & 1 ? upv[d] : upu;
+                cur = lane == 2 ? l2 : lane == 3 ? l3 : lane == 4 ? l4 : lane == 5 ? l5 : cur;
+                if (l) *l = cur - dm[d];
+            }
+            rt.code = lane == pp[d] ? cc : rt.code;
+            rt.got = lane == pp[d] ? dm[d] : rt.got;
+            rt.routed = pp[d] + 1;
+            // the same in the registers read before
+            const int aa = near ? -1 : pod ? cc : div_floor(cc, t.h, t.rh), cx = near || pod ? -1 : cc;
+            upu -= dm[d];
+#pragma unroll
+            for (int i = 0; i < I; ++i) {
+                x2[i] -= ca[i] == aa ? dm[d] : 0;
+                x4[i] -= c[i] == cx ? dm[d] : 0;
+            }
+#pragma unroll
+            for (int e = d + 1; e < D; ++e) {
+                upv[e] -= v[e] == v[d] ? dm[d] : 0;
+#pragma unroll
+                for (int i = 0; i < I; ++i) {
+                    x3[e][i] -= ev[e] == ev[d] && ca[i] == aa ? dm[d] : 0;
+                    x5[e][i] -= pv[e] == pv[d] && c[i] == cx ? dm[d] : 0;
+                }
+            }
+        }
+        __threadfence_block();
+    }
+    return true;
+}
+
+// The same, one peer at a time (any number of candidates).
+__device__ __forceinline__ bool route_peers_each(const Topo &t, const State &st, int u, int P, Routing &rt, int lane) {
+    const int eu = edge_of(t, u), pu = pod_of(t, u);
+    for (int p = 0; p < P; ++p) {
+        const int v = __builtin_amdgcn_readlane(rt.pk.x, p), ed = __builtin_amdgcn_readlane(rt.pk.y, p);
+        const int dm = __builtin_amdgcn_readlane(rt.pk.z, p);
+        if (v == u) continue;
+        const Widest wd = widest_wave_links(t, st, u, v, eu, pu, ed & 0xffff, ed >> 16, lane);
+        const int c = 1023 - static_cast<int>(wd.key & 1023u);
+        if (static_cast<int>(wd.key >> 10) < dm) return false;
+        int *l = path_link_lane(t, st, u, v, c, lane);
+        int cur = wd.link[0];
+#pragma unroll
+        for (int x = 1; x < 6; ++x) cur = lane == x ? wd.link[x] : cur;
+        if (l) *l = cur - dm;
+        rt.code = lane == p ? c : rt.code;
+        rt.got = lane == p ? dm : rt.got;
+        rt.routed = p + 1;
+        __threadfence_block();
+    }
+    return true;
+}
+
 // Commit of container s on server u with its P placed peers (servers and
 // minimum demands in the LDS peer list, ascending container index): route
 // each remote peer's minimum on its widest shortest path under the current
@@ -433,6 +573,8 @@ __device__ __forceinline__ void path_apply_lanes(const Topo &t, const State &st,
 // server needs no link and gets its maximum.  Run by one whole wave; lane 0
 // writes the server's resources, lane p peer p's route code and
 // allocation.  pbmax[p]: peer p's maximum demand (LDS or global).
+// TOGETHER: route_peers reads two peers' links together.
+template <bool TOGETHER>
 __device__ __forceinline__ bool commit_wave(const Topo &t, const State &st, const Batch &b, int u, const StepIn &s,
                                             int P, const Smem &sm, const int *pbmax, int lane) {
     const int pmax = lane < P ? pbmax[lane] : 0;
@@ -444,39 +586,17 @@ __device__ __forceinline__ bool commit_wave(const Topo &t, const State &st, cons
     // the commit ends
     const int cpu_u = st.cpu[u], ram_u = st.ram[u], npl_u = st.npl[u];
     if (cpu_u < s.cpu || ram_u < s.ram) return false;
-    const int eu = edge_of(t, u), pu = pod_of(t, u);
-    int routed = 0, mycode = -1, mine = pmax;   // lane p keeps peer p's path choice and allocation
     // lane p holds peer p's record (P <= 64), handed out per peer below
-    const int4 mypk = lane < P ? sm.pk[lane] : make_int4(u, 0, 0, 0);
-    bool ok = true;
-    for (int p = 0; p < P; ++p) {
-        const int4 pk = make_int4(__builtin_amdgcn_readlane(mypk.x, p), __builtin_amdgcn_readlane(mypk.y, p),
-                                  __builtin_amdgcn_readlane(mypk.z, p), 0);
-        const int v = pk.x;
-        if (v == u) {
-            routed = p + 1;
-            continue;
-        }
-        const Widest wd = widest_wave_links(t, st, u, v, eu, pu, pk.y & 0xffff, pk.y >> 16, lane);
-        const int bn = static_cast<int>(wd.key >> 10);
-        const int c = 1023 - static_cast<int>(wd.key & 1023u);
-        if (bn < pk.z) { ok = false; break; }
-        // lane x writes link x of the path with its residual less the demand
-        // (the residuals were just read; no other wave writes them meanwhile)
-        {
-            int *l = path_link_lane(t, st, u, v, c, lane);
-            int cur = wd.link[0];
-#pragma unroll
-            for (int x = 1; x < 6; ++x) cur = lane == x ? wd.link[x] : cur;
-            if (l) *l = cur - pk.z;
-        }
-        mycode = lane == p ? c : mycode;
-        mine = lane == p ? pk.z : mine;
-        __threadfence_block();
-        routed = p + 1;
-    }
+    Routing rt{lane < P ? sm.pk[lane] : make_int4(u, 0, 0, 0), -1, pmax, 0};
+    bool ok;
+    if (TOGETHER && t.hh <= 4 * kWave) ok = route_peers<4, 2>(t, st, u, P, rt, lane);
+    else if (TOGETHER && t.hh <= 9 * kWave) ok = route_peers<9, 2>(t, st, u, P, rt, lane);
+    else ok = route_peers_each(t, st, u, P, rt, lane);
+    const int4 mypk = rt.pk;
+    const int mycode = rt.code;
+    int mine = rt.got;
     if (!ok) {
-        for (int p = routed - 1; p >= 0; --p) {
+        for (int p = rt.routed - 1; p >= 0; --p) {
             const int v = __builtin_amdgcn_readlane(mypk.x, p);
             if (v != u)
                 path_apply_lanes<false>(t, st, u, v, __builtin_amdgcn_readlane(mycode, p),
@@ -616,7 +736,13 @@ __device__ __forceinline__ void table_T(const Topo &t, const State &st, const Sm
                     val = max(val, max(max(min(a4.x, b4.x), min(a4.y, b4.y)), max(min(a4.z, b4.z), min(a4.w, b4.w))));
                 }
             } else {
-                for (int j = 0; j < t.h; ++j) val = max(val, min(x[j], y[j]));
+                // eight entries in flight, the last one repeated past the end
+                for (int j0 = 0; j0 < t.h; j0 += 8)
+#pragma unroll
+                    for (int d = 0; d < 8; ++d) {
+                        const int j = min(j0 + d, t.h - 1);
+                        val = max(val, min(x[j], y[j]));
+                    }
             }
         }
         sm.tabT[it] = val;
@@ -645,7 +771,12 @@ __device__ __forceinline__ void table_E(const Topo &t, const State &st, const Sm
                                        max(min(min(a4.z, b4.z), max(t4.z, lim)), min(min(a4.w, b4.w), max(t4.w, lim)))));
                 }
             } else {
-                for (int a = 0; a < t.h; ++a) val = max(val, min(min(x[a], y[a]), max(T[a], lim)));
+                for (int a0 = 0; a0 < t.h; a0 += 8)
+#pragma unroll
+                    for (int d = 0; d < 8; ++d) {
+                        const int a = min(a0 + d, t.h - 1);
+                        val = max(val, min(min(x[a], y[a]), max(T[a], lim)));
+                    }
             }
         }
         sm.tabE[it] = val;
@@ -672,7 +803,12 @@ __device__ __forceinline__ void load_peers(const Topo &t, const State &st, const
     if (LIMITS && P > 0) {
         for (int x = threadIdx.x; x < t.nsw; x += BS) {
             int se = 0;
-            for (int a = 0; a < t.h; ++a) se += st.ea[x * t.h + a];
+            for (int a0 = 0; a0 < t.h; a0 += 8)
+#pragma unroll
+                for (int d = 0; d < 8; ++d) {
+                    const int v = st.ea[x * t.h + min(a0 + d, t.h - 1)];
+                    se += a0 + d < t.h ? v : 0;
+                }
             sm.capE[x] = se;
         }
         // per pod: one wave sums the pod's h*h aggregation-core residuals
@@ -937,17 +1073,26 @@ __device__ __forceinline__ void column_factors_lds(const Smem &sm, const Method 
     constexpr int NW = BS / kWave;
     const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
     float *f = reinterpret_cast<float *>(sm.wst);
-    for (int c = wid; c < crit_count<CS>(m); c += NW) {
+    // (with a known list and one wave per workgroup the columns unroll, and
+    // their reductions run side by side)
+#pragma unroll
+    for (int c0_ = 0; c0_ < (CS ? CS : kMaxCrit); c0_ += NW) {
+        const int c = c0_ + wid;
+        if (c >= crit_count<CS>(m)) break;
         const int *col = xs + static_cast<size_t>(c) * N;
         unsigned long long s2 = 0;
         int hi = -kBig - 1, lo = kBig;
-#pragma unroll 8
-        for (int u = lane; u < N; u += kWave) {
-            const int x = col[u];
-            s2 += static_cast<unsigned long long>(static_cast<unsigned>(x)) * static_cast<unsigned>(x);
-            hi = max(hi, x);
-            lo = min(lo, x);
-        }
+        // eight values in flight, the last server's repeated past the end
+        // (and not summed)
+        for (int base = lane; base < N; base += 8 * kWave)
+#pragma unroll
+            for (int d = 0; d < 8; ++d) {
+                const int u = base + d * kWave;
+                const int x = col[min(u, N - 1)];
+                s2 += u < N ? static_cast<unsigned long long>(static_cast<unsigned>(x)) * static_cast<unsigned>(x) : 0ull;
+                hi = max(hi, x);
+                lo = min(lo, x);
+            }
         const unsigned c0 = static_cast<unsigned>(wave_sum(static_cast<int>(s2 & 0x1ffffu)));
         const unsigned c1 = static_cast<unsigned>(wave_sum(static_cast<int>((s2 >> 17) & 0x1ffffu)));
         const unsigned c2 = static_cast<unsigned>(wave_sum(static_cast<int>(s2 >> 34)));
@@ -1000,19 +1145,32 @@ __device__ __forceinline__ int trace_slot(const Trace &tr, int inst, int rid, in
 
 // Routing after the last unit of request r is placed (section V-D, with
 // Method::route_end): every routed pair's widest minimum-hop path is chosen
-// on the residuals the placement left, all pairs independently (one wave per
-// unit's pairs); then every minimum demand is taken off its links at once.
+// on the residuals the placement left, all pairs independently; then every
+// minimum demand is taken off its links at once.
 // If a link goes negative the request does not fit: everything it took is
 // given back and it is rejected with failed_at = n.  Otherwise wave 0 tops
 // each pair up, in pair order, by what its most loaded link still has, to
 // at most the pair's maximum.  host(g) is the server of unit
 // g (u for the unit just placed).  Returns true when the request was
 // accepted.
+// The pairs' own data come one pair per lane or thread (their owner by a
+// search in the request's offsets), so that memory is waited for once per 64
+// pairs; only the choice of a path and the top-ups take a wave per pair.
 template <int BS, class HostFn>
 __device__ __forceinline__ bool route_request_end(const Topo &t, const State &st, const Batch &b, int *lds_ok, const StepIn &s,
-                                  HostFn host) {
+                                  const ReqView &rv, HostFn host) {
     constexpr int NW = BS / kWave;
-    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+    const int lane = threadIdx.x & (kWave - 1), wid = uniform(threadIdx.x / kWave);
+    const int pb = b.poff[s.g0], npair = uniform(b.poff[s.g0 + s.n] - pb);
+    auto owner = [&](int q) {                              // largest unit whose pairs start at or before q
+        int lo = 0, hi = s.n - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            const int at = rv.rpoff ? rv.rpoff[mid] : b.poff[s.g0 + mid] - pb;
+            if (at <= q) lo = mid; else hi = mid - 1;
+        }
+        return lo;
+    };
     // All waves of the workgroup share one CU and its write-through L1, and
     // the link updates below are L2 atomics, so ordering inside the routine
     // needs only workgroup fences; one agent fence at the end of an accepted
@@ -1020,59 +1178,66 @@ __device__ __forceinline__ bool route_request_end(const Topo &t, const State &st
     __threadfence_block();
     if (threadIdx.x == 0) *lds_ok = 1;
     __syncthreads();
-    for (int g = wid; g < s.n; g += NW) {
-        const int u = host(g), eu = edge_of(t, u), pu = pod_of(t, u);
-        for (int x = b.poff[s.g0 + g]; x < b.poff[s.g0 + g + 1]; ++x) {
-            const int v = host(b.pj[x]);
-            int c = -1;
-            if (v != u) {
-                const unsigned best = widest_wave(t, st, u, v, eu, pu, edge_of(t, v), pod_of(t, v), lane);
-                c = 1023 - static_cast<int>(best & 1023u);
-            }
-            if (lane == 0) {
-                b.code[x] = c;
-                b.pbwa[x] = c >= 0 ? b.pbw[x] : b.pbmax[x];
-            }
+    // every pair's path: the pairs in equal shares over the waves
+    const int per = (npair + NW - 1) / NW, w1 = min(npair, (wid + 1) * per);
+    for (int base = wid * per; base < w1; base += kWave) {
+        const int q = min(base + lane, w1 - 1);
+        const int u = host(owner(q)), v = host(b.pj[pb + q]);
+        const int want = b.pbw[pb + q], most = b.pbmax[pb + q];
+        int code = -1;
+        for (int x = 0; x < min(kWave, w1 - base); ++x) {
+            const int ux = __builtin_amdgcn_readlane(u, x), vx = __builtin_amdgcn_readlane(v, x);
+            if (ux == vx) continue;
+            const unsigned best = widest_wave(t, st, ux, vx, edge_of(t, ux), pod_of(t, ux), edge_of(t, vx),
+                                              pod_of(t, vx), lane);
+            code = lane == x ? 1023 - static_cast<int>(best & 1023u) : code;
+        }
+        if (base + lane < w1) {
+            b.code[pb + q] = code;
+            b.pbwa[pb + q] = code >= 0 ? want : most;
         }
     }
     __threadfence_block();
     __syncthreads();
-    for (int g = wid; g < s.n; g += NW) {                  // take every demand off its path
-        const int u = host(g);
-        for (int x = b.poff[s.g0 + g]; x < b.poff[s.g0 + g + 1]; ++x) {
-            const int c = b.code[x];
-            if (c >= 0) path_apply_lanes<true>(t, st, u, host(b.pj[x]), c, -b.pbwa[x], lane);
-        }
+    for (int q = threadIdx.x; q < npair; q += BS) {        // take every demand off its path
+        const int c = b.code[pb + q];
+        if (c >= 0) path_apply<true>(t, st, host(owner(q)), host(b.pj[pb + q]), c, -b.pbwa[pb + q]);
     }
     __threadfence_block();
     __syncthreads();
-    for (int g = wid; g < s.n; g += NW) {                  // any link overdrawn?
-        const int u = host(g);
-        for (int x = b.poff[s.g0 + g]; x < b.poff[s.g0 + g + 1]; ++x) {
-            const int c = b.code[x];
-            if (c >= 0) {
-                const int *l = path_link_lane(t, st, u, host(b.pj[x]), c, lane);
-                if (l && __hip_atomic_load(l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < 0) *lds_ok = 0;
-            }
+    for (int q = threadIdx.x; q < npair; q += BS) {        // any link overdrawn?
+        const int c = b.code[pb + q];
+        if (c < 0) continue;
+        const int u = host(owner(q)), v = host(b.pj[pb + q]);
+        bool over = false;
+        for (int x = 0; x < 6; ++x) {
+            const int *l = path_link(t, st, u, v, c, x);
+            over |= l && __hip_atomic_load(l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < 0;
         }
+        if (over) *lds_ok = 0;
     }
     __syncthreads();
     if (*lds_ok) {
         if (wid == 0)
-            for (int g = 0; g < s.n; ++g) {
-                const int u = host(g);
-                for (int x = b.poff[s.g0 + g]; x < b.poff[s.g0 + g + 1]; ++x) {
-                    const int c = b.code[x], room = b.pbmax[x] - b.pbw[x];
-                    if (c < 0 || room <= 0) continue;
-                    const int v = host(b.pj[x]);
-                    const int *l = path_link_lane(t, st, u, v, c, lane);
+            for (int base = 0; base < npair; base += kWave) {
+                const int q = min(base + lane, npair - 1);
+                const int u = host(owner(q)), v = host(b.pj[pb + q]), code = b.code[pb + q];
+                const int want = b.pbw[pb + q], room = b.pbmax[pb + q] - want;
+                const bool can = base + lane < npair && code >= 0 && room > 0;
+                int got = 0;
+                for (unsigned long long todo = __ballot(can); todo; todo &= todo - 1) {
+                    const int x = __builtin_ctzll(todo);
+                    const int ux = __builtin_amdgcn_readlane(u, x), vx = __builtin_amdgcn_readlane(v, x);
+                    const int c = __builtin_amdgcn_readlane(code, x);
+                    const int *l = path_link_lane(t, st, ux, vx, c, lane);
                     const int left = l ? __hip_atomic_load(l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : kBig;
-                    const int add = min(room, wave_min(left));
+                    const int add = min(__builtin_amdgcn_readlane(room, x), wave_min(left));
                     if (add <= 0) continue;
-                    path_apply_lanes<true>(t, st, u, v, c, -add, lane);
-                    if (lane == 0) b.pbwa[x] = b.pbw[x] + add;
+                    path_apply_lanes<true>(t, st, ux, vx, c, -add, lane);
+                    got = lane == x ? add : got;
                     __threadfence_block();
                 }
+                if (got) b.pbwa[pb + q] = want + got;
             }
         __threadfence();
         vm_drain();
@@ -1151,7 +1316,7 @@ __device__ __forceinline__ bool select_commit(const Topo &t, const State &st, co
             const GPtr<int> o_host = b.host;              // read before the commit's fences
             const GPtr<float> o_score = b.score;
             const GPtr<long long> o_tse = b.tse;
-            const bool ok = commit_wave(t, st, b, u, s, m_route_end ? 0 : s.P, sm, sm.pbw, lane);
+            const bool ok = commit_wave<false>(t, st, b, u, s, m_route_end ? 0 : s.P, sm, sm.pbw, lane);
             if (lane == 0) {
                 sm.misc[M_OK] = ok;
                 if (ok) {
@@ -1168,7 +1333,7 @@ __device__ __forceinline__ bool select_commit(const Topo &t, const State &st, co
         __syncthreads();
         if (sm.misc[M_OK]) {
             if (m_route_end && s.i == s.n - 1)
-                return route_request_end<BS>(t, st, b, sm.misc + M_ROUTE, s,
+                return route_request_end<BS>(t, st, b, sm.misc + M_ROUTE, s, rv,
                                              [&](int g) { return g == s.i ? u : rv.hosts[g]; });
             return true;
         }
