@@ -81,10 +81,10 @@ def lib():
         P = C.c_void_p
         i32p = C.POINTER(C.c_int32)
         L.dc_create.argtypes = [C.POINTER(dc_config), C.POINTER(P)]
-        L.dc_submit_request.argtypes = [P, C.c_int32, C.c_int32, i32p, i32p, C.c_int32, i32p, i32p,
-                                        C.POINTER(C.c_int64)]
-        L.dc_submit_request_ranged.argtypes = [P, C.c_int32, C.c_int32, i32p, i32p, i32p, i32p, C.c_int32, i32p,
-                                               i32p, i32p, C.POINTER(C.c_int64)]
+        # arrays by address (a pointer object for each takes longer than the call)
+        L.dc_submit_request.argtypes = [P, C.c_int32, C.c_int32, P, P, C.c_int32, P, P, C.POINTER(C.c_int64)]
+        L.dc_submit_request_ranged.argtypes = [P, C.c_int32, C.c_int32, P, P, P, P, C.c_int32, P, P, P,
+                                               C.POINTER(C.c_int64)]
         L.dc_get_alloc.argtypes = [P, C.c_int64, i32p, i32p, i32p]
         L.dc_schedule.argtypes = [P, C.c_int32, C.POINTER(dc_result), C.POINTER(C.c_int32)]
         L.dc_release.argtypes = [P, C.c_int64]
@@ -125,6 +125,10 @@ def _i32(a) -> np.ndarray:
 
 def _p32(a: np.ndarray):
     return a.ctypes.data_as(C.POINTER(C.c_int32))
+
+
+def _addr(a: np.ndarray) -> int:
+    return a.__array_interface__["data"][0]
 
 
 def _stream_handle(stream) -> Optional[int]:
@@ -229,14 +233,14 @@ class Scheduler:
         rid = C.c_int64()
         mx = [getattr(req, k, None) for k in ("cpu_max", "ram_max", "bw_max")]
         if all(x is None for x in mx):
-            _check(lib().dc_submit_request(self._ctx, instance, len(cpu), _p32(cpu), _p32(ram), len(edges) // 3,
-                                           _p32(edges) if len(edges) else None,
-                                           _p32(pod) if pod is not None else None, C.byref(rid)),
+            _check(lib().dc_submit_request(self._ctx, instance, len(cpu), _addr(cpu), _addr(ram), len(edges) // 3,
+                                           _addr(edges) if len(edges) else None,
+                                           _addr(pod) if pod is not None else None, C.byref(rid)),
                    "dc_submit_request")
             return rid.value
         cx, rx, bx = (None if x is None else _i32(x) for x in mx)
-        opt = lambda a: _p32(a) if a is not None and len(a) else None
-        _check(lib().dc_submit_request_ranged(self._ctx, instance, len(cpu), _p32(cpu), opt(cx), _p32(ram), opt(rx),
+        opt = lambda a: _addr(a) if a is not None and len(a) else None
+        _check(lib().dc_submit_request_ranged(self._ctx, instance, len(cpu), _addr(cpu), opt(cx), _addr(ram), opt(rx),
                                               len(edges) // 3, opt(edges), opt(bx), opt(pod), C.byref(rid)),
                "dc_submit_request_ranged")
         return rid.value

@@ -734,6 +734,13 @@ __global__ __launch_bounds__(BS) void k_release(Params p) {
     give_back<BS>(p.t, p.st, p.b, p.s.r, n);
 }
 
+// Outputs of a batch before it runs: -1 up to `neg`, 1 up to `one`, 0 up to
+// n (one launch instead of a fill for each).
+__global__ void k_reset_outputs(int *dst, long long neg, long long one, long long n) {
+    for (long long x = blockIdx.x * (long long)blockDim.x + threadIdx.x; x < n; x += (long long)gridDim.x * blockDim.x)
+        dst[x] = x < neg ? -1 : x < one ? 1 : 0;
+}
+
 __global__ void k_fill_i32(int *dst, int value, long long n) {
     for (long long x = blockIdx.x * (long long)blockDim.x + threadIdx.x; x < n; x += (long long)gridDim.x * blockDim.x)
         dst[x] = value;

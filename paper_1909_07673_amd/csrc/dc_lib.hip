@@ -204,10 +204,8 @@ struct DevBatch {
     std::vector<long long> tsb, tse;
     hipGraphExec_t gexec = nullptr;    // batched form: captured launch of this batch
     Shape gshape{0, 0, 0};             // launch shape it was captured with
-    int *pinned = nullptr;             // pinned host copy of the outputs, route codes left out
     ~DevBatch() {
         if (gexec) (void)hipGraphExecDestroy(gexec);
-        if (pinned) (void)hipHostFree(pinned);
     }
 };
 
@@ -309,6 +307,13 @@ struct dc_ctx {
     bool plain_res = false;        // plain kernel stages state + scratch in LDS
     size_t lds_plain = 0, lds_select = 0;
     std::vector<std::unique_ptr<DevBatch>> batches;
+    // the batches' device memory, cut from slabs (freed with the context),
+    // and a pinned buffer for what goes up and comes back: an allocation for
+    // each would cost a small call more than its kernel
+    std::vector<int *> slabs;
+    size_t slab_at = 0, slab_end = 0;      // free part of the last slab (int32 units)
+    int *pinned = nullptr;
+    size_t pinned_ints = 0;
     std::vector<int> queued;       // batches uploaded and waiting to run
     std::vector<int> pend_inst;
     std::vector<Units> pend_units;
@@ -442,18 +447,46 @@ Params base_params(dc_ctx *ctx, const DevBatch &b, int inst) {
 // Output region of a batch: host[Ct], code[Pt], failat[R] (all -1), then
 // status[R] (1), then score[Ct], tsb[R], tse[R] (0; the stamps are int64).
 int reset_outputs(dc_ctx *ctx, DevBatch &b) {
-    int *out = b.dmem + b.in_ints;
-    const long long neg = (long long)b.Ct + b.Pt + b.R;
-    hipLaunchKernelGGL(k_fill_i32, dim3(64), dim3(256), 0, ctx->stream, out, -1, neg);
-    hipLaunchKernelGGL(k_fill_i32, dim3(16), dim3(256), 0, ctx->stream, out + neg, 1, (long long)b.R);
-    hipLaunchKernelGGL(k_fill_i32, dim3(64), dim3(256), 0, ctx->stream, out + neg + b.R, 0,
-                       (long long)b.out_ints - neg - b.R);
+    const long long neg = (long long)b.Ct + b.Pt + b.R, all = (long long)b.out_ints;
+    hipLaunchKernelGGL(k_reset_outputs, dim3((unsigned)std::min<long long>(64, (all + 255) / 256)), dim3(256), 0,
+                       ctx->stream, b.dmem + b.in_ints, neg, neg + b.R, all);
     HIPCHK(hipGetLastError());
     return DC_OK;
 }
 
+// n int32 of device memory for a batch, 16-byte aligned.
+int batch_alloc(dc_ctx *ctx, size_t n, int **out) {
+    n = align4(n);
+    if (ctx->slab_end - ctx->slab_at < n) {
+        const size_t slab = std::max<size_t>(n, (size_t)1 << 18);      // 1 MiB
+        int *m = nullptr;
+        HIPCHK(hipMalloc(&m, slab * sizeof(int)));
+        ctx->slabs.push_back(m);
+        ctx->slab_at = 0;
+        ctx->slab_end = slab;
+    }
+    *out = ctx->slabs.back() + ctx->slab_at;
+    ctx->slab_at += n;
+    return DC_OK;
+}
+
+// The pinned buffer, at least n int32; what it held is lost when it grows.
+int pinned_at_least(dc_ctx *ctx, size_t n) {
+    if (ctx->pinned_ints >= n) return DC_OK;
+    HIPCHK(hipStreamSynchronize(ctx->stream));      // a copy from it may be under way
+    if (ctx->pinned) HIPCHK(hipHostFree(ctx->pinned));
+    ctx->pinned = nullptr;
+    ctx->pinned_ints = 0;
+    const size_t want = std::max<size_t>(n + n / 2, 1 << 14);
+    HIPCHK(hipHostMalloc(reinterpret_cast<void **>(&ctx->pinned), want * sizeof(int), 0));
+    ctx->pinned_ints = want;
+    return DC_OK;
+}
+
 // Turn the pending queue into one uploaded batch (requests grouped by
-// instance, FCFS order kept within an instance).
+// instance, FCFS order kept within an instance).  The copy from the pinned
+// buffer is under way on return; the caller waits for the stream before it
+// returns to its own caller.
 int upload_pending(dc_ctx *ctx) {
     const size_t R = ctx->pend_ids.size();
     if (R == 0) return DC_OK;
@@ -504,9 +537,11 @@ int upload_pending(dc_ctx *ctx) {
     const size_t n_out = b.o_alloc + 2 * (size_t)b.Ct + b.Pt;
     b.in_ints = n_in;
     b.out_ints = n_out;
-    std::vector<int> img(n_in, 0);
+    int prc = pinned_at_least(ctx, n_in);
+    if (prc || (prc = batch_alloc(ctx, n_in + n_out, &b.dmem))) return prc;
+    int *img = ctx->pinned;
     size_t o = 0;
-    auto put = [&](const std::vector<int> &v) { std::memcpy(img.data() + o, v.data(), v.size() * sizeof(int)); o += v.size(); };
+    auto put = [&](const std::vector<int> &v) { std::memcpy(img + o, v.data(), v.size() * sizeof(int)); o += v.size(); };
     const size_t o_coff = o; put(b.coff);
     const size_t o_cpu = o; put(b.cpu);
     const size_t o_ram = o; put(b.ram);
@@ -520,8 +555,8 @@ int upload_pending(dc_ctx *ctx) {
     const size_t o_cmax = o; put(b.cmax);
     const size_t o_rmax = o; put(b.rmax);
     const size_t o_pbmax = o; put(b.pbmax);
-    HIPCHK(hipMalloc(&b.dmem, (n_in + n_out) * sizeof(int)));
-    HIPCHK(hipMemcpyAsync(b.dmem, img.data(), n_in * sizeof(int), hipMemcpyHostToDevice, ctx->stream));
+    if (o < n_in) img[o] = 0;
+    HIPCHK(hipMemcpyAsync(b.dmem, img, n_in * sizeof(int), hipMemcpyHostToDevice, ctx->stream));
     int *d = b.dmem;
     int *out = d + n_in;
     b.view.coff = d + o_coff;
@@ -551,7 +586,6 @@ int upload_pending(dc_ctx *ctx) {
     }
     int rc = reset_outputs(ctx, b);
     if (rc) return rc;
-    HIPCHK(hipStreamSynchronize(ctx->stream));   // img is pageable host memory
     const int bi = (int)ctx->batches.size();
     for (int r = 0; r < b.R; ++r) ctx->loc[b.ids[r]] = ReqLoc{bi, r, false};
     ctx->batches.push_back(std::move(B));
@@ -832,18 +866,27 @@ int run_batched(dc_ctx *ctx, DevBatch &b, const Shape &sh) {
     return DC_OK;
 }
 
-// Copies the outputs back through a pinned buffer: the servers, then
+// Copies the outputs back through the pinned buffer: the servers, then
 // everything after the route codes (failed_at, status, scores, timestamps).
 // The route codes stay on the device; dc_get_paths fetches the few it needs.
-int collect(dc_ctx *ctx, DevBatch &b) {
+// The results go, in request id order, to *dst, which moves past them, as far
+// as `room` reaches, the others to ctx->ready.
+int collect(dc_ctx *ctx, DevBatch &b, dc_result **dst, int64_t *room) {
     const int *dout = b.dmem + b.in_ints;
     const size_t tail0 = (size_t)b.Ct + b.Pt, tail = b.o_alloc - tail0;   // the allocations stay on the device
-    if (!b.pinned) HIPCHK(hipHostMalloc(reinterpret_cast<void **>(&b.pinned), (b.Ct + tail) * sizeof(int), 0));
-    int *out = b.pinned;
-    HIPCHK(hipMemcpyAsync(out, dout, (size_t)b.Ct * sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
-    HIPCHK(hipMemcpyAsync(out + b.Ct, dout + tail0, tail * sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
+    const int prc = pinned_at_least(ctx, tail0 + tail);
+    if (prc) return prc;
+    int *out = ctx->pinned;
+    // few route codes cost less than a second copy
+    const bool whole = b.Pt <= 1 << 14;
+    if (whole) {
+        HIPCHK(hipMemcpyAsync(out, dout, b.o_alloc * sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
+    } else {
+        HIPCHK(hipMemcpyAsync(out, dout, (size_t)b.Ct * sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
+        HIPCHK(hipMemcpyAsync(out + b.Ct, dout + tail0, tail * sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
+    }
     HIPCHK(hipStreamSynchronize(ctx->stream));
-    const int *t0 = out + b.Ct;                        // output offset tail0 maps here
+    const int *t0 = out + (whole ? tail0 : b.Ct);      // output offset tail0 maps here
     b.host.assign(out, out + b.Ct);
     b.failat.assign(t0, t0 + b.R);
     b.status.assign(t0 + b.R, t0 + 2 * b.R);
@@ -858,12 +901,17 @@ int collect(dc_ctx *ctx, DevBatch &b) {
     // results in request id order
     std::vector<int> order(b.R);
     for (int r = 0; r < b.R; ++r) order[r] = r;
-    std::sort(order.begin(), order.end(), [&](int a, int c) { return b.ids[a] < b.ids[c]; });
+    if (!std::is_sorted(b.ids.begin(), b.ids.end()))
+        std::sort(order.begin(), order.end(), [&](int a, int c) { return b.ids[a] < b.ids[c]; });
     const size_t at = ctx->ready.size();
-    ctx->ready.resize(at + order.size());
+    const size_t direct = at ? 0 : (size_t)std::min<int64_t>(*room, (int64_t)order.size());
+    ctx->ready.resize(at + order.size() - direct);
+    dc_result *first = *dst;
+    *dst += direct;
+    *room -= (int64_t)direct;
     for (size_t k = 0; k < order.size(); ++k) {
         const int r = order[k];
-        dc_result &res = ctx->ready[at + k];
+        dc_result &res = k < direct ? first[k] : ctx->ready[at + k - direct];
         const int g0 = b.coff[r], c0 = b.cuoff[r];
         res.req_id = b.ids[r];
         res.instance = b.inst[r];
@@ -1760,6 +1808,20 @@ int dc_schedule(dc_ctx *ctx, int32_t max_results, dc_result *out, int32_t *n_out
     if (ctx->poisoned) return DC_EDEVICE;
     int rc = ctx->sv ? serve_poll(ctx) : upload_pending(ctx);
     if (rc) return rc;
+    dc_result *dst = out;
+    int64_t room = max_results;
+    // results of earlier calls come first
+    {
+        const size_t k = std::min<size_t>((size_t)room, ctx->ready.size() - ctx->ready_head);
+        if (k > 0) std::memcpy(dst, ctx->ready.data() + ctx->ready_head, sizeof(dc_result) * k);
+        ctx->ready_head += k;
+        dst += k;
+        room -= (int64_t)k;
+        if (ctx->ready_head == ctx->ready.size()) {
+            ctx->ready.clear();
+            ctx->ready_head = 0;
+        }
+    }
     if (!ctx->sv && !ctx->queued.empty()) {
         ctx->last_launches = 0;
         ctx->last_steps = 0;
@@ -1772,7 +1834,7 @@ int dc_schedule(dc_ctx *ctx, int32_t max_results, dc_result *out, int32_t *n_out
         HIPCHK(hipEventRecord(ctx->ev1, ctx->stream));
         HIPCHK(hipGetLastError());
         for (int bi : ctx->queued) {
-            rc = collect(ctx, *ctx->batches[bi]);
+            rc = collect(ctx, *ctx->batches[bi], &dst, &room);
             if (rc) return rc;
         }
         rc = grid_check(ctx);
@@ -1780,16 +1842,7 @@ int dc_schedule(dc_ctx *ctx, int32_t max_results, dc_result *out, int32_t *n_out
         HIPCHK(hipEventElapsedTime(&ctx->last_ms, ctx->ev0, ctx->ev1));
         ctx->queued.clear();
     }
-    int k = 0;
-    const size_t avail = ctx->ready.size() - ctx->ready_head;
-    k = (int)std::min<size_t>((size_t)max_results, avail);
-    if (k > 0) std::memcpy(out, ctx->ready.data() + ctx->ready_head, sizeof(dc_result) * (size_t)k);
-    ctx->ready_head += (size_t)k;
-    if (ctx->ready_head == ctx->ready.size()) {
-        ctx->ready.clear();
-        ctx->ready_head = 0;
-    }
-    if (n_out) *n_out = k;
+    if (n_out) *n_out = (int)(max_results - room);
     return DC_OK;
 }
 
@@ -1951,6 +2004,7 @@ int dc_rewind(dc_ctx *ctx) {
     if (!ctx) return DC_EINVAL;
     if (ctx->poisoned) return DC_EDEVICE;
     if (ctx->sv) return DC_ESTATE;
+    const bool fresh = !ctx->pend_ids.empty();
     int rc = upload_pending(ctx);
     if (rc) return rc;
     HIPCHK(hipMemcpyAsync(ctx->d_state, ctx->d_init, (size_t)ctx->I * 6 * ctx->N * sizeof(int),
@@ -1966,7 +2020,7 @@ int dc_rewind(dc_ctx *ctx) {
     }
     ctx->ready.clear();
     ctx->ready_head = 0;
-    ctx->ready_head = 0;
+    if (fresh) HIPCHK(hipStreamSynchronize(ctx->stream));
     return DC_OK;
 }
 
@@ -2003,6 +2057,7 @@ int dc_autotune_cached(dc_ctx *ctx, const char *cache_path, dc_tune *out) {
     const bool batched = ctx->cfg.mode == DC_MODE_BATCHED;
     int rc = upload_pending(ctx);
     if (rc) return rc;
+    HIPCHK(hipStreamSynchronize(ctx->stream));
     const std::string key = tune_key(ctx);
     if (cache_path && *cache_path) {
         Shape sh;
@@ -2175,8 +2230,8 @@ void dc_destroy(dc_ctx *ctx) {
         if (sv.aux) (void)hipStreamDestroy(sv.aux);
     }
     if (quiet) {
-        for (auto &b : ctx->batches)
-            if (b->dmem) (void)hipFree(b->dmem);
+        for (int *m : ctx->slabs) (void)hipFree(m);
+        if (ctx->pinned) (void)hipHostFree(ctx->pinned);
         int *ptrs[] = {ctx->d_state, ctx->d_init, ctx->d_xs, ctx->d_colpart, ctx->d_tmeta, ctx->d_tcount, ctx->d_grid,
                        ctx->d_ysort, ctx->d_runs};
         for (int *p : ptrs)
@@ -2189,7 +2244,6 @@ void dc_destroy(dc_ctx *ctx) {
         if (ctx->d_tscore) (void)hipFree(ctx->d_tscore);
     } else {
         std::fprintf(stderr, "libdcsched: the device did not finish this context's work; its memory is left allocated\n");
-        for (auto &b : ctx->batches) b->pinned = nullptr;   // left allocated too
     }
     if (ctx->ev0) (void)hipEventDestroy(ctx->ev0);
     if (ctx->ev1) (void)hipEventDestroy(ctx->ev1);
