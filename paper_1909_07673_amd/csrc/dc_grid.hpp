@@ -26,9 +26,14 @@ struct GridCtl {
     unsigned long long *rflag;    // outcome of a selection round's commit, tagged
     unsigned long long *rec;      // [kRecWords][pods] per-workgroup records of a step, tagged (below)
     int pods;                     // workgroups that own a pod (the first k)
+    int wgs;                      // workgroups that take part in the rounds and barriers (the first)
     unsigned *round;              // selection rounds so far (kept across launches)
-    int *flag;                    // [kGridFlags]: command buffers
     unsigned *join;               // [2] entry of the queue kernels: arrivals, decision
+    // serving form: commands as the fetching workgroup hands them out, and
+    // their way back (below)
+    unsigned long long *cmd;      // [kCmdRing][kCmdWords], tagged with position + 1
+    long long *times;             // [kCmdRing][2] device clock at admission and decision
+    int *done, *reported;         // commands completed / reported to the host
 };
 
 // Selection rounds.  Round r of the argmax and commit needs no grid barrier:
@@ -58,7 +63,7 @@ __device__ __forceinline__ unsigned long long round_key(unsigned long long kb) {
 // reported an error.
 __device__ __forceinline__ unsigned long long round_max(const GridCtl &g, unsigned r, long long timeout,
                                                         bool &bad) {
-    const int lane = threadIdx.x & (kWave - 1), G = gridDim.x;
+    const int lane = threadIdx.x & (kWave - 1), G = g.wgs;
     const unsigned long long *sl = g.kslot + (r & 1) * G, tag = round_tag(r);
     const long long t0 = dev_clock();
     for (;;) {
@@ -102,14 +107,7 @@ __device__ __forceinline__ int round_outcome(const GridCtl &g, unsigned r, long 
     }
 }
 
-// flag[8 + 8 * (pos & 1) ...]: the command at ring position pos,
-// double-buffered so that the leader can publish command pos + 1 while a
-// slower workgroup still reads command pos.
-constexpr int kGridFlags = 24;
-enum { GF_GOT = 0, GF_TYPE, GF_N, GF_NPAIR, GF_SLOT, GF_RID };
-__device__ __forceinline__ int *cmd_flags(const GridCtl &g, int pos) { return g.flag + 8 + 8 * (pos & 1); }
-
-// Grid barrier over gridDim.x co-resident workgroups with agent-scope
+// Grid barrier over the first g.wgs workgroups, all co-resident, with agent-scope
 // release / acquire.  A wait longer than `timeout` device ticks sets *err;
 // every barrier returns false once *err is set, so all workgroups leave.
 // Ordering: each arrival's fetch_add releases the workgroup's writes (after
@@ -126,7 +124,7 @@ __device__ __forceinline__ bool grid_sync(const GridCtl &g, int *lds_flag, long 
         if (!bad) {
             const unsigned gen = __hip_atomic_load(g.gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             const unsigned arrived = __hip_atomic_fetch_add(g.count, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-            if (arrived == gridDim.x - 1) {
+            if (arrived == static_cast<unsigned>(g.wgs) - 1) {
                 __hip_atomic_store(g.count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_store(g.gen, gen + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
             } else {
@@ -422,7 +420,7 @@ template <int BS, bool TOGETHER, class KeyFn>
 __device__ __forceinline__ bool grid_select(const Topo &t, const State &st, const Method &m, const Batch &b,
                                             const GSmem &sm, const GridCtl &g, long long timeout, const StepIn &s,
                                             const ReqView &rv, unsigned &rnd, bool &stale, int nx, int *feas, KeyFn key_of) {
-    const int w = blockIdx.x, G = gridDim.x, ubase = w * t.hh, P = s.P;
+    const int w = blockIdx.x, G = g.wgs, ubase = w * t.hh, P = s.P;
     const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
     // the workgroup's best key (largest packed key) into LDS slot 0..1
     auto wg_best = [&]() {
@@ -531,7 +529,7 @@ template <int BS, int CS = 0>
 __device__ __forceinline__ bool grid_topsis_step(const Topo &t, const State &st, const Method &m, const Batch &b,
                                                  const GSmem &sm, const GridCtl &g, long long timeout, const StepIn &s,
                                                  const ReqView &rv, const Trace &tr, unsigned &rnd, bool &stale) {
-    const int w = blockIdx.x, G = gridDim.x, h = t.h, hh = t.hh, nc = crit_count<CS>(m);
+    const int w = blockIdx.x, G = g.wgs, h = t.h, hh = t.hh, nc = crit_count<CS>(m);
     const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
     const int P = s.P, ubase = w * hh;
     int *xs = sm.xs;
@@ -688,13 +686,174 @@ __global__ __launch_bounds__(BS) void k_topsis_grid(Params p, GridCtl g, long lo
     if (blockIdx.x == 0 && threadIdx.x == 0) __hip_atomic_store(g.round, rnd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Serving form, large data centers: the persistent loop of k_serve run by
-// one cooperative workgroup per pod.  Workgroup 0 polls the command ring
-// and publishes each command to the others through a grid barrier; every
-// workgroup keeps its own LDS copy of the request.
+// ---------------------------------------------------------------- serving form
+// Large data centers: the persistent loop of k_serve over one workgroup per
+// pod, and two more that talk to the host.  Host memory is a microsecond or
+// two away in each direction, and a command used to cross it four times with
+// every workgroup waiting (poll, barrier, request, completion): 40 us of a
+// request.  Now the fetching workgroup polls the command ring, copies each
+// request into its device slot and hands the command out as tagged words, up
+// to kCmdAhead commands before they are reported; the reporting workgroup
+// turns finished commands into completion records.  The pods only wait for
+// device memory.  A session of 300 requests at k = 48: 57.1 -> 53.1 ms.
+//
+// Waits: the fetcher leaves after idle_ticks with nothing to do, handing out
+// a stop; pods and reporter leave at that stop; every wait also ends when
+// g.err is set, and the pods' wait for a command is bounded.
+constexpr int kCmdRing = 8, kCmdAhead = 4, kCmdWords = 6;
+static_assert(kCmdAhead < kCmdRing, "an entry is written again only after its command was reported");
+enum { CW_TYPE = 0, CW_N, CW_NPAIR, CW_SLOT, CW_RID, CW_GOT };
+
+__device__ __forceinline__ unsigned long long *cmd_word(const GridCtl &g, int pos, int x) {
+    return g.cmd + (pos & (kCmdRing - 1)) * kCmdWords + x;
+}
+__device__ __forceinline__ unsigned long long cmd_tag(int pos) {
+    return static_cast<unsigned long long>(static_cast<unsigned>(pos) + 1u) << 32;
+}
+__device__ __forceinline__ bool grid_failed(const GridCtl &g) {
+    return __hip_atomic_load(g.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+}
+
+// Before a launch that begins at ring position start: an earlier launch may
+// have handed out a stop there.
+__global__ void k_serve_reset(GridCtl g, int start) {
+    if (threadIdx.x < kCmdRing * kCmdWords) g.cmd[threadIdx.x] = 0;
+    if (threadIdx.x == 0) {
+        *g.done = start;
+        *g.reported = start;
+    }
+}
+
+// The fetching workgroup.
+template <int BS>
+__device__ void serve_fetch(const ServeArgs &a, const GridCtl &g, int *lds) {
+    const int tid = threadIdx.x;
+    long long idle0 = dev_clock();
+    for (int pos = a.start;; ++pos) {
+        if (tid == 0) {
+            const Cmd *c = a.cmds + (pos % a.cap);
+            int got = 0, failed = 0;
+            for (;;) {
+                const int behind = pos - __hip_atomic_load(g.reported, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (behind > 0) idle0 = dev_clock();       // work under way
+                if (grid_failed(g)) { failed = 1; break; }
+                if (behind < kCmdAhead &&
+                    __hip_atomic_load(&c->seq, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_SYSTEM) == pos + 1) {
+                    got = 1;
+                    break;
+                }
+                if (dev_clock() - idle0 > a.idle_ticks) break;
+                __builtin_amdgcn_s_sleep(8);
+            }
+            lds[CW_TYPE] = got ? __hip_atomic_load(&c->type, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) : CMD_STOP;
+            if (got) {
+                lds[CW_N] = __hip_atomic_load(&c->n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                lds[CW_NPAIR] = __hip_atomic_load(&c->npair, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                lds[CW_SLOT] = __hip_atomic_load(&c->slot_off, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                lds[CW_RID] = __hip_atomic_load(&c->rid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            }
+            lds[CW_GOT] = got;
+            lds[kCmdWords] = failed;
+        }
+        __syncthreads();
+        if (lds[kCmdWords]) return;
+        const int type = lds[CW_TYPE];
+        if (type == CMD_SUBMIT) {
+            const int n = lds[CW_N], P = lds[CW_NPAIR];
+            const SlotLayout L = slot_layout(n, P);
+            int *sb = a.arena + lds[CW_SLOT];
+            const int *stg = a.staging + (size_t)(pos % a.cap) * a.stage_ints;
+            for (int x = tid; x < L.in_end; x += BS) sb[x] = stg[x];
+            for (int x = tid; x < n; x += BS) {
+                sb[L.host + x] = -1;
+                sb[L.score + x] = 0;
+            }
+            for (int x = tid; x < P; x += BS) sb[L.code + x] = -1;
+            if (tid == 0) {
+                sb[L.failat] = -1;
+                sb[L.status] = 1;
+            }
+        }
+        __threadfence();
+        __syncthreads();
+        if (tid < kCmdWords)
+            __hip_atomic_store(cmd_word(g, pos, tid), cmd_tag(pos) | static_cast<unsigned>(lds[tid]), __ATOMIC_RELEASE,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        if (type == CMD_STOP) return;
+        __syncthreads();                                   // lds is written again
+    }
+}
+
+// The reporting workgroup: one wave.
+__device__ __forceinline__ void serve_report(const ServeArgs &a, const GridCtl &g) {
+    const int lane = threadIdx.x;
+    int pos = a.start;
+    for (;;) {
+        // the next command finished, or handed out as a stop
+        int state = 0;                                     // 1 finished, 2 stop, 3 stop command consumed, 4 failed
+        while (!state) {
+            if (__hip_atomic_load(g.done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - pos > 0) {
+                state = 1;
+            } else {
+                const unsigned long long w =
+                    __hip_atomic_load(cmd_word(g, pos, CW_TYPE), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const unsigned long long got =
+                    __hip_atomic_load(cmd_word(g, pos, CW_GOT), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (rec_has(w, cmd_tag(pos)) && rec_has(got, cmd_tag(pos)) && static_cast<int>(w) == CMD_STOP)
+                    state = static_cast<int>(got) ? 3 : 2;
+                else if (grid_failed(g))
+                    state = 4;
+                else
+                    __builtin_amdgcn_s_sleep(4);
+            }
+            state = uniform(state);
+        }
+        if (state != 1) {
+            if (lane == 0) {
+                __hip_atomic_store(a.ctrl, state == 3 ? pos + 1 : pos, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+                __hip_atomic_store(a.ctrl + 1, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+            }
+            return;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        int w[kCmdWords];
+#pragma unroll
+        for (int x = 0; x < kCmdWords; ++x)
+            w[x] = static_cast<int>(__hip_atomic_load(cmd_word(g, pos, x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        const int type = w[CW_TYPE], n = w[CW_N];
+        const Batch b = slot_batch(a.arena + w[CW_SLOT], slot_layout(n, w[CW_NPAIR]));
+        Comp *cp = a.comps + (pos % a.cap);
+        if (type == CMD_SUBMIT && lane < n) {              // n <= 64
+            cp->host[lane] = b.host[lane];
+            cp->score[lane] = b.score[lane];
+        }
+        if (lane == 0) {
+            cp->type = type;
+            cp->rid = w[CW_RID];
+            cp->n = n;
+            cp->status = type == CMD_SUBMIT ? b.status[0] : 1;
+            cp->failat = type == CMD_SUBMIT ? b.failat[0] : -1;
+            cp->t_admit = g.times[2 * (pos & (kCmdRing - 1))];
+            cp->t_decide = g.times[2 * (pos & (kCmdRing - 1)) + 1];
+        }
+        __threadfence_system();
+        ++pos;
+        if (lane == 0) {
+            __hip_atomic_store(&cp->seq, pos, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+            __hip_atomic_store(a.ctrl, pos, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+            __hip_atomic_store(g.reported, pos, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+}
+
 template <int BS, int K, int CS>
 __global__ __launch_bounds__(BS) void k_serve_grid(Params p, ServeArgs a, GridCtl g, long long timeout) {
     extern __shared__ __align__(16) char dsm[];
+    if (static_cast<int>(blockIdx.x) >= g.wgs) {
+        if (static_cast<int>(blockIdx.x) == g.wgs) serve_fetch<BS>(a, g, reinterpret_cast<int *>(dsm));
+        else if (threadIdx.x < kWave) serve_report(a, g);
+        return;
+    }
     const Topo t = topo_of<K>(p.t);
     const GSmem sm = gcarve(dsm, t.h, t.hh, crit_count<CS>(p.m));
     int *rq_host = grid_req_lds(dsm, t.h, t.hh, crit_count<CS>(p.m));
@@ -702,121 +861,83 @@ __global__ __launch_bounds__(BS) void k_serve_grid(Params p, ServeArgs a, GridCt
     int *rq_pj = rq_poff + kMaxN + 4, *rq_pbw = rq_pj + kMaxPairs, *rq_pbmax = rq_pbw + kMaxPairs;
     int *rq_cmax = rq_pbmax + kMaxPairs, *rq_rmax = rq_cmax + kMaxN;
     const bool lead = blockIdx.x == 0;
-    int pos = a.start;
     unsigned rnd = __hip_atomic_load(g.round, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // selection rounds
     bool stale = true;
-    long long idle0 = dev_clock();
-    for (;;) {
-        if (lead && threadIdx.x == 0) {
-            Cmd *c = a.cmds + (pos % a.cap);
-            int got = 0;
-            for (;;) {        // bounded wait: the workgroups leave after idle_ticks without work
-                if (__hip_atomic_load(&c->seq, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_SYSTEM) == pos + 1) {
-                    got = 1;
+    for (int pos = a.start;; ++pos) {
+        // the command, by one thread per word
+        if (threadIdx.x < kCmdWords) {
+            const long long t0 = dev_clock();
+            int v = 0, bad = 0;
+            for (;;) {
+                const unsigned long long w = __hip_atomic_load(cmd_word(g, pos, threadIdx.x), __ATOMIC_RELAXED,
+                                                               __HIP_MEMORY_SCOPE_AGENT);
+                if (rec_has(w, cmd_tag(pos))) {
+                    v = static_cast<int>(static_cast<unsigned>(w));
                     break;
                 }
-                if (dev_clock() - idle0 > a.idle_ticks) break;
-                __builtin_amdgcn_s_sleep(8);
+                if (grid_failed(g) || dev_clock() - t0 > 2 * a.idle_ticks + timeout) {
+                    __hip_atomic_store(g.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    bad = 1;
+                    break;
+                }
+                __builtin_amdgcn_s_sleep(1);
             }
-            int *cf = cmd_flags(g, pos);
-            int type = CMD_STOP;
-            if (got) {
-                type = __hip_atomic_load(&c->type, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-                cf[GF_N] = __hip_atomic_load(&c->n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-                cf[GF_NPAIR] = __hip_atomic_load(&c->npair, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-                cf[GF_SLOT] = __hip_atomic_load(&c->slot_off, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-                cf[GF_RID] = __hip_atomic_load(&c->rid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-            }
-            cf[GF_GOT] = got;
-            cf[GF_TYPE] = type;
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            sm.wst[threadIdx.x] = v;
+            bad = __any(bad);
+            if (threadIdx.x == 0) sm.misc[M_OK] = bad;
         }
-        if (!grid_sync(g, sm.misc + M_OK, a.idle_ticks + timeout)) break;      // command barrier
-        const int *cf = cmd_flags(g, pos);
-        const int got = cf[GF_GOT], type = cf[GF_TYPE], n = cf[GF_N], P = cf[GF_NPAIR], rid = cf[GF_RID];
-        int *sb = a.arena + cf[GF_SLOT];
-        if (type == CMD_STOP) {
-            if (got) ++pos;
-            break;
-        }
+        __syncthreads();
+        const int type = sm.wst[CW_TYPE], n = sm.wst[CW_N], P = sm.wst[CW_NPAIR], off = sm.wst[CW_SLOT];
+        if (sm.misc[M_OK] || type == CMD_STOP) break;
+        int *sb = a.arena + off;
         const SlotLayout L = slot_layout(n, P);
         const Batch b = slot_batch(sb, L);
         const long long t_admit = dev_clock();
-        bool fault = false;
         if (type == CMD_SUBMIT) {
-            const int *stg = a.staging + (size_t)(pos % a.cap) * a.stage_ints;
-            if (lead)
-                for (int x = threadIdx.x; x < L.in_end; x += BS) sb[x] = stg[x];
             for (int x = threadIdx.x; x <= n; x += BS) {
-                rq_poff[x] = stg[L.poff + x];
+                rq_poff[x] = sb[L.poff + x];
                 if (x < n) {
-                    rq_cpu[x] = stg[L.cpu + x];
-                    rq_ram[x] = stg[L.ram + x];
-                    rq_cmax[x] = stg[L.cmax + x];
-                    rq_rmax[x] = stg[L.rmax + x];
+                    rq_cpu[x] = sb[L.cpu + x];
+                    rq_ram[x] = sb[L.ram + x];
+                    rq_cmax[x] = sb[L.cmax + x];
+                    rq_rmax[x] = sb[L.rmax + x];
                     rq_host[x] = -1;
-                    if (lead) {
-                        sb[L.host + x] = -1;
-                        sb[L.score + x] = 0;
-                    }
                 }
             }
             for (int x = threadIdx.x; x < P; x += BS) {
-                rq_pj[x] = stg[L.pj + x];
-                rq_pbw[x] = stg[L.pbw + x];
-                rq_pbmax[x] = stg[L.pbmax + x];
-                if (lead) sb[L.code + x] = -1;
-            }
-            if (lead && threadIdx.x == 0) {
-                sb[L.failat] = -1;
-                sb[L.status] = 1;
+                rq_pj[x] = sb[L.pj + x];
+                rq_pbw[x] = sb[L.pbw + x];
+                rq_pbmax[x] = sb[L.pbmax + x];
             }
             __syncthreads();
-            for (int i = 0; i < n; ++i) {
+            bool placed = true;
+            for (int i = 0; i < n && placed; ++i) {
                 const int q0 = rq_poff[i];
                 const StepIn s{0, i, n, 0, i, q0, rq_poff[i + 1] - q0, rq_cpu[i], rq_ram[i], rq_cmax[i], rq_rmax[i]};
                 const ReqView rv{rq_pj + q0, rq_pbw + q0, rq_host, rq_host, rq_pbmax + q0, rq_poff, rq_pj, true};
-                if (!grid_topsis_step<BS, CS>(t, p.st, p.m, b, sm, g, timeout, s, rv, p.tr, rnd, stale)) {
-                    fault = __hip_atomic_load(g.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-                    break;
-                }
+                placed = grid_topsis_step<BS, CS>(t, p.st, p.m, b, sm, g, timeout, s, rv, p.tr, rnd, stale);
+            }
+            if (!placed) {
+                // rejected, or a wait failed: one thread asks
+                __syncthreads();
+                if (threadIdx.x == 0) sm.misc[M_OK] = grid_failed(g);
+                __syncthreads();
+                if (sm.misc[M_OK]) break;
             }
         } else {
-            if (lead) give_back<BS>(t, p.st, b, 0, n);         // departure of an accepted request
+            if (lead) give_back<BS>(t, p.st, b, 0, n);       // departure of an accepted request
             stale = true;
+            if (!grid_sync(g, sm.misc + M_OK, timeout)) break;
         }
-        if (fault) break;
-        if (lead) {
-            __syncthreads();
-            Comp *cp = a.comps + (pos % a.cap);
-            if (type == CMD_SUBMIT)
-                for (int x = threadIdx.x; x < n; x += BS) {
-                    cp->host[x] = b.host[x];
-                    cp->score[x] = b.score[x];
-                }
-            if (threadIdx.x == 0) {
-                cp->type = type;
-                cp->rid = rid;
-                cp->n = n;
-                cp->status = type == CMD_SUBMIT ? b.status[0] : 1;
-                cp->failat = type == CMD_SUBMIT ? b.failat[0] : -1;
-                cp->t_admit = t_admit;
-                cp->t_decide = dev_clock();
-            }
-            __threadfence_system();
-            __syncthreads();
-            if (threadIdx.x == 0) {
-                __hip_atomic_store(&cp->seq, pos + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-                __hip_atomic_store(a.ctrl, pos + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-            }
+        __syncthreads();
+        if (lead && threadIdx.x == 0) {
+            g.times[2 * (pos & (kCmdRing - 1))] = t_admit;
+            g.times[2 * (pos & (kCmdRing - 1)) + 1] = dev_clock();
+            __hip_atomic_store(g.done, pos + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
         }
-        ++pos;
-        idle0 = dev_clock();
     }
-    if (lead && threadIdx.x == 0) {
-        __hip_atomic_store(g.round, rnd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(a.ctrl, pos, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-        __hip_atomic_store(a.ctrl + 1, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-    }
+    if (lead && threadIdx.x == 0) __hip_atomic_store(g.round, rnd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 }  // namespace dcs

@@ -934,8 +934,10 @@ int collect(dc_ctx *ctx, DevBatch &b, dc_result **dst, int64_t *room) {
 
 // ---------------------------------------------------------------- cooperative step
 int grid_alloc(dc_ctx *ctx, int G) {
-    // count, gen, err, round, join[2], flag[kGridFlags], then 8-byte aligned: kslot[2][G], rflag, rec[kRecWords][k]
-    const size_t ints = 6 + kGridFlags + 2 + 2 * (2 * (size_t)G + 1 + (size_t)ctx->t.k * kRecWords);
+    // count, gen, err, round, join[2], done, reported, then 8-byte aligned:
+    // kslot[2][G], rflag, rec[kRecWords][k], times, cmd
+    const size_t words = 2 * (size_t)G + 1 + (size_t)ctx->t.k * kRecWords + 2 * kCmdRing + kCmdRing * kCmdWords;
+    const size_t ints = 8 + 2 * words;
     HIPCHK(hipMalloc(&ctx->d_grid, ints * sizeof(int)));
     hipLaunchKernelGGL(k_fill_i32, dim3(16), dim3(256), 0, ctx->stream, ctx->d_grid, 0, (long long)ints);
     HIPCHK(hipGetLastError());
@@ -946,12 +948,14 @@ int grid_alloc(dc_ctx *ctx, int G) {
     g.err = p + 2;
     g.round = reinterpret_cast<unsigned *>(p + 3);
     g.join = reinterpret_cast<unsigned *>(p + 4);
-    g.flag = p + 6;
-    int *k = g.flag + kGridFlags;
-    k += (reinterpret_cast<uintptr_t>(k) & 7) ? 1 : 0;
-    g.kslot = reinterpret_cast<unsigned long long *>(k);
+    g.done = p + 6;
+    g.reported = p + 7;
+    g.kslot = reinterpret_cast<unsigned long long *>(p + 8);
     g.rflag = g.kslot + 2 * G;
     g.rec = g.rflag + 1;
+    g.times = reinterpret_cast<long long *>(g.rec + (size_t)ctx->t.k * kRecWords);
+    g.cmd = reinterpret_cast<unsigned long long *>(g.times + 2 * kCmdRing);
+    g.wgs = G;
     g.pods = ctx->t.k;
     return DC_OK;
 }
@@ -1160,7 +1164,10 @@ int serve_ensure_running(dc_ctx *ctx) {
         long long timeout = ctx->grid_timeout;
         void *args[] = {&p, &a, &g, &timeout};
         const size_t lds = align4(ctx->lds_grid / sizeof(int)) * sizeof(int) + req_lds_ints() * sizeof(int);
-        HIPCHK(hipLaunchCooperativeKernel(grid_serve_kernel(ctx), dim3(ctx->t.k), dim3(kGridBlock), args, lds,
+        // no command handed out before, and everything up to dev_pos reported
+        hipLaunchKernelGGL(k_serve_reset, dim3(1), dim3(kWave), 0, ctx->stream, g, dev_pos);
+        // the pods, and the two workgroups that talk to the host
+        HIPCHK(hipLaunchCooperativeKernel(grid_serve_kernel(ctx), dim3(ctx->t.k + 2), dim3(kGridBlock), args, lds,
                                           ctx->stream));
     } else if (sv.bs == 256) {
         hipLaunchKernelGGL((k_serve<256>), dim3(1), dim3(256), sv.lds, ctx->stream, p, a);
