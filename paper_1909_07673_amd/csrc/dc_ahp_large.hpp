@@ -196,7 +196,11 @@ __device__ __forceinline__ void row_block(const Params &p, const AhpLarge &a, in
         const float rq = rcp2(q);
         const float llo = saaty_level(pmin, q, rmin, rq);
         const float lhi = in ? saaty_level(pmax, q, rmax, rq) : llo;
-        if (__all(lhi - llo <= 1.f)) {
+        if (__all(lhi == llo)) {
+            const float e = level2520(sign * llo);
+#pragma unroll
+            for (int r = 0; r < R; ++r) acc[r] = fmaf(e, si, acc[r]);
+        } else if (__all(lhi - llo <= 1.f)) {
             const float elo = level2520(sign * llo), ehi = level2520(sign * lhi);
             const int from = static_cast<int>(level_from(lhi, q));
 #pragma unroll

@@ -654,8 +654,7 @@ void launch_plain_step(dc_ctx *ctx, const Params &p) {
         ctx->last_launches += 1;
     } else {
         const int bx = (ctx->N + kAhpBlock - 1) / kAhpBlock;
-        // criteria over several workgroups, each with G * BS servers at a time
-        const int ncw = (ctx->N + host_group(BS) * BS - 1) / (host_group(BS) * BS);
+        const int ncw = (ctx->N + BS - 1) / BS;        // criteria: BS servers a workgroup
         if (BS == 1024 && specialised_ahp5(ctx, kAhpK))
             hipLaunchKernelGGL((k_criteria_plain<1024, kAhpK, 5>), dim3(ncw), dim3(BS), ctx->lds_plain, ctx->stream,
                                p);

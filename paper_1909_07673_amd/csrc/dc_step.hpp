@@ -716,13 +716,18 @@ __device__ __forceinline__ void rollback_request(const Topo &t, const State &st,
 //   E[eg] = max_a min(ea(eg, a), ea(ev, a), T[(p, a)] or +inf in pod pv)   eg != ev
 // so that the widest shortest path from u to v has bottleneck
 // min(up[u], up[v], E[edge(u)]) (or min(up[u], up[v]) on the same edge).
-// peer_pod(pc): the pod of peer pbeg + pc.
+// peer_pod(pc): the pod of peer pbeg + pc.  Sw: the switches wanted, whole
+// pods of them (all, or those above a workgroup's servers).
+struct Switches {
+    int first, n;
+};
 template <int BS, class PeerPod>
 __device__ __forceinline__ void table_T(const Topo &t, const State &st, const Smem &sm, int pbeg, int pn,
-                                        PeerPod peer_pod) {
-    const int tot = pn * t.nsw;
+                                        PeerPod peer_pod, const Switches *sw = nullptr) {
+    const int tot = pn * (sw ? sw->n : t.nsw);
     for (int it = threadIdx.x; it < tot; it += BS) {
-        const int pc = div_floor(it, t.nsw, t.rnsw), ag = it - pc * t.nsw;
+        const int pc = sw ? it / sw->n : div_floor(it, t.nsw, t.rnsw);
+        const int ag = sw ? sw->first + it - pc * sw->n : it - pc * t.nsw;
         const int pv = peer_pod(pc), pa = edge_of(t, ag);
         int val = 0;
         if (pa != pv) {
@@ -745,15 +750,17 @@ __device__ __forceinline__ void table_T(const Topo &t, const State &st, const Sm
                     }
             }
         }
-        sm.tabT[it] = val;
+        sm.tabT[sw ? pc * t.nsw + ag : it] = val;
     }
 }
 
 template <int BS>
-__device__ __forceinline__ void table_E(const Topo &t, const State &st, const Smem &sm, int pbeg, int pn) {
-    const int tot = pn * t.nsw;
+__device__ __forceinline__ void table_E(const Topo &t, const State &st, const Smem &sm, int pbeg, int pn,
+                                        const Switches *sw = nullptr) {
+    const int tot = pn * (sw ? sw->n : t.nsw);
     for (int it = threadIdx.x; it < tot; it += BS) {
-        const int pc = div_floor(it, t.nsw, t.rnsw), eg = it - pc * t.nsw;
+        const int pc = sw ? it / sw->n : div_floor(it, t.nsw, t.rnsw);
+        const int eg = sw ? sw->first + it - pc * sw->n : it - pc * t.nsw;
         const int ed = sm.pk[pbeg + pc].y;
         const int ev = ed & 0xffff, pv = ed >> 16, pe = edge_of(t, eg);
         int val = 0;
@@ -779,7 +786,7 @@ __device__ __forceinline__ void table_E(const Topo &t, const State &st, const Sm
                     }
             }
         }
-        sm.tabE[it] = val;
+        sm.tabE[sw ? pc * t.nsw + eg : it] = val;
     }
 }
 
@@ -863,14 +870,21 @@ __device__ __forceinline__ void peer_deficits(const Smem &sm, int P) {
 // satisfies, which spare the commit loop from trying servers bound to fail:
 // the server's uplink, its edge switch's and its pod's uplinks each carry
 // the demand of the peers outside them, and the peer-side deficits.
-// With nwg > 1, workgroup wg of nwg takes every nwg-th group of G * BS
-// servers (the other workgroups build the same peer tables for theirs).
+// OWN: workgroup wg of nwg takes the wg-th group of G * BS servers only, and
+// builds the tables of the switches above them.
 // T0: the first chunk's table T was built by load_peers<.., true>.
-template <int BS, bool STATS, int G = host_group(BS), int CS = 0, bool T0 = false>
+template <int BS, bool STATS, int G = host_group(BS), int CS = 0, bool T0 = false, bool OWN = false>
 __device__ __forceinline__ void criteria_stage(const Topo &t, const State &st, const Method &m, const Smem &sm, int *xs,
                                int cpu_i, int ram_i, int P, int pc_cap, int wg = 0, int nwg = 1) {
     const int N = t.N, nc = crit_count<CS>(m);
     const int nch = P == 0 ? 1 : (P + pc_cap - 1) / pc_cap;
+    Switches own{};
+    if (OWN) {
+        const int u0 = min(wg * G * BS, N - 1), u1 = min(N, (wg + 1) * G * BS) - 1;
+        own.first = pod_of(t, u0) * t.h;
+        own.n = (pod_of(t, u1) + 1) * t.h - own.first;
+    }
+    const Switches *sw = OWN ? &own : nullptr;
     unsigned long long s2[kMaxCrit];
     int mx[kMaxCrit], mn[kMaxCrit];
 #pragma unroll
@@ -882,10 +896,10 @@ __device__ __forceinline__ void criteria_stage(const Topo &t, const State &st, c
             if (ch == 0) peer_deficits<BS>(sm, P);
             if (!(T0 && ch == 0)) {
                 if (ch > 0) __syncthreads();            // previous chunk done with the tables
-                table_T<BS>(t, st, sm, pbeg, pn, [&](int pc) { return sm.pk[pbeg + pc].y >> 16; });
+                table_T<BS>(t, st, sm, pbeg, pn, [&](int pc) { return sm.pk[pbeg + pc].y >> 16; }, sw);
                 __syncthreads();
             }
-            table_E<BS>(t, st, sm, pbeg, pn);
+            table_E<BS>(t, st, sm, pbeg, pn, sw);
             __syncthreads();
         }
         const int dh0 = sm.misc[M_DH0], dh1 = sm.misc[M_DH1];
