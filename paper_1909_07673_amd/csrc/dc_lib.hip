@@ -983,6 +983,11 @@ TopsisQueueFn topsis_queue_fn(const dc_ctx *ctx) {
                                   k_topsis_queue<kGridBlock, 0, 0>);
 }
 
+using AhpQueueFn = void (*)(Params, GridCtl, AhpGrid, unsigned, long long, long long);
+AhpQueueFn ahp_queue_fn(const dc_ctx *ctx) {
+    return ahp_queue_block(ctx->N) == kAhpQueueBlock ? k_ahp_queue<kAhpQueueBlock> : k_ahp_queue<kAhpQueueBlock / 2>;
+}
+
 // Largest value criterion c can take: residuals stay within the capacities,
 // path bandwidth within the server's uplink, hops within six per peer.
 int crit_max(const dc_ctx *ctx, int c) {
@@ -1054,9 +1059,10 @@ int queue_init(dc_ctx *ctx) {
         if (vmax >= 1 << 17 || ctx->lds_queue > kLdsMax) return DC_OK;
         // a workgroup per pod, and enough of them that a slice of a
         // criterion's ranks is one row per thread
-        ctx->queue_wgs = std::max(k, nc * ((ctx->N + kAhpQueueBlock - 1) / kAhpQueueBlock));
+        const int bs = ahp_queue_block(ctx->N);
+        ctx->queue_wgs = std::max(k, nc * ((ctx->N + bs - 1) / bs));
         if (ctx->queue_wgs > kWave) return DC_OK;
-        if (set_lds(ctx, k_ahp_queue<kAhpQueueBlock>, ctx->lds_queue)) return DC_EDEVICE;
+        if (set_lds(ctx, ahp_queue_fn(ctx), ctx->lds_queue)) return DC_EDEVICE;
         const size_t words = 3 * (size_t)nc * ctx->N;
         HIPCHK(hipMalloc(&ctx->d_words, words * sizeof(unsigned long long)));
         hipLaunchKernelGGL(k_fill_i32, dim3(64), dim3(256), 0, ctx->stream, reinterpret_cast<int *>(ctx->d_words), 0,
@@ -1082,7 +1088,7 @@ int run_queue(dc_ctx *ctx, DevBatch &b, bool *ran) {
         hipLaunchKernelGGL(topsis_queue_fn(ctx), dim3(ctx->queue_wgs), dim3(kGridBlock), ctx->lds_queue, ctx->stream, p,
                            ctx->grid, epoch, ctx->patience, kWait);
     else
-        hipLaunchKernelGGL((k_ahp_queue<kAhpQueueBlock>), dim3(ctx->queue_wgs), dim3(kAhpQueueBlock), ctx->lds_queue,
+        hipLaunchKernelGGL(ahp_queue_fn(ctx), dim3(ctx->queue_wgs), dim3(ahp_queue_block(ctx->N)), ctx->lds_queue,
                            ctx->stream, p, ctx->grid, ctx->ahp, epoch, ctx->patience, kWait);
     HIPCHK(hipGetLastError());
     HIPCHK(hipMemcpyAsync(ctx->h_ctl, ctx->grid.err, 4 * sizeof(int), hipMemcpyDeviceToHost, ctx->stream));

@@ -151,8 +151,13 @@ struct AhpGrid {
     int fbytes;               // LDS of the position table, 16-byte multiple
 };
 
+// Threads per workgroup: 1,024, and 512 up to 4,096 servers (at most eight
+// servers a thread): 24 arrivals at k = 20 took 1.72 ms with 1,024, 1.59 with
+// 512, 1.68 with 256, the scans and barriers of the larger ones against the
+// column sums of the smaller.
 constexpr int kAhpQueueBlock = 1024;
 constexpr int kAhpPerThread = kAhpSortMax / kAhpQueueBlock;
+inline int ahp_queue_block(int N) { return N > kAhpSortMax / 2 ? kAhpQueueBlock : kAhpQueueBlock / 2; }
 
 // Position in the prefix sums P with the low bits exchanged, so that the
 // threads' runs of up to eight start in different LDS banks.

@@ -101,6 +101,8 @@ C8 = (0, 1, 2, 3, 4, 5, 0, 4)
     (16, 2, 24, 20, None, None),                     # 1,024 servers: one per thread
     (18, 2, 24, 12, C5, (1, 0, 1, 0, 1)),
     (20, 4, 4, 24, None, None),
+    (24, 2, 24, 8, C5, (0, 0, 0, 0, 1)),             # 3,456: column sums shared out, 512 threads
+    (26, 2, 24, 8, None, None),                      # 4,394: 1,024 threads
     (30, 2, 32, 6, (4,), (0,)),                      # one criterion, 30 slices
     (32, 8, 64, 6, C5, (0, 0, 0, 0, 1)),             # the largest
 ])
