@@ -13,7 +13,7 @@ aggregation-core links, 0-70 % background load), each with 64-512 FCFS
 requests of 2-48 containers, TOPSIS over (CPU, RAM, active, path
 bandwidth), batched form: one persistent launch per step, replayed from a
 HIP graph, with the autotuned launch shape.  The line also carries the
-plain form on one k=16 data center (one launch per container step), the
+plain form on one k=16 data center (its queue in one launch), the
 serving form against the plain form on a k=48 Poisson trace, and the
 scoring stage alone over resident matrices.  Other workloads (--workload)
 measure the plain form, the large AHP case, the serving form and the
@@ -45,26 +45,26 @@ VALU_LANE_OPS_PACKED = 157.3e12 / 2
 WORKLOADS = {
     "plain": dict(preset="plain", mode="plain", method="topsis",
                   text="k=16 fat-tree (1024 hosts), 2000 FCFS requests of 2-32 containers, 0-70% background, "
-                       "TOPSIS on CPU/RAM/active/path-bw, plain form (one launch per container step)"),
+                       "TOPSIS on CPU/RAM/active/path-bw, plain form (the queue in one launch)"),
     "batched": dict(preset="batched", mode="batched", method="topsis",
                     text="256 independent k=16 fat-trees (1024 hosts each), 64-512 requests of 2-48 containers "
                          "per instance, TOPSIS, batched form (one persistent launch)"),
     "ahp": dict(preset="ahp", mode="plain", method="ahp",
                 text="k=32 fat-tree (8192 hosts), 500 FCFS requests of 8-64 containers, 0-70% background, AHP "
-                     "(Saaty 1-9) on CPU/RAM/uplink/path-bw/hops(cost), seven launches per container step "
+                     "(Saaty 1-9) on CPU/RAM/uplink/path-bw/hops(cost), the queue in one launch "
                      "(criteria, run sort, run merge, column sums, row sums, global priority, select)"),
     "pods": dict(preset="pods", mode="plain", method="topsis",
                  text="k=16 fat-tree (1024 hosts), 2000 FCFS requests of 2-32 containers with up to half of each "
                       "request's containers in pods of 2-4 (one placement per pod), 0-70% background, TOPSIS, "
-                      "plain form (one launch per pod step)"),
+                      "plain form (the queue in one launch)"),
     "route_end": dict(preset="plain", mode="plain", method="topsis", routing=1,
                       text="k=16 fat-tree (1024 hosts), 2000 FCFS requests of 2-32 containers, 0-70% background, "
                            "TOPSIS, links routed after each request's last container (one wave per pair on the "
-                           "residuals the placement left), plain form (one launch per container step)"),
+                           "residuals the placement left), plain form (the queue in one launch)"),
     "ranges": dict(preset="ranges", mode="plain", method="topsis",
                    text="k=16 fat-tree (1024 hosts), 2000 FCFS requests of 2-32 containers with up to half in pods "
                         "and demands as [min, 2 x min] intervals (each placement given up to the maximum), 0-70% "
-                        "background, TOPSIS, plain form (one launch per pod step)"),
+                        "background, TOPSIS, plain form (the queue in one launch)"),
     "paper_e2": dict(preset=None, mode="events", method="topsis",
                      text="the paper's GPU evaluation shape (section VI-A): k=20 fat-tree (2000 servers of 24 cores / "
                           "256 GB, 1 Gbps links), 6000 requests of 4 containers (up to half in pods, demands as "
@@ -568,7 +568,7 @@ def run_serving(args, wl, variants_all=True):
     reqs, arr, dep = make_trace(seed=0, duration_s=args.trace_s)
     forms = {}
     # serving: the cooperative persistent kernel (the default at this size);
-    # plain: one launch per container step on one workgroup (the default);
+    # plain: the queue in one launch over one workgroup per pod (the default);
     # the other two variants for comparison
     variants = (("serving", dc.DC_MODE_SERVING, 0), ("plain", dc.DC_MODE_PLAIN, 0),
                 ("serving_1wg", dc.DC_MODE_SERVING, 1), ("plain_grid", dc.DC_MODE_PLAIN, 2))

@@ -101,19 +101,29 @@ typedef struct dc_config {
     const int32_t *link_used; /* nullable host array [n_instances][3][N]: Mbps already in use     */
     void *stream;           /* hipStream_t to launch on (e.g. torch's), NULL = own stream */
     size_t mem_budget;      /* serving: device bytes for live request slots (0 = 256 MiB) */
-    int32_t block;          /* threads per workgroup, 0 = automatic / autotuned     */
+    int32_t block;          /* threads per workgroup, 0 = automatic / autotuned (a size
+                               asked for keeps to one workgroup per TOPSIS step and
+                               one launch per AHP stage)                           */
     int32_t trace_stride;   /* record the score vector of every trace_stride-th step (0 = off) */
     int32_t trace_cap;      /* at most this many recorded steps                     */
-    int32_t grid;           /* TOPSIS plain and serving forms: 0 = automatic (the
-                               serving form from k = 32 on runs one cooperative
-                               workgroup per pod; the plain form one workgroup),
-                               1 = one workgroup per step, 2 = one workgroup per pod */
+    int32_t grid;           /* plain and serving forms: 0 = automatic.  Plain: a
+                               queue in one launch, TOPSIS on one workgroup where
+                               the state fits its LDS and on one per pod beyond,
+                               AHP (1-9 scale, up to 8,192 servers) over several;
+                               serving from k = 32 on: one workgroup per pod.
+                               1 = one workgroup per TOPSIS step (plain AHP: one
+                               launch per stage), 2 = TOPSIS on one workgroup per
+                               pod, launched cooperatively.  No choice changes a
+                               result.                                            */
     int32_t graph;          /* batched form: 0 = automatic (on), 1 = launch directly,
                                2 = capture each queued batch's launch in a HIP graph
                                once per workgroup size and replay it afterwards   */
     int32_t grid_timeout_us; /* cooperative step: longest wait at one grid barrier
                                before the step gives up and the context reports
-                               DC_EDEVICE (0 = 100000 us)                         */
+                               DC_EDEVICE (0 = 100000 us).  Plain queue over
+                               several workgroups: longest wait for them to meet
+                               before the queue runs launch by launch instead
+                               (0 = 20000 us)                                     */
     int32_t routing;        /* 0 = each unit's links are routed when it is placed;
                                1 = a request's links are routed after its last
                                unit is placed (section V-D): every pair's widest

@@ -1036,7 +1036,18 @@ int large_init(dc_ctx *ctx) {
 // block size asked for).  TOPSIS where the state does not fit one workgroup
 // (from k = 22 on): a step over one workgroup per pod.  AHP on the 1-9 scale
 // up to 8,192 servers, where the position table of every criterion fits LDS
-// beside the prefix sums.
+// beside the prefix sums.  A device (or a partition of one) that cannot hold
+// all the workgroups at once keeps to one launch per step.
+template <class F>
+bool all_resident(F kernel, int block, size_t lds, int wgs) {
+    int dev = 0, cus = 0, per = 0;
+    return hipGetDevice(&dev) == hipSuccess &&
+           hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+           hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, reinterpret_cast<const void *>(kernel), block, lds) ==
+               hipSuccess &&
+           (long long)per * cus >= wgs;
+}
+
 int queue_init(dc_ctx *ctx) {
     const dc_config &cfg = ctx->cfg;
     if (cfg.mode != DC_MODE_PLAIN || ctx->I != 1 || cfg.grid != 0 || cfg.block != 0) return DC_OK;
@@ -1046,6 +1057,7 @@ int queue_init(dc_ctx *ctx) {
         ctx->queue_wgs = k;
         ctx->lds_queue = align4(gsmem_bytes(h, hh, nc) / sizeof(int)) * sizeof(int) + kQueueReqInts * sizeof(int);
         if (set_lds(ctx, topsis_queue_fn(ctx), ctx->lds_queue)) return DC_EDEVICE;
+        if (!all_resident(topsis_queue_fn(ctx), kGridBlock, ctx->lds_queue, k)) return DC_OK;
         ctx->queue = dc_ctx::QUEUE_TOPSIS;
     } else {
         if (!ctx->ahp_sorted) return DC_OK;
@@ -1063,6 +1075,7 @@ int queue_init(dc_ctx *ctx) {
         ctx->queue_wgs = std::max(k, nc * ((ctx->N + bs - 1) / bs));
         if (ctx->queue_wgs > kWave) return DC_OK;
         if (set_lds(ctx, ahp_queue_fn(ctx), ctx->lds_queue)) return DC_EDEVICE;
+        if (!all_resident(ahp_queue_fn(ctx), bs, ctx->lds_queue, ctx->queue_wgs)) return DC_OK;
         const size_t words = 3 * (size_t)nc * ctx->N;
         HIPCHK(hipMalloc(&ctx->d_words, words * sizeof(unsigned long long)));
         hipLaunchKernelGGL(k_fill_i32, dim3(64), dim3(256), 0, ctx->stream, reinterpret_cast<int *>(ctx->d_words), 0,
