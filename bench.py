@@ -319,10 +319,10 @@ TILE_T, TILE_C, TILE_N = 32768, 4, 1024
 # (their SHA-256); reported as null otherwise.
 TILE_TRAFFIC = {
     "sources": ('paper_1909_07673_amd/csrc/dc_tiles.hpp', 'paper_1909_07673_amd/csrc/dc_step.hpp'),
-    "sha256": "08556909eae8570b3b7579798445f363612b5a483a503d8710709e86ecb2d892",
+    "sha256": "7f40e27858c634f483e1c549eac37205c1597e55ba84af80211d89e26e99c67d",
     "copy_kib": 524288.0,
-    "fetch_kib": 262212.31, "fetch_copy_kib": 262162.13,
-    "write_kib": 517.64, "write_copy_kib": 524288.0,
+    "fetch_kib": 262221.28, "fetch_copy_kib": 262161.69,
+    "write_kib": 517.75, "write_copy_kib": 524288.0,
 }
 # the batched kernel at the default workload (taken with
 # `bench.py --workload batched --no-extras --no-cpu-baseline --steps 1
@@ -331,9 +331,9 @@ TILE_TRAFFIC = {
 # launch shape (workgroup size, servers per thread, peer chunk) does not change
 BATCHED_TRAFFIC = {
     "sources": ('paper_1909_07673_amd/csrc/dc_kernels.hpp', 'paper_1909_07673_amd/csrc/dc_step.hpp'),
-    "sha256": "ca7aa44e0890ffe041a6034f91d4e5c7c362a0e19566e8175c74f09c93c173b4",
+    "sha256": "b58b057989f0b14d4ab17054baae64a0b8baf872abe75894376e02df82742d70",
     "copy_kib": 524288.0,
-    "fetch_kib": 119050.13, "fetch_copy_kib": 262161.5,
+    "fetch_kib": 119034.38, "fetch_copy_kib": 262162.06,
     "write_kib": 39380.88, "write_copy_kib": 524288.0,
 }
 

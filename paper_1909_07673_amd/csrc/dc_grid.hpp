@@ -14,8 +14,9 @@
 namespace dcs {
 
 // Threads per pod workgroup.  The step is bound by memory latency and the
-// waits between workgroups, not by threads: 1024 threads measured no faster
-// than 256.
+// waits between workgroups: a session of 300 requests at k = 48 (576 servers a
+// pod) took 62.6 ms with 256 threads, 60.3 with 512, 65.8 with 576 and 84.7
+// with 1,024, where registers spill.
 constexpr int kGridBlock = 512;
 
 // Cross-workgroup state, in device memory.

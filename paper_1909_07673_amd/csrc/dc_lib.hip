@@ -448,7 +448,7 @@ Params base_params(dc_ctx *ctx, const DevBatch &b, int inst) {
 // status[R] (1), then score[Ct], tsb[R], tse[R] (0; the stamps are int64).
 int reset_outputs(dc_ctx *ctx, DevBatch &b) {
     const long long neg = (long long)b.Ct + b.Pt + b.R, all = (long long)b.out_ints;
-    hipLaunchKernelGGL(k_reset_outputs, dim3((unsigned)std::min<long long>(64, (all + 255) / 256)), dim3(256), 0,
+    hipLaunchKernelGGL(k_reset_outputs, dim3((unsigned)std::min<long long>(2048, (all + 255) / 256)), dim3(256), 0,
                        ctx->stream, b.dmem + b.in_ints, neg, neg + b.R, all);
     HIPCHK(hipGetLastError());
     return DC_OK;
