@@ -1434,6 +1434,7 @@ struct TilePath {
 // Up to 1 MiB of criteria one workgroup per tile, beyond it (few tiles) the
 // split: a 27,648 x 4 tile alone took 31-35 us over seven workgroups behind
 // an allocation and a select launch, 17.7 us with one workgroup (41 us split).
+// With 4-byte loads half of that: 57 x 6 x 24,334 took 69 us, 49 split.
 constexpr long long kBigTileInts = 1 << 18;
 
 int tiles_prepare(int64_t T, int32_t C, int32_t N, const int32_t *x, const uint8_t *feasible, const int32_t *cost,
@@ -1461,10 +1462,15 @@ int tiles_prepare(int64_t T, int32_t C, int32_t N, const int32_t *x, const uint8
     // fewest wavefronts whose registers hold the tile: 4V servers per thread
     // and criterion, V a power of two with C * V <= 16 (V <= 8)
     const int vmax = C <= 2 ? 8 : C <= 4 ? 4 : 2;
+    // with 4-byte loads half of that from two criteria on: 48 loads and more
+    // a thread took longer than reading the tile twice (1,024 x 4 x 2,662: 48
+    // against 32 us); several wavefronts are built from vmax / 4 < V on
+    const int vcap = !vec && C > 1 && C <= 4 ? vmax / 2 : vmax;
+    const int vfirst = C <= 2 ? 4 : C <= 4 ? 2 : 1;
     int nw = 0, v = 0;
     for (int w : {1, 4, 16}) {
-        v = 1;
-        while (v < vmax && 256 * v * w < N) v *= 2;
+        v = w == 1 ? 1 : vfirst;
+        while (v < vcap && 256 * v * w < N) v *= 2;
         if (256 * v * w >= N) { nw = w; break; }
     }
     // the scratch of the two-launch split, which the calls of its range are
@@ -1476,7 +1482,7 @@ int tiles_prepare(int64_t T, int32_t C, int32_t N, const int32_t *x, const uint8
         path->kind = TILE_REG;
         path->V = v;
         path->NW = nw;
-    } else if ((long long)C * N <= kBigTileInts || !splits) {
+    } else if ((long long)C * N <= (vec ? kBigTileInts : kBigTileInts / 2) || !splits) {
         path->kind = TILE_BIG;
     } else {
         path->kind = TILE_SPLIT;
