@@ -337,10 +337,12 @@ int dc_last_timing(dc_ctx *ctx, float *ms, int64_t *launches, int64_t *steps);
  * T >= 2^31, C outside 1..DC_MAX_CRIT, N outside 1..2^20, a null x, best or
  * weight, or a weight that is not positive; DC_ENOMEM when the large-tile
  * path's partials cannot be allocated; DC_EDEVICE when the launch fails.
- * Tiles that fit the registers of one, four or sixteen wavefronts (up to
- * 32,768 servers at C <= 2, 16,384 at C <= 4, 8,192 beyond) are read once,
- * with 16-byte loads where x and scores are 16-byte aligned and N % 4 == 0.
- * Larger tiles take one workgroup each or, from 1 MiB on, several, with
+ * Tiles that fit the registers of one, four or sixteen wavefronts are read
+ * once, with 16-byte loads where x and scores are 16-byte aligned and
+ * N % 4 == 0 (up to 32,768 servers at C <= 2, 16,384 at C <= 4, 8,192
+ * beyond), otherwise with 4-byte loads (half of that at C = 2 to 4).  Larger
+ * tiles take one workgroup each or, from 1 MiB on (512 KiB with 4-byte
+ * loads), several, with
  * partials in device memory allocated on the stream for the call
  * (stream-ordered) and freed behind it. */
 int dc_topsis_tiles(int64_t T, int32_t C, int32_t N, const int32_t *x, const uint8_t *feasible,

@@ -194,3 +194,19 @@ def test_tiles_register_path_edges(T, C, N):
     torch.cuda.synchronize()
     assert np.array_equal(best, b2.cpu().numpy())
     assert bscore.tobytes() == s2.cpu().numpy().tobytes() and sc.tobytes() == sc2.cpu().numpy().tobytes()
+
+
+# sizes that are no multiple of four, where the register kernels with 4-byte
+# loads change their number of wavefronts and give way to the others
+ODD_EDGES = [(2, 1, 2049), (2, 1, 32766), (2, 2, 1023), (2, 2, 1026), (3, 2, 4567), (2, 2, 16383), (2, 2, 16385),
+             (2, 3, 511), (2, 4, 514), (3, 4, 2662), (2, 4, 8191), (2, 3, 8193), (2, 6, 21850), (2, 6, 24334)]
+
+
+@pytest.mark.parametrize("T,C,N", ODD_EDGES)
+def test_tiles_odd_size_edges(T, C, N):
+    x, feas = make_tiles(seed=T * 13 + C * 5 + N, T=T, N=N, C=C, feasible_p=0.6)
+    w = np.arange(1, C + 1) / (C * (C + 1) / 2)
+    cost = [c % 3 == 1 for c in range(C)]
+    best, bscore, sc = _run(x, feas, w, cost)
+    for t in range(T):
+        _check_tile(x[t], feas[t], w, cost, sc[t], best[t], bscore[t])
