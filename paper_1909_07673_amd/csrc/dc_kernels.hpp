@@ -494,6 +494,17 @@ __global__ __launch_bounds__(kAhpBlock) void k_ahp_sort_col(Params p) {
     }
 }
 
+// The prefix sums of 1 / colsum over the sorted positions are taken in
+// kAhpBlock chunks of 2^ahp_lg_chunk positions: each chunk's sum, an inclusive
+// scan of them that doubles its distance, then each chunk position by position
+// from the sum before it.  Every form of the 1-9 scale up to kAhpSortMax
+// servers adds in this order, so their scores are the same bit for bit.
+__host__ __device__ inline int ahp_lg_chunk(int N) {
+    int lg = 0;
+    while ((kAhpBlock << lg) < N) ++lg;
+    return lg;
+}
+
 // Pass D: row sums of the column-normalised matrix, L_c[i] * N =
 // sum_j a(i, j) / colsum[j], from prefix sums of 1 / colsum in sorted
 // order.  One partial per row (nJ = 1).  Grid (ceil(N/256), 1, nc).
@@ -506,7 +517,7 @@ __global__ __launch_bounds__(kAhpBlock) void k_ahp_sort_row(Params p) {
     __shared__ double P[kAhpSortMax + kAhpBlock + 2];
     __shared__ double sh[kAhpBlock];
     const int N = p.t.N, c = blockIdx.z, tid = threadIdx.x;
-    const int e = max((N + kAhpBlock - 1) / kAhpBlock, 1), lgE = e > 1 ? 32 - __builtin_clz(e - 1) : 0, E = 1 << lgE;
+    const int lgE = ahp_lg_chunk(N), E = 1 << lgE;
     auto at = [lgE](int q) { return q + (q >> lgE); };
     lds_load_i32<kAhpBlock>(y, p.ysort + (size_t)c * N, N);
     const double *w = p.wsort + (size_t)c * N;

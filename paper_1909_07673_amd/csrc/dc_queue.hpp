@@ -159,10 +159,18 @@ constexpr int kAhpQueueBlock = 1024;
 constexpr int kAhpPerThread = kAhpSortMax / kAhpQueueBlock;
 inline int ahp_queue_block(int N) { return N > kAhpSortMax / 2 ? kAhpQueueBlock : kAhpQueueBlock / 2; }
 
-// Position in the prefix sums P with the low bits exchanged, so that the
-// threads' runs of up to eight start in different LDS banks.
-__device__ __forceinline__ int swz(int q) { return q ^ ((q >> 3) & 7); }
-__host__ __device__ inline int ahp_p_slots(int N) { return (N + 8) & ~7; }
+// Slot of the prefix sum before position q (0 <= q <= N): those behind the
+// positions of a chunk of 2^lg lie together, their low bits exchanged by the
+// chunk's number so that the threads' chunks start in different LDS banks;
+// the one before position 0 comes first of all.
+__device__ __forceinline__ int p_slot(int q, int lg) {
+    const int E = 1 << lg, m = q - 1;
+    return (m ^ ((m >> lg) & (E - 1))) + E;
+}
+__host__ __device__ inline int ahp_p_slots(int N) {
+    const int E = 1 << ahp_lg_chunk(N);
+    return E + ((N + E - 1) & ~(E - 1));
+}
 
 struct AhpSmem {
     GSmem g;              // tables over F; xs: feasibility row, then global priorities
@@ -170,6 +178,7 @@ struct AhpSmem {
     double *scan;         // [kMaxWaves]
     unsigned *F;          // [(V + 3) / 2] positions, 16 bits each
     double *P;            // [ahp_p_slots(N)]
+    double *chunk;        // [kAhpBlock] sums of chunks (over g.wst)
 };
 
 __host__ __device__ inline size_t ahp_fixed_ints(int h, int hh) {
@@ -194,6 +203,8 @@ __device__ inline AhpSmem ahp_carve(char *base, int h, int hh, int fbytes) {
     (void)carve_tabs(s.g, p, h);
     s.F = reinterpret_cast<unsigned *>(p);
     s.P = reinterpret_cast<double *>(reinterpret_cast<char *>(p) + fbytes);
+    static_assert(kAhpBlock * sizeof(double) <= kStatFields * kMaxWaves * sizeof(int), "chunk sums over the statistics slots");
+    s.chunk = reinterpret_cast<double *>(s.g.wst);
     return s;
 }
 
@@ -245,6 +256,40 @@ __device__ __forceinline__ T block_scan(T v, T *slots, T &total) {
     total = read_lane(w, BS / kWave - 1);
     const T before = wid ? read_lane(w, wid - 1) : T(0);
     return before + (inc - v);
+}
+
+// Sum of the chunks before chunk 64 wid + lane, by the tree of
+// block_excl_scan<kAhpBlock> over the chunk sums sh: a wave holds all of them,
+// four neighbours a lane, so that the eight distances need no barrier.
+__device__ __forceinline__ double chunks_before(const double *sh, int wid) {
+    static_assert(kAhpBlock == 4 * kWave, "four chunks a lane");
+    const int lane = threadIdx.x & (kWave - 1);
+    double a[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) a[j] = sh[4 * lane + j];
+    // distances 1 and 2: a neighbour's or the next lane's (wave_shr:1)
+    const double p3 = dpp_zero<0x138, 0xf>(a[3]);
+    a[3] += a[2]; a[2] += a[1]; a[1] += a[0]; a[0] += p3;
+    const double q2 = dpp_zero<0x138, 0xf>(a[2]), q3 = dpp_zero<0x138, 0xf>(a[3]);
+    a[3] += a[1]; a[2] += a[0]; a[1] += q3; a[0] += q2;
+#pragma unroll
+    for (int s = 1; s < kWave; s <<= 1) {              // distances 4 s
+        double o[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            o[j] = s == 1 ? dpp_zero<0x138, 0xf>(a[j])
+                 : s == 2 ? dpp_zero<0x138, 0xf>(dpp_zero<0x138, 0xf>(a[j])) : __shfl_up(a[j], s);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) a[j] += lane >= s ? o[j] : 0.0;
+    }
+    const int t = wid * kWave + lane - 1, src = max(t, 0) >> 2;
+    double r = 0.0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const double o = __shfl(a[j], src);
+        r = t >= 0 && (t & 3) == j ? o : r;
+    }
+    return r;
 }
 
 // The bounds of saaty_buckets for a value v, looked up: at(t) is the number
@@ -308,7 +353,11 @@ constexpr int kAhpSplitColumns = 3 * kAhpQueueBlock;
 // LDS read (the sorted form took 13 dependent reads per bound).  Column sums
 // are exact integers as before.  Where the values of a criterion fill more
 // bins than LDS holds (capacities past some 40,000 at 8,192 servers) the
-// sorted passes remain.
+// sorted passes remain.  The prefix sums of 1 / column sum take one term per
+// server in the order of those passes, so the scores do not depend on which of
+// the two ran: 1.2 to 1.5 us of a step (of 30 at 8,192 servers, 22 at 2,000)
+// more than a block scan of one term per distinct value, whose other order of
+// additions rounded a row sum in some 10^9 to the next FP32 value.
 template <int BS>
 __device__ __forceinline__ bool ahp_local_rank(const AhpSmem &sm, const AhpGrid &a, const GridCtl &g, int N, int c,
                                                bool cost, int s, int S, unsigned long long tag, long long timeout) {
@@ -343,33 +392,60 @@ __device__ __forceinline__ bool ahp_local_rank(const AhpSmem &sm, const AhpGrid 
     __syncthreads();
     if (sm.g.misc[M_OK]) return false;
     // histogram; where a wave's values repeat (path bandwidths capped by one
-    // peer's uplink), the servers with its first lane's value count as one
+    // peer's uplink), the servers with its first lane's value count as one.
+    // What is counted before a server among those of its value goes above its
+    // value (V < 2^17, N < 2^14; an array of its own would spill)
+    const int copy = tid & ((1 << lg) - 1), lane = tid & (kWave - 1);
+    auto val = [&](int e) { return v[e] & 0x1ffff; };
+    auto pos = [&](int e) { return static_cast<int>(static_cast<unsigned>(v[e]) >> 17); };
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-        if (e * BS >= N) break;
+        if (e * BS >= N) continue;
         const bool in = e * BS + tid < N;
+        unsigned was = 0;
         if (copies) {
-            if (in) atomicAdd(H + (v[e] << lg) + (tid & ((1 << lg) - 1)), 1u);
+            if (in) was = atomicAdd(H + (v[e] << lg) + copy, 1u);
         } else {
-            const int v0 = uniform(v[e]);
-            const bool same = in && v[e] == v0;
+            const int half = 16 * (v[e] & 1);
+            const bool same = in && v[e] == uniform(v[e]);
             const unsigned long long m = __ballot(same);
-            const bool first = same && (tid & (kWave - 1)) == __builtin_ctzll(m);
+            const bool first = same && lane == __builtin_ctzll(m);
             const unsigned cnt = first ? static_cast<unsigned>(__builtin_popcountll(m)) : 1u;
-            if (in && (!same || first)) atomicAdd(sm.F + (v[e] >> 1), cnt << (16 * (v[e] & 1)));
+            if (in && (!same || first)) was = atomicAdd(sm.F + (v[e] >> 1), cnt << half) >> half & 0xffffu;
+        }
+        v[e] |= static_cast<int>(was << 17);
+    }
+    if (!copies) {
+        // (apart, so that all additions are under way before one is waited for)
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            if (e * BS >= N) continue;
+            const bool same = e * BS + tid < N && val(e) == uniform(val(e));
+            const unsigned long long m = __ballot(same);
+            const int group = __builtin_amdgcn_readlane(pos(e), m ? __builtin_ctzll(m) : 0);
+            const unsigned ahead = __builtin_amdgcn_mbcnt_hi(m >> 32, __builtin_amdgcn_mbcnt_lo(m, 0));
+            if (same) v[e] = val(e) | static_cast<int>((group + ahead) << 17);
         }
     }
     __syncthreads();
     if (copies) {
+        // a value's copies, each left with the count of those before it
         for (int x = tid; x < 2 * fw; x += BS) {
             unsigned cnt = 0;
-            if (x <= V)
-                for (int y = 0; y < 1 << lg; ++y) cnt += H[(x << lg) + ((y + tid) & ((1 << lg) - 1))];
+            if (x <= V) {
+                unsigned h[8];
+#pragma unroll
+                for (int y = 0; y < 8; ++y) h[y] = y < 1 << lg ? H[(x << lg) + ((y + tid) & ((1 << lg) - 1))] : 0u;
+#pragma unroll
+                for (int y = 0; y < 8; ++y) {
+                    if (y < 1 << lg) H[(x << lg) + ((y + tid) & ((1 << lg) - 1))] = cnt;
+                    cnt += h[y];
+                }
+            }
             F16[x] = static_cast<unsigned short>(cnt);
         }
         __syncthreads();
     }
-    for (int x = tid; x < ahp_p_slots(N); x += BS) sm.P[x] = 0.0;
     // counts to positions: each thread scans an odd number of words, so the
     // threads' runs start in different banks
     {
@@ -399,8 +475,16 @@ __device__ __forceinline__ bool ahp_local_rank(const AhpSmem &sm, const AhpGrid 
     }
     __syncthreads();
     auto F = [&](int t) { return static_cast<int>(F16[t]); };
-    // 1 / column sum, times the number of servers with the value, at the
-    // value's first position (servers of equal value write the same)
+    // each server's position in ascending order (equal values in any order:
+    // their terms are the same), and at each position 1 / column sum
+    const int lgE = ahp_lg_chunk(N);
+    auto positions = [&]() {
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            if (e * BS + tid < N)
+                v[e] += static_cast<int>(F(val(e)) + (copies ? H[(val(e) << lg) + copy] : 0u)) << 17;
+        if (copies) __syncthreads();                      // H makes room for P
+    };
     SaatyBuckets rb;
     if (N > kAhpSplitColumns) {
         unsigned long long *zw = a.zw + static_cast<size_t>(c) * N;
@@ -409,46 +493,63 @@ __device__ __forceinline__ bool ahp_local_rank(const AhpSmem &sm, const AhpGrid 
             const int cs = saaty_sum<int>(rb, N, cost, [](int lo, int hi) { return hi - lo; });
             __hip_atomic_store(zw + row, tag | static_cast<unsigned>(cs), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
+        positions();
         int z[E];
         bad = !words_get<E>(g, mine, [&](int e) { return zw + e * BS + tid; }, tag, timeout, z);
         if (bad) sm.g.misc[M_OK] = 1;
 #pragma unroll
         for (int e = 0; e < E; ++e)
-            if (!bad && e * BS + tid < N) {
-                const int lv = F(v[e]);
-                sm.P[swz(lv)] = static_cast<double>(F(v[e] + 1) - lv) / static_cast<double>(z[e]);
-            }
+            if (!bad && e * BS + tid < N) sm.P[p_slot(pos(e) + 1, lgE)] = 1.0 / static_cast<double>(z[e]);
     } else {
+        positions();
 #pragma unroll
         for (int e = 0; e < E; ++e)
             if (e * BS + tid < N) {
-                const SaatyBuckets b = saaty_positions(v[e], V, N, F);
+                const SaatyBuckets b = saaty_positions(val(e), V, N, F);
                 const int cs = saaty_sum<int>(b, N, cost, [](int lo, int hi) { return hi - lo; });
-                sm.P[swz(b.lv)] = static_cast<double>(b.uv - b.lv) / static_cast<double>(cs);
+                sm.P[p_slot(pos(e) + 1, lgE)] = 1.0 / static_cast<double>(cs);
             }
         rb = saaty_positions(v[E], V, N, F);
     }
+    if (tid == 0) sm.P[0] = 0.0;
     __syncthreads();
     if (sm.g.misc[M_OK]) return false;
-    // prefix sums
+    // prefix sums, in the order of k_ahp_sort_row: four waves take a chunk a
+    // thread
     {
-        const int per = (N + BS - 1) / BS, q0 = min(N, tid * per), q1 = min(N, q0 + per);
-        double d[E], sum = 0.0, total;
+        const int len = min(N, (tid + 1) << lgE) - (tid << lgE), swap = tid & ((1 << lgE) - 1);
+        double *chunk = sm.P + ((tid + 1) << lgE);        // slot of the chunk's first
+        constexpr int U = 8;                              // terms in flight
+        if (tid < kAhpBlock) {
+            double run = 0.0;
+            for (int m = 0; m < len; m += U) {
+                double d[U];
 #pragma unroll
-        for (int j = 0; j < E; ++j) d[j] = q0 + j < q1 ? sm.P[swz(q0 + j)] : 0.0;
+                for (int j = 0; j < U; ++j) d[j] = m + j < len ? chunk[(m + j) ^ swap] : 0.0;
 #pragma unroll
-        for (int j = 0; j < E; ++j) sum += d[j];
-        double at = block_scan<BS>(sum, sm.scan, total);
-#pragma unroll
-        for (int j = 0; j < E; ++j) {
-            if (q0 + j < q1) sm.P[swz(q0 + j)] = at;
-            at += d[j];
+                for (int j = 0; j < U; ++j) run += d[j];
+            }
+            sm.chunk[tid] = run;
         }
-        if (tid == 0) sm.P[swz(N)] = total;
+        __syncthreads();
+        if (tid < kAhpBlock) {
+            double run = chunks_before(sm.chunk, uniform(tid / kWave));
+            for (int m = 0; m < len; m += U) {
+                double d[U];
+#pragma unroll
+                for (int j = 0; j < U; ++j) d[j] = m + j < len ? chunk[(m + j) ^ swap] : 0.0;
+#pragma unroll
+                for (int j = 0; j < U; ++j) {
+                    run += d[j];
+                    if (m + j < len) chunk[(m + j) ^ swap] = run;
+                }
+            }
+        }
     }
     __syncthreads();
     if (has_row) {
-        const double r = saaty_sum<double>(rb, N, !cost, [&](int lo, int hi) { return sm.P[swz(hi)] - sm.P[swz(lo)]; });
+        const double r = saaty_sum<double>(
+            rb, N, !cost, [&](int lo, int hi) { return sm.P[p_slot(hi, lgE)] - sm.P[p_slot(lo, lgE)]; });
         __hip_atomic_store(a.lw + static_cast<size_t>(c) * N + row, tag | __float_as_uint(static_cast<float>(r)),
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }

@@ -196,3 +196,32 @@ def test_ahp_large_matches_pairwise(k, up, cost):
     for f in ("status", "failed_at", "host"):
         np.testing.assert_array_equal(a[f], b[f])
     np.testing.assert_array_equal(ta, tb)
+
+
+# data centers of 8,192 servers whose residual CPU draws (numpy's generator of
+# this seed, uniform over 0..40,000; cost says which way it counts) have a row
+# sum near the middle of two FP32 values: found on the CPU as those where prefix
+# sums taken in another order of FP64 additions round it to the other one
+ROUNDING_SEEDS = [(37977, 1), (55437, 1), (57282, 1), (69294, 1), (82920, 0), (90644, 1), (96662, 1), (107159, 1)]
+
+
+@pytest.mark.parametrize("seed,cost", ROUNDING_SEEDS)
+def test_ahp_score_bits_on_every_path(seed, cost):
+    """One launch for the queue and one launch per stage (which the first falls
+    back to when its workgroups cannot meet) add the same FP64 terms in the same
+    order: every score of the step is the same bit for bit."""
+    cpu = np.random.default_rng(seed).integers(0, 40001, 8192).astype(np.int32)
+    inst = make_instance(32, 40000, 256, 40000, 100000, 100000, background=0.0, rng=np.random.default_rng(0))
+    inst.host_used = np.stack([40000 - cpu, np.zeros_like(cpu)])
+    req = make_requests(1, np.random.default_rng(1), 1, 1)[0]
+    out = []
+    for grid in (0, 1):
+        s = dc.Scheduler([inst], method=dc.DC_AHP, crit=(dc.DC_CRIT_CPU,), cost=(cost,), grid=grid, trace_stride=1,
+                         trace_cap=4)
+        s.submit(req)
+        res = s.schedule_array()
+        assert (s.last_timing()[1] == 1) == (grid == 0)
+        out.append((s.trace()[1].view(np.uint32).copy(), res["host"].copy(), s.state(0)))
+        s.close()
+    for a, b in zip(*out):
+        np.testing.assert_array_equal(a, b)
