@@ -42,7 +42,10 @@ struct GridCtl {
 // 64-bit word, tagged with r, which a wave of every workgroup polls until all
 // slots carry r (the payload is the word itself, so no fence is needed);
 // workgroup 0 then commits and publishes the outcome tagged with r (release),
-// which the others poll for (acquire).  A workgroup publishes round r + 2 in
+// which the others poll for (acquire).  A round that ends with no server left
+// has no outcome, so the outcome's word may be any number of rounds old: it
+// carries 31 bits of r (rec_tag below), where the slots, written in every
+// round, need only tell r from r - 2.  A workgroup publishes round r + 2 in
 // the same slot only after the outcome of round r + 1, which workgroup 0
 // gives only after reading every slot of round r + 1, so nothing is
 // overwritten before every workgroup has read it.  Keys are packed as
@@ -89,14 +92,21 @@ __device__ __forceinline__ unsigned long long round_max(const GridCtl &g, unsign
     }
 }
 
+// Tag of a word in its high half: 31 bits of a round's number, the top bit
+// set.
+__device__ __forceinline__ unsigned long long rec_tag(unsigned r) {
+    return static_cast<unsigned long long>(r | 0x80000000u) << 32;
+}
+__device__ __forceinline__ bool rec_has(unsigned long long v, unsigned long long tag) { return (v >> 32) == (tag >> 32); }
+
 // Thread: waits for workgroup 0's outcome of round r; -1 when the wait
 // timed out or a workgroup reported an error.
 __device__ __forceinline__ int round_outcome(const GridCtl &g, unsigned r, long long timeout) {
-    const unsigned long long tag = round_tag(r);
+    const unsigned long long tag = rec_tag(r);
     const long long t0 = dev_clock();
     for (;;) {
         const unsigned long long v = __hip_atomic_load(g.rflag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if ((v & ~kRoundPayload) == tag) {
+        if (rec_has(v, tag)) {
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
             return static_cast<int>(v & 3u);
         }
@@ -151,8 +161,8 @@ __device__ __forceinline__ bool grid_sync(const GridCtl &g, int *lds_flag, long 
 // Records of a step: instead of a grid barrier, each workgroup publishes
 // its column-statistics partials, its edge switches' and its pod's summed
 // residuals (and workgroup 0 the trace slot) as 64-bit words, the value in
-// the low half and in the high half a tag made of the number of the step's
-// first selection round with the top bit set (never 0, which the words hold
+// the low half and in the high half rec_tag of the step's
+// first selection round (never 0, which the words hold
 // initially); a reader polls a word until it carries that tag, so no fence
 // is needed.  Every word is written at every step, a step has fewer than
 // 2^31 rounds, so a word read with the current tag was written in this step.
@@ -161,9 +171,6 @@ __device__ __forceinline__ bool grid_sync(const GridCtl &g, int *lds_flag, long 
 // publishes after it has read the records.  A wave reads one word of every
 // workgroup at once, so the words are laid out by word, then workgroup: one
 // poll then takes a few cache lines a word instead of one per workgroup.
-__device__ __forceinline__ unsigned long long rec_tag(unsigned r) {
-    return static_cast<unsigned long long>(r | 0x80000000u) << 32;
-}
 constexpr int kRecWords = 80;
 constexpr int kRecCapE = 5 * kMaxCrit;            // then h edge switches (h <= 32)
 constexpr int kRecCapP = kRecCapE + 32;
@@ -178,7 +185,6 @@ __device__ __forceinline__ void rec_put(const GridCtl &g, int w, int x, unsigned
 __device__ __forceinline__ unsigned long long rec_load(const GridCtl &g, int w, int x) {
     return __hip_atomic_load(g.rec + x * g.pods + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ bool rec_has(unsigned long long v, unsigned long long tag) { return (v >> 32) == (tag >> 32); }
 
 // Thread: n words of the records (workgroup ws[j], word xs[j]) once all
 // carry tag, every poll with all its loads in flight together; false when
@@ -497,7 +503,7 @@ __device__ __forceinline__ bool grid_select(const Topo &t, const State &st, cons
                                             [&](int q) { return q == s.i ? u : rv.hosts[q]; }) ? 1 : 2;
             __syncthreads();
             if (threadIdx.x == 0) {
-                __hip_atomic_store(g.rflag, round_tag(r) | static_cast<unsigned>(res), __ATOMIC_RELEASE,
+                __hip_atomic_store(g.rflag, rec_tag(r) | static_cast<unsigned>(res), __ATOMIC_RELEASE,
                                    __HIP_MEMORY_SCOPE_AGENT);
                 sm.misc[M_RES] = res;
             }

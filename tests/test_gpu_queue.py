@@ -225,3 +225,30 @@ def test_ahp_score_bits_on_every_path(seed, cost):
         s.close()
     for a, b in zip(*out):
         np.testing.assert_array_equal(a, b)
+
+
+def test_topsis_queue_after_65535_rounds_without_outcome():
+    """A request that is placed, 65,535 that find no server (one round each,
+    none with an outcome), then requests that are placed again: the outcome the
+    workgroups waited for last is 65,536 rounds old, and must not be taken for
+    the next one.  As if the requests between had not been there."""
+    inst, reqs = _queue(22, 6, 12, 6, seed=33)
+    none = make_requests(1, np.random.default_rng(1), 1, 1)[0]
+    none.cpu = np.full(1, 33, np.int32)                  # one core more than a server has
+    want = _schedule(inst, reqs, grid=1)
+    assert want["status"][0] == 1 and want["status"][1:].sum() >= 2
+    s = dc.Scheduler([inst])
+    s.submit(reqs[0])
+    for _ in range(65535):
+        s.submit(none)
+    for r in reqs[1:]:
+        s.submit(r)
+    res = s.schedule_array()
+    assert s.last_timing()[1] == 1                        # one launch for all of them
+    assert not res["status"][1:65536].any() and not res["failed_at"][1:65536].any()
+    mine = res[[0, *range(65536, len(res))]]
+    for f in ("status", "n", "failed_at", "host"):
+        np.testing.assert_array_equal(mine[f], want[f])
+    np.testing.assert_array_equal(mine["score"].view(np.uint32), want["score"].view(np.uint32))
+    np.testing.assert_array_equal(s.state(0), want["state"])
+    s.close()
