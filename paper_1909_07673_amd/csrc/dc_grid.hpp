@@ -933,7 +933,13 @@ __global__ __launch_bounds__(BS) void k_serve_grid(Params p, ServeArgs a, GridCt
                 if (sm.misc[M_OK]) break;
             }
         } else {
-            if (lead) give_back<BS>(t, p.st, b, 0, n);       // departure of an accepted request
+            // departure of an accepted request; each thread waits for its own
+            // updates, whose last ones are atomics nobody else would wait for
+            // before thread 0 releases them all in grid_sync
+            if (lead) {
+                give_back<BS>(t, p.st, b, 0, n);
+                __threadfence();
+            }
             stale = true;
             if (!grid_sync(g, sm.misc + M_OK, timeout)) break;
         }
