@@ -721,7 +721,24 @@ __device__ __forceinline__ void rollback_request(const Topo &t, const State &st,
 struct Switches {
     int first, n;
 };
-template <int BS, class PeerPod>
+
+// f(j, true) for the n links of a switch.  RES, a state in LDS: eight in
+// flight, the last again (false) past the end, which hides the LDS latency.  A
+// state in memory, where n is no multiple of eight, spends more on the links
+// read again than it hides: a step of 12 containers at k = 22 (n = 11) took 6 %
+// longer so, at k = 26 (13) too.
+template <bool RES, class F>
+__device__ __forceinline__ void each_link(int n, F f) {
+    if (RES) {
+        for (int j0 = 0; j0 < n; j0 += 8)
+#pragma unroll
+            for (int d = 0; d < 8; ++d) f(min(j0 + d, n - 1), j0 + d < n);
+    } else {
+        for (int j = 0; j < n; ++j) f(j, true);
+    }
+}
+
+template <int BS, bool RES, class PeerPod>
 __device__ __forceinline__ void table_T(const Topo &t, const State &st, const Smem &sm, int pbeg, int pn,
                                         PeerPod peer_pod, const Switches *sw = nullptr) {
     const int tot = pn * (sw ? sw->n : t.nsw);
@@ -741,20 +758,14 @@ __device__ __forceinline__ void table_T(const Topo &t, const State &st, const Sm
                     val = max(val, max(max(min(a4.x, b4.x), min(a4.y, b4.y)), max(min(a4.z, b4.z), min(a4.w, b4.w))));
                 }
             } else {
-                // eight entries in flight, the last one repeated past the end
-                for (int j0 = 0; j0 < t.h; j0 += 8)
-#pragma unroll
-                    for (int d = 0; d < 8; ++d) {
-                        const int j = min(j0 + d, t.h - 1);
-                        val = max(val, min(x[j], y[j]));
-                    }
+                each_link<RES>(t.h, [&](int j, bool) { val = max(val, min(x[j], y[j])); });
             }
         }
         sm.tabT[sw ? pc * t.nsw + ag : it] = val;
     }
 }
 
-template <int BS>
+template <int BS, bool RES>
 __device__ __forceinline__ void table_E(const Topo &t, const State &st, const Smem &sm, int pbeg, int pn,
                                         const Switches *sw = nullptr) {
     const int tot = pn * (sw ? sw->n : t.nsw);
@@ -778,12 +789,7 @@ __device__ __forceinline__ void table_E(const Topo &t, const State &st, const Sm
                                        max(min(min(a4.z, b4.z), max(t4.z, lim)), min(min(a4.w, b4.w), max(t4.w, lim)))));
                 }
             } else {
-                for (int a0 = 0; a0 < t.h; a0 += 8)
-#pragma unroll
-                    for (int d = 0; d < 8; ++d) {
-                        const int a = min(a0 + d, t.h - 1);
-                        val = max(val, min(min(x[a], y[a]), max(T[a], lim)));
-                    }
+                each_link<RES>(t.h, [&](int a, bool) { val = max(val, min(min(x[a], y[a]), max(T[a], lim))); });
             }
         }
         sm.tabE[sw ? pc * t.nsw + eg : it] = val;
@@ -795,8 +801,9 @@ __device__ __forceinline__ void table_E(const Topo &t, const State &st, const Sm
 // the summed residuals per edge switch and per pod when LIMITS, and the
 // reset of the reduction slots.  With T0, also the aggregation table T of
 // the first pc_cap peers, each peer's pod taken from the request itself,
-// so that T needs no barrier of its own.  Ends with a barrier.
-template <int BS, bool LIMITS, bool T0 = false>
+// so that T needs no barrier of its own.  RES: as each_link.  Ends with a
+// barrier.
+template <int BS, bool LIMITS, bool T0 = false, bool RES = false>
 __device__ __forceinline__ void load_peers(const Topo &t, const State &st, const ReqView &rv, const Smem &sm,
                                            int P, int pc_cap = 0) {
     for (int p = threadIdx.x; p < P; p += BS) {
@@ -810,12 +817,10 @@ __device__ __forceinline__ void load_peers(const Topo &t, const State &st, const
     if (LIMITS && P > 0) {
         for (int x = threadIdx.x; x < t.nsw; x += BS) {
             int se = 0;
-            for (int a0 = 0; a0 < t.h; a0 += 8)
-#pragma unroll
-                for (int d = 0; d < 8; ++d) {
-                    const int v = st.ea[x * t.h + min(a0 + d, t.h - 1)];
-                    se += a0 + d < t.h ? v : 0;
-                }
+            each_link<RES>(t.h, [&](int a, bool in) {
+                const int v = st.ea[x * t.h + a];
+                se += in ? v : 0;
+            });
             sm.capE[x] = se;
         }
         // per pod: one wave sums the pod's h*h aggregation-core residuals
@@ -828,7 +833,7 @@ __device__ __forceinline__ void load_peers(const Topo &t, const State &st, const
         }
     }
     if (T0 && P > 0)
-        table_T<BS>(t, st, sm, 0, min(P, pc_cap), [&](int pc) { return pod_of(t, rv.hosts[rv.pj[pc]]); });
+        table_T<BS, RES>(t, st, sm, 0, min(P, pc_cap), [&](int pc) { return pod_of(t, rv.hosts[rv.pj[pc]]); });
     __syncthreads();
 }
 
@@ -873,7 +878,8 @@ __device__ __forceinline__ void peer_deficits(const Smem &sm, int P) {
 // OWN: workgroup wg of nwg takes the wg-th group of G * BS servers only, and
 // builds the tables of the switches above them.
 // T0: the first chunk's table T was built by load_peers<.., true>.
-template <int BS, bool STATS, int G = host_group(BS), int CS = 0, bool T0 = false, bool OWN = false>
+// RES: as each_link.
+template <int BS, bool STATS, int G = host_group(BS), int CS = 0, bool T0 = false, bool OWN = false, bool RES = false>
 __device__ __forceinline__ void criteria_stage(const Topo &t, const State &st, const Method &m, const Smem &sm, int *xs,
                                int cpu_i, int ram_i, int P, int pc_cap, int wg = 0, int nwg = 1) {
     const int N = t.N, nc = crit_count<CS>(m);
@@ -896,10 +902,10 @@ __device__ __forceinline__ void criteria_stage(const Topo &t, const State &st, c
             if (ch == 0) peer_deficits<BS>(sm, P);
             if (!(T0 && ch == 0)) {
                 if (ch > 0) __syncthreads();            // previous chunk done with the tables
-                table_T<BS>(t, st, sm, pbeg, pn, [&](int pc) { return sm.pk[pbeg + pc].y >> 16; }, sw);
+                table_T<BS, RES>(t, st, sm, pbeg, pn, [&](int pc) { return sm.pk[pbeg + pc].y >> 16; }, sw);
                 __syncthreads();
             }
-            table_E<BS>(t, st, sm, pbeg, pn, sw);
+            table_E<BS, RES>(t, st, sm, pbeg, pn, sw);
             __syncthreads();
         }
         const int dh0 = sm.misc[M_DH0], dh1 = sm.misc[M_DH1];
@@ -1362,8 +1368,8 @@ __device__ __forceinline__ bool select_commit(const Topo &t, const State &st, co
 // raw units (swapped for cost criteria); Rank = Ed- / (Ed+ + Ed-), 0 when
 // both are 0.  Column statistics are exact integer reductions.  Returns
 // false when the request was rejected at this container.
-// XS_LDS: the criteria rows xs are in LDS, so the column statistics are
-// taken from them afterwards by one wave per criterion.
+// XS_LDS: the criteria rows xs (and the state) are in LDS, so the column
+// statistics are taken from them afterwards by one wave per criterion.
 template <int BS, int G = host_group(BS), bool XS_LDS = false, int CS = 0>
 __device__ __forceinline__ bool topsis_step(const Topo &t, const State &st, const Method &m, const Batch &b, const Smem &sm,
                             int *xs, int pc_cap, const Trace &tr, int inst, const StepIn &s, const ReqView &rv) {
@@ -1376,9 +1382,9 @@ __device__ __forceinline__ bool topsis_step(const Topo &t, const State &st, cons
         }
         sm.misc[M_TRACE] = slot;
     }
-    load_peers<BS, true, true>(t, st, rv, sm, s.P, pc_cap);
+    load_peers<BS, true, true, XS_LDS>(t, st, rv, sm, s.P, pc_cap);
     const int nc = crit_count<CS>(m), N = t.N;
-    criteria_stage<BS, !XS_LDS, G, CS, true>(t, st, m, sm, xs, s.cpu, s.ram, s.P, pc_cap);
+    criteria_stage<BS, !XS_LDS, G, CS, true, false, XS_LDS>(t, st, m, sm, xs, s.cpu, s.ram, s.P, pc_cap);
     __syncthreads();
 
     float q[kMaxCrit], ap[kMaxCrit], am[kMaxCrit];
