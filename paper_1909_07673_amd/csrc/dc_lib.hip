@@ -600,7 +600,7 @@ bool specialised_ahp5(const dc_ctx *ctx, int K) {
     static const int crit[5] = {DC_CRIT_CPU, DC_CRIT_RAM, DC_CRIT_UPLINK, DC_CRIT_PATHBW, DC_CRIT_HOPS};
     if (ctx->t.k != K || ctx->m.method != DC_AHP || ctx->m.nc != 5) return false;
     for (int c = 0; c < 5; ++c)
-        if (ctx->m.crit[c] != crit[c] || ctx->m.cost[c] != (c == 4)) return false;
+        if (crit_of(ctx->m, c) != crit[c] || ctx->m.cost[c] != (c == 4)) return false;
     return true;
 }
 
@@ -610,7 +610,7 @@ bool specialised_ahp5(const dc_ctx *ctx, int K) {
 bool default_criteria(const dc_ctx *ctx) {
     if (ctx->m.method != DC_TOPSIS || ctx->m.nc != 4) return false;
     for (int c = 0; c < 4; ++c)
-        if (ctx->m.crit[c] != c || ctx->m.cost[c] != 0) return false;
+        if (crit_of(ctx->m, c) != c || ctx->m.cost[c] != 0) return false;
     return true;
 }
 bool specialised(const dc_ctx *ctx, int K) { return ctx->t.k == K && default_criteria(ctx); }
@@ -992,7 +992,7 @@ AhpQueueFn ahp_queue_fn(const dc_ctx *ctx) {
 // path bandwidth within the server's uplink, hops within six per peer.
 int crit_max(const dc_ctx *ctx, int c) {
     const dc_config &cfg = ctx->cfg;
-    switch (ctx->m.crit[c]) {
+    switch (crit_of(ctx->m, c)) {
     case CRIT_CPU: return cfg.host_cpu;
     case CRIT_RAM: return cfg.host_ram;
     case CRIT_ACTIVE: return 1;
@@ -1654,7 +1654,7 @@ int dc_create(const dc_config *cfg, dc_ctx **out) {
     ctx->m.nc = cfg->ncrit;
     ctx->m.route_end = cfg->routing;
     for (int c = 0; c < DC_MAX_CRIT; ++c) {
-        ctx->m.crit[c] = c < cfg->ncrit ? cfg->crit[c] : 0;
+        ctx->m.codes |= c < cfg->ncrit ? static_cast<unsigned>(cfg->crit[c]) << (4 * c) : 0u;
         ctx->m.cost[c] = c < cfg->ncrit ? (cfg->crit_cost[c] != 0) : 0;
         ctx->m.w[c] = c < cfg->ncrit ? cfg->weight[c] : 0.f;
     }

@@ -69,10 +69,17 @@ struct State {
 struct Method {
     int method, scale, nc;
     int route_end;      // 1: links routed after a request's last unit is placed (section V-D)
-    int crit[kMaxCrit];
+    unsigned codes;     // criterion c in bits 4c..4c+3
     int cost[kMaxCrit];
     float w[kMaxCrit];
 };
+
+// Criterion c of a method.  One register holds the list: as an array it took
+// sixteen scalar registers (with the costs) through every loop of a step, which
+// where a kernel has none to spare are spilled and brought back at each
+// criterion (the single-workgroup serving kernel: 3,100 register moves against
+// 1,230, a request of two to four containers at k = 8 19.3 us against 18.2).
+__host__ __device__ __forceinline__ int crit_of(const Method &m, int c) { return m.codes >> (4 * c) & 15; }
 
 // Criteria of a step: CS = 0 takes them from the method; CS = 4 is the
 // default list (CPU, RAM, active, path bandwidth; all benefits) and CS = 5
@@ -82,7 +89,7 @@ template <int CS> __device__ __forceinline__ int crit_count(const Method &m) { r
 template <int CS> __device__ __forceinline__ int crit_at(const Method &m, int c) {
     if (CS == 4) return c;
     if (CS == 5) return c < 2 ? c : c == 2 ? CRIT_UPLINK : c == 3 ? CRIT_PATHBW : CRIT_HOPS;
-    return m.crit[c];
+    return crit_of(m, c);
 }
 template <int CS> __device__ __forceinline__ int crit_cost(const Method &m, int c) {
     if (CS == 4) return 0;
