@@ -108,8 +108,10 @@ typedef struct dc_config {
     int32_t trace_cap;      /* at most this many recorded steps                     */
     int32_t grid;           /* plain and serving forms: 0 = automatic.  Plain: a
                                queue in one launch, TOPSIS on one workgroup where
-                               the state fits its LDS and on one per pod beyond,
-                               AHP (1-9 scale, up to 8,192 servers) over several;
+                               the state fits its LDS and on one per pod beyond
+                               (criteria other than the default four: from k = 28
+                               on, one launch per step before), AHP (1-9 scale, up
+                               to 8,192 servers) over several;
                                serving from k = 32 on: one workgroup per pod.
                                1 = one workgroup per TOPSIS step (plain AHP: one
                                launch per stage), 2 = TOPSIS on one workgroup per

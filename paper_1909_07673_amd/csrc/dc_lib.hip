@@ -1034,10 +1034,17 @@ int large_init(dc_ctx *ctx) {
 // Which plain contexts run their queue in one launch over several
 // workgroups: one data center, left to the automatic choice (grid = 0 and no
 // block size asked for).  TOPSIS where the state does not fit one workgroup
-// (from k = 22 on): a step over one workgroup per pod.  AHP on the 1-9 scale
+// (from k = 20 to 22 on): a step over one workgroup per pod.  On the default
+// criteria that is always the faster form (40 requests of two containers at
+// k = 22: 1.27 ms step by step, 0.96 so).  With other lists, which no kernel is
+// compiled for, the exchanges between workgroups of a smaller data center cost
+// more than one workgroup's step: the same requests on five criteria took 1.48
+// ms step by step and 1.84 so at k = 24, 1.71 and 1.91 at k = 26, 1.93 and
+// 1.83 at k = 28, so those take it from kQueueAnyK on.  AHP on the 1-9 scale
 // up to 8,192 servers, where the position table of every criterion fits LDS
 // beside the prefix sums.  A device (or a partition of one) that cannot hold
 // all the workgroups at once keeps to one launch per step.
+constexpr int kQueueAnyK = 28;
 template <class F>
 bool all_resident(F kernel, int block, size_t lds, int wgs) {
     int dev = 0, cus = 0, per = 0;
@@ -1053,7 +1060,7 @@ int queue_init(dc_ctx *ctx) {
     if (cfg.mode != DC_MODE_PLAIN || ctx->I != 1 || cfg.grid != 0 || cfg.block != 0) return DC_OK;
     const int k = ctx->t.k, h = ctx->t.h, hh = ctx->t.hh, nc = ctx->m.nc;
     if (ctx->m.method == DC_TOPSIS) {
-        if (ctx->plain_res) return DC_OK;
+        if (ctx->plain_res || (k < kQueueAnyK && !default_criteria(ctx))) return DC_OK;
         ctx->queue_wgs = k;
         ctx->lds_queue = align4(gsmem_bytes(h, hh, nc) / sizeof(int)) * sizeof(int) + kQueueReqInts * sizeof(int);
         if (set_lds(ctx, topsis_queue_fn(ctx), ctx->lds_queue)) return DC_EDEVICE;

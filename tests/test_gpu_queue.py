@@ -252,3 +252,25 @@ def test_topsis_queue_after_65535_rounds_without_outcome():
     np.testing.assert_array_equal(mine["score"].view(np.uint32), want["score"].view(np.uint32))
     np.testing.assert_array_equal(s.state(0), want["state"])
     s.close()
+
+
+@pytest.mark.parametrize("k,crit,cost,one", [
+    (20, C8, (0, 0, 0, 0, 0, 1, 1, 1), False),      # eight criteria: the state does not fit one workgroup
+    (22, None, None, True),
+    (26, C5, (0, 0, 0, 0, 1), False),
+    (28, C5, (0, 0, 0, 0, 1), True),
+])
+def test_topsis_queue_where_it_is_faster(k, crit, cost, one):
+    """Beyond one workgroup's LDS a queue runs in one launch on the default
+    criteria at any size, on others from k = 28 on, and step by step below;
+    the same results as the cooperative steps."""
+    inst, reqs = _queue(k, 2, 12, 8, seed=41)
+    kw = {} if crit is None else dict(crit=crit, cost=cost)
+    s = dc.Scheduler([inst], **kw)
+    for r in reqs:
+        s.submit(r)
+    s.schedule_array()
+    launches, steps = s.last_timing()[1:]
+    assert launches == (1 if one else steps)
+    s.close()
+    _same(_schedule(inst, reqs, **kw), _schedule(inst, reqs, grid=2, **kw))
