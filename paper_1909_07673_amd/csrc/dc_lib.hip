@@ -1438,11 +1438,23 @@ struct TilePath {
     size_t refuse = 0;      // dc_topsis_tiles_noalloc: refused when above its static buffer
 };
 
-// Up to 1 MiB of criteria one workgroup per tile, beyond it (few tiles) the
-// split: a 27,648 x 4 tile alone took 31-35 us over seven workgroups behind
-// an allocation and a select launch, 17.7 us with one workgroup (41 us split).
-// With 4-byte loads half of that: 57 x 6 x 24,334 took 69 us, 49 split.
+// Tiles past the registers: one workgroup each, in one launch without scratch,
+// or the split.  One workgroup's time goes with the servers (a thread has C
+// loads under way for each), the split's hardly.  One matrix not read before,
+// with a mask and every score (us, one workgroup / split):
+//   40,960 servers, C = 1 to 6:  34 / 40, 38 / 46, 43 / 48, 48 / 54, 55 / 60, 62 / 65
+//   57,344, C = 1 to 4:          42 / 38, 47 / 46, 54 / 50, 62 / 55
+//   4-byte loads, 12,289, C = 3 to 6: 41 / 47, 43 / 52, 48 / 57, 50 / 62
+//   4-byte loads, 20,001, C = 3 to 6: 56 / 46, 60 / 52, 66 / 57, 70 / 61
+// (from the caches the lines lie higher).  Tiles enough to fill the device are
+// faster one workgroup each: 64 x 4 x 65,536 in 67 / 82, 256 x 2 x 65,535 with
+// 4-byte loads in 1 / 1.3.  Past 1 MiB of criteria (512 KiB with 4-byte loads)
+// always the split.
 constexpr long long kBigTileInts = 1 << 18;
+bool one_workgroup(int64_t T, int C, int N, bool vec) {
+    if ((long long)C * N > (vec ? kBigTileInts : kBigTileInts / 2)) return false;
+    return vec ? N <= 40960 || T >= 64 : N <= 14336 || T >= 256;
+}
 
 int tiles_prepare(int64_t T, int32_t C, int32_t N, const int32_t *x, const uint8_t *feasible, const int32_t *cost,
                   const float *weight, float *scores, int32_t *best, float *best_score, TileArgs *a, TilePath *path) {
@@ -1489,7 +1501,7 @@ int tiles_prepare(int64_t T, int32_t C, int32_t N, const int32_t *x, const uint8
         path->kind = TILE_REG;
         path->V = v;
         path->NW = nw;
-    } else if ((long long)C * N <= (vec ? kBigTileInts : kBigTileInts / 2) || !splits) {
+    } else if (one_workgroup(T, C, N, vec) || !splits) {
         path->kind = TILE_BIG;
     } else {
         path->kind = TILE_SPLIT;

@@ -210,3 +210,19 @@ def test_tiles_odd_size_edges(T, C, N):
     best, bscore, sc = _run(x, feas, w, cost)
     for t in range(T):
         _check_tile(x[t], feas[t], w, cost, sc[t], best[t], bscore[t])
+
+
+# around the lines between one workgroup per tile and slices over several: by
+# servers, by tiles, and by both loads
+LINES = [(1, 4, 40960), (1, 4, 40964), (63, 1, 40964), (64, 1, 40964), (2, 3, 14335), (2, 3, 14337), (255, 2, 16385),
+         (256, 2, 16385)]
+
+
+@pytest.mark.parametrize("T,C,N", LINES)
+def test_tiles_around_the_split(T, C, N):
+    x, feas = make_tiles(seed=T * 17 + C * 3 + N, T=T, N=N, C=C, feasible_p=0.6)
+    w = np.arange(1, C + 1) / (C * (C + 1) / 2)
+    cost = [c % 3 == 1 for c in range(C)]
+    best, bscore, sc = _run(x, feas, w, cost)
+    for t in sorted({0, T // 2, T - 1}):
+        _check_tile(x[t], feas[t], w, cost, sc[t], best[t], bscore[t])
