@@ -344,8 +344,8 @@ int dc_last_timing(dc_ctx *ctx, float *ms, int64_t *launches, int64_t *steps);
  * N % 4 == 0 (up to 32,768 servers at C <= 2, 16,384 at C <= 4, 8,192
  * beyond), otherwise with 4-byte loads (half of that at C = 2 to 4).  Larger
  * tiles take one workgroup each, up to 40,960 servers (14,336 with 4-byte
- * loads), or any number where there are 64 tiles (256) and up to 1 MiB of
- * criteria a tile (512 KiB); otherwise up to 1,024 tiles take several, with
+ * loads), or any number where there are 64 tiles and 16-byte loads, and up to
+ * 1 MiB of criteria a tile (512 KiB); otherwise up to 1,024 tiles take several, with
  * partials in device memory allocated on the stream for the call
  * (stream-ordered) and freed behind it. */
 int dc_topsis_tiles(int64_t T, int32_t C, int32_t N, const int32_t *x, const uint8_t *feasible,

@@ -1446,14 +1446,13 @@ struct TilePath {
 //   57,344, C = 1 to 4:          42 / 38, 47 / 46, 54 / 50, 62 / 55
 //   4-byte loads, 12,289, C = 3 to 6: 41 / 47, 43 / 52, 48 / 57, 50 / 62
 //   4-byte loads, 20,001, C = 3 to 6: 56 / 46, 60 / 52, 66 / 57, 70 / 61
-// (from the caches the lines lie higher).  Tiles enough to fill the device are
-// faster one workgroup each: 64 x 4 x 65,536 in 67 / 82, 256 x 2 x 65,535 with
-// 4-byte loads in 1 / 1.3.  Past 1 MiB of criteria (512 KiB with 4-byte loads)
-// always the split.
+// (from the caches the lines lie higher).  With 16-byte loads, tiles enough to
+// fill the device are faster one workgroup each: 64 x 4 x 65,536 in 67 / 82.
+// Past 1 MiB of criteria (512 KiB with 4-byte loads) always the split.
 constexpr long long kBigTileInts = 1 << 18;
 bool one_workgroup(int64_t T, int C, int N, bool vec) {
     if ((long long)C * N > (vec ? kBigTileInts : kBigTileInts / 2)) return false;
-    return vec ? N <= 40960 || T >= 64 : N <= 14336 || T >= 256;
+    return vec ? N <= 40960 || T >= 64 : N <= 14336;
 }
 
 int tiles_prepare(int64_t T, int32_t C, int32_t N, const int32_t *x, const uint8_t *feasible, const int32_t *cost,
@@ -1488,6 +1487,10 @@ int tiles_prepare(int64_t T, int32_t C, int32_t N, const int32_t *x, const uint8
     const int vfirst = C <= 2 ? 4 : C <= 4 ? 2 : 1;
     int nw = 0, v = 0;
     for (int w : {1, 4, 16}) {
+        // 4-byte loads and few tiles, whose masks come a byte at a time: four
+        // wavefronts from 257 servers on (64 tiles of 1 x 2,046 with masks 22 us
+        // in one wavefront each, 11.4 in four; 4,096 of 1 x 510 0.6 times as fast)
+        if (w == 1 && !vec && C <= 2 && N > 256 && T <= 512) continue;
         v = w == 1 ? 1 : vfirst;
         while (v < vcap && 256 * v * w < N) v *= 2;
         if (256 * v * w >= N) { nw = w; break; }
@@ -1582,7 +1585,10 @@ int tiles_launch(const TileArgs &a, int64_t T, const TilePath &path, void *work,
         if (rc) return rc;
     } else if (path.kind == TILE_BIG) {
         const dim3 grid(static_cast<unsigned>(T)), block(kBigTileBlock);
+        // (thousands of tiles of one criterion with 4-byte loads and masks, 1 x
+        // 42,725: 1,024 threads took 1.15 times as long as 256)
         if (path.W == 4) hipLaunchKernelGGL(k_topsis_tiles_big<4>, grid, block, 0, st, a);
+        else if (a.C == 1) hipLaunchKernelGGL((k_topsis_tiles_big<1, 256>), grid, dim3(256), 0, st, a);
         else hipLaunchKernelGGL(k_topsis_tiles_big<1>, grid, block, 0, st, a);
     } else {
         const TileSplit sp = split_carve(work, T, a.N, a.C);

@@ -268,16 +268,17 @@ __global__ __launch_bounds__(NW == 1 ? kTileBlock : NW *kWave) void k_topsis_til
     }
 }
 
-// Tiles too large for the registers: one workgroup of 1,024 threads per tile,
+// Tiles too large for the registers: one workgroup of 1,024 threads (256 where a
+// server is one 4-byte load, dc_lib.hip) per tile,
 // which reads the tile for its statistics and again, from the caches, for
 // the scores.  A single tile takes one compute unit's cache bandwidth (at
 // most 1 MiB, dc_lib.hip), yet one launch without scratch ends sooner than
 // several workgroups would behind an allocation and a second launch.
 constexpr int kBigTileBlock = 1024;
 
-template <int W>
-__global__ __launch_bounds__(kBigTileBlock) void k_topsis_tiles_big(TileArgs a) {
-    constexpr int BS = kBigTileBlock, NW = BS / kWave;
+template <int W, int BS = kBigTileBlock>
+__global__ __launch_bounds__(BS) void k_topsis_tiles_big(TileArgs a) {
+    constexpr int NW = BS / kWave;
     const int t = blockIdx.x, N = a.N, C = a.C;
     const int *x = a.x + static_cast<size_t>(t) * C * N;
     unsigned long long s2[kMaxCrit];

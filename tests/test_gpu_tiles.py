@@ -214,8 +214,8 @@ def test_tiles_odd_size_edges(T, C, N):
 
 # around the lines between one workgroup per tile and slices over several: by
 # servers, by tiles, and by both loads
-LINES = [(1, 4, 40960), (1, 4, 40964), (63, 1, 40964), (64, 1, 40964), (2, 3, 14335), (2, 3, 14337), (255, 2, 16385),
-         (256, 2, 16385)]
+LINES = [(1, 4, 40960), (1, 4, 40964), (63, 1, 40964), (64, 1, 40964), (2, 3, 14335), (2, 3, 14337), (257, 2, 16385),
+         (1025, 1, 32769)]
 
 
 @pytest.mark.parametrize("T,C,N", LINES)
