@@ -1455,6 +1455,45 @@ bool one_workgroup(int64_t T, int C, int N, bool vec) {
     return vec ? N <= 40960 || T >= 64 : N <= 14336;
 }
 
+// Fewest wavefronts (NW; 0: none) whose registers hold a tile: 4V servers per
+// thread and criterion, V a power of two with C * V <= 16 (V <= 8).
+struct TileRegs {
+    int V, NW;
+};
+constexpr int tile_vmax(int C) { return C <= 2 ? 8 : C <= 4 ? 4 : 2; }
+constexpr bool tile_built(int C, int V, int NW) {
+    return V <= tile_vmax(C) && (NW == 1 || ((NW == 4 || NW == 16) && 4 * V > tile_vmax(C)));
+}
+constexpr TileRegs tile_regs(bool vec, int64_t T, int C, int N) {
+    // with 4-byte loads half of that from two criteria on: 48 loads and more
+    // a thread took longer than reading the tile twice (1,024 x 4 x 2,662: 48
+    // against 32 us); several wavefronts are built from vmax / 4 < V on
+    const int vcap = !vec && C > 1 && C <= 4 ? tile_vmax(C) / 2 : tile_vmax(C);
+    const int vfirst = C <= 2 ? 4 : C <= 4 ? 2 : 1;
+    for (int w = 1; w <= 16; w *= 4) {
+        // 4-byte loads and few tiles, whose masks come a byte at a time: four
+        // wavefronts from 257 servers on (64 tiles of 1 x 2,046 with masks 22 us
+        // in one wavefront each, 11.4 in four; 4,096 of 1 x 510 0.6 times as fast)
+        if (w == 1 && !vec && C <= 2 && N > 256 && T <= 512) continue;
+        int v = w == 1 ? 1 : vfirst;
+        while (v < vcap && 256 * v * w < N) v *= 2;
+        if (256 * v * w >= N) return {v, w};
+    }
+    return {0, 0};
+}
+
+// Every choice is built: at each size where it changes, at both its sides.
+constexpr bool tile_choices_built() {
+    for (int C = 1; C <= DC_MAX_CRIT; ++C)
+        for (int x = 0; x < 16; ++x)
+            for (int n = 256 << (x / 2), k = 0; k < 4; ++k) {
+                const TileRegs r = tile_regs(k & 1, k & 2 ? 512 : 513, C, n + (x & 1));
+                if (r.NW && !tile_built(C, r.V, r.NW)) return false;
+            }
+    return true;
+}
+static_assert(tile_choices_built(), "a choice of tile_regs has no kernel");
+
 int tiles_prepare(int64_t T, int32_t C, int32_t N, const int32_t *x, const uint8_t *feasible, const int32_t *cost,
                   const float *weight, float *scores, int32_t *best, float *best_score, TileArgs *a, TilePath *path) {
     if (T < 0 || T > 0x7fffffffLL || C < 1 || C > DC_MAX_CRIT || N < 1 || N > (1 << 20)) return DC_EINVAL;
@@ -1477,33 +1516,16 @@ int tiles_prepare(int64_t T, int32_t C, int32_t N, const int32_t *x, const uint8
     const bool vec = N % 4 == 0 && al(x, 16) && (!scores || al(scores, 16)) && (!feasible || al(feasible, 4));
     path->C = C;
     path->W = vec ? 4 : 1;
-    // fewest wavefronts whose registers hold the tile: 4V servers per thread
-    // and criterion, V a power of two with C * V <= 16 (V <= 8)
-    const int vmax = C <= 2 ? 8 : C <= 4 ? 4 : 2;
-    // with 4-byte loads half of that from two criteria on: 48 loads and more
-    // a thread took longer than reading the tile twice (1,024 x 4 x 2,662: 48
-    // against 32 us); several wavefronts are built from vmax / 4 < V on
-    const int vcap = !vec && C > 1 && C <= 4 ? vmax / 2 : vmax;
-    const int vfirst = C <= 2 ? 4 : C <= 4 ? 2 : 1;
-    int nw = 0, v = 0;
-    for (int w : {1, 4, 16}) {
-        // 4-byte loads and few tiles, whose masks come a byte at a time: four
-        // wavefronts from 257 servers on (64 tiles of 1 x 2,046 with masks 22 us
-        // in one wavefront each, 11.4 in four; 4,096 of 1 x 510 0.6 times as fast)
-        if (w == 1 && !vec && C <= 2 && N > 256 && T <= 512) continue;
-        v = w == 1 ? 1 : vfirst;
-        while (v < vcap && 256 * v * w < N) v *= 2;
-        if (256 * v * w >= N) { nw = w; break; }
-    }
+    const TileRegs regs = tile_regs(vec, T, C, N);
     // the scratch of the two-launch split, which the calls of its range are
     // measured by against the static buffer whichever kernels they take
-    const bool in_regs1 = vec && nw == 1;
+    const bool in_regs1 = vec && regs.NW == 1;
     const bool splits = !in_regs1 && N >= 2 * kSplitSlice && T <= kSplitMaxTiles;
     path->refuse = splits ? split_scratch_bytes(T, N, C) : 0;
-    if (nw) {
+    if (regs.NW) {
         path->kind = TILE_REG;
-        path->V = v;
-        path->NW = nw;
+        path->V = regs.V;
+        path->NW = regs.NW;
     } else if (one_workgroup(T, C, N, vec) || !splits) {
         path->kind = TILE_BIG;
     } else {
@@ -1537,16 +1559,12 @@ int launch_tiles_reg(const TileArgs &a, int64_t T, int NW, hipStream_t st) {
     // four wavefronts take what one cannot hold, sixteen what four cannot;
     // a workgroup per tile, within the launch's limit on threads
     const dim3 grid((unsigned)std::min<int64_t>(T, 1 << 20));
-    constexpr int vmax = C <= 2 ? 8 : C <= 4 ? 4 : 2;
-    if constexpr (4 * V > vmax)
-        if (NW == 4)
-            hipLaunchKernelGGL((k_topsis_tiles_reg<C, V, W, 4>), grid, dim3(4 * kWave), 0, st, a,
-                               (long long)T);
-    if constexpr (4 * V > vmax)
-        if (NW == 16)
-            hipLaunchKernelGGL((k_topsis_tiles_reg<C, V, W, 16>), grid, dim3(16 * kWave), 0, st, a,
-                               (long long)T);
-    return DC_OK;
+    if constexpr (tile_built(C, V, 4)) {
+        if (NW == 4) hipLaunchKernelGGL((k_topsis_tiles_reg<C, V, W, 4>), grid, dim3(4 * kWave), 0, st, a, (long long)T);
+        else hipLaunchKernelGGL((k_topsis_tiles_reg<C, V, W, 16>), grid, dim3(16 * kWave), 0, st, a, (long long)T);
+        return DC_OK;
+    }
+    return DC_EDEVICE;      // not built, and not chosen (tile_choices_built)
 }
 
 template <int C, int W>
@@ -1561,7 +1579,7 @@ int launch_tiles_reg_v(const TileArgs &a, int64_t T, const TilePath &p, hipStrea
         if constexpr (C <= 2) return launch_tiles_reg<C, 8, W>(a, T, p.NW, st);
         break;
     }
-    return DC_EINVAL;       // unreachable: V <= vmax of its C
+    return DC_EDEVICE;      // not built, and not chosen (tile_choices_built)
 }
 
 template <int W>
