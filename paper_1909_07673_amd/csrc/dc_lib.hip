@@ -344,8 +344,6 @@ struct dc_ctx {
     AhpLarge large{};
     void *d_large = nullptr;
     size_t lds_count = 0;
-    unsigned long long *d_words = nullptr; // its value, column and rank words
-    int *h_ctl = nullptr;          // pinned: err, round, join[2] after a launch
     hipError_t launch_err = hipSuccess;    // first failed cooperative launch of a run
     hipStream_t cap_stream = nullptr;      // graph capture (batched form)
 };
@@ -932,13 +930,14 @@ int collect(dc_ctx *ctx, DevBatch &b, dc_result **dst, int64_t *room) {
 }
 
 // ---------------------------------------------------------------- cooperative step
-int grid_alloc(dc_ctx *ctx, int G) {
+int grid_alloc(dc_ctx *ctx, int G, size_t more = 0, unsigned long long **extra = nullptr) {
     // count, gen, err, round, join[2], done, reported, then 8-byte aligned:
-    // kslot[2][G], rflag, rec[kRecWords][k], times, cmd
-    const size_t words = 2 * (size_t)G + 1 + (size_t)ctx->t.k * kRecWords + 2 * kCmdRing + kCmdRing * kCmdWords;
+    // kslot[2][G], rflag, rec[kRecWords][k], times, cmd, and `more` words
+    const size_t own = 2 * (size_t)G + 1 + (size_t)ctx->t.k * kRecWords + 2 * kCmdRing + kCmdRing * kCmdWords;
+    const size_t words = own + more;
     const size_t ints = 8 + 2 * words;
     HIPCHK(hipMalloc(&ctx->d_grid, ints * sizeof(int)));
-    hipLaunchKernelGGL(k_fill_i32, dim3(16), dim3(256), 0, ctx->stream, ctx->d_grid, 0, (long long)ints);
+    hipLaunchKernelGGL(k_fill_i32, dim3(more ? 64 : 16), dim3(256), 0, ctx->stream, ctx->d_grid, 0, (long long)ints);
     HIPCHK(hipGetLastError());
     int *p = ctx->d_grid;
     GridCtl &g = ctx->grid;
@@ -956,6 +955,7 @@ int grid_alloc(dc_ctx *ctx, int G) {
     g.cmd = reinterpret_cast<unsigned long long *>(g.times + 2 * kCmdRing);
     g.wgs = G;
     g.pods = ctx->t.k;
+    if (extra) *extra = g.kslot + own;
     return DC_OK;
 }
 
@@ -1059,6 +1059,7 @@ int queue_init(dc_ctx *ctx) {
     const dc_config &cfg = ctx->cfg;
     if (cfg.mode != DC_MODE_PLAIN || ctx->I != 1 || cfg.grid != 0 || cfg.block != 0) return DC_OK;
     const int k = ctx->t.k, h = ctx->t.h, hh = ctx->t.hh, nc = ctx->m.nc;
+    size_t words = 0;
     if (ctx->m.method == DC_TOPSIS) {
         if (ctx->plain_res || (k < kQueueAnyK && !default_criteria(ctx))) return DC_OK;
         ctx->queue_wgs = k;
@@ -1083,18 +1084,17 @@ int queue_init(dc_ctx *ctx) {
         if (ctx->queue_wgs > kWave) return DC_OK;
         if (set_lds(ctx, ahp_queue_fn(ctx), ctx->lds_queue)) return DC_EDEVICE;
         if (!all_resident(ahp_queue_fn(ctx), bs, ctx->lds_queue, ctx->queue_wgs)) return DC_OK;
-        const size_t words = 3 * (size_t)nc * ctx->N;
-        HIPCHK(hipMalloc(&ctx->d_words, words * sizeof(unsigned long long)));
-        hipLaunchKernelGGL(k_fill_i32, dim3(64), dim3(256), 0, ctx->stream, reinterpret_cast<int *>(ctx->d_words), 0,
-                           2 * (long long)words);
-        ctx->ahp.xw = ctx->d_words;
-        ctx->ahp.zw = ctx->d_words + (size_t)nc * ctx->N;
-        ctx->ahp.lw = ctx->d_words + 2 * (size_t)nc * ctx->N;
+        words = (size_t)nc * ctx->N;
         ctx->queue = dc_ctx::QUEUE_AHP;
     }
-    HIPCHK(hipHostMalloc(reinterpret_cast<void **>(&ctx->h_ctl), 4 * sizeof(int), 0));
     if (cfg.grid_timeout_us > 0) ctx->patience = 100LL * cfg.grid_timeout_us;
-    return grid_alloc(ctx, ctx->queue_wgs);
+    // the value, column and rank words of an AHP step behind the records
+    unsigned long long *w = nullptr;
+    const int rc = grid_alloc(ctx, ctx->queue_wgs, 3 * words, &w);
+    ctx->ahp.xw = w;
+    ctx->ahp.zw = w + words;
+    ctx->ahp.lw = w + 2 * words;
+    return rc;
 }
 
 // Runs a batch in one launch; *ran is false when its workgroups did not
@@ -1111,14 +1111,19 @@ int run_queue(dc_ctx *ctx, DevBatch &b, bool *ran) {
         hipLaunchKernelGGL(ahp_queue_fn(ctx), dim3(ctx->queue_wgs), dim3(ahp_queue_block(ctx->N)), ctx->lds_queue,
                            ctx->stream, p, ctx->grid, ctx->ahp, epoch, ctx->patience, kWait);
     HIPCHK(hipGetLastError());
-    HIPCHK(hipMemcpyAsync(ctx->h_ctl, ctx->grid.err, 4 * sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
+    // err, round, join[2] into the pinned buffer (any upload from it lies before
+    // this copy on the stream)
+    const int prc = pinned_at_least(ctx, 4);
+    if (prc) return prc;
+    const int *ctl = ctx->pinned;
+    HIPCHK(hipMemcpyAsync(ctx->pinned, ctx->grid.err, 4 * sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
     HIPCHK(hipStreamSynchronize(ctx->stream));
-    if (ctx->h_ctl[0]) {
+    if (ctl[0]) {
         ctx->poisoned = true;
         std::fprintf(stderr, "libdcsched: a wait inside a queue kernel timed out\n");
         return DC_EDEVICE;
     }
-    *ran = static_cast<unsigned>(ctx->h_ctl[3]) == 2 * epoch;
+    *ran = static_cast<unsigned>(ctl[3]) == 2 * epoch;
     ctx->last_launches += 1;
     if (*ran) ctx->last_steps += b.Ct;
     return DC_OK;
@@ -2312,9 +2317,7 @@ void dc_destroy(dc_ctx *ctx) {
             if (p) (void)hipFree(p);
         if (ctx->d_rowpart) (void)hipFree(ctx->d_rowpart);
         if (ctx->d_wsort) (void)hipFree(ctx->d_wsort);
-        if (ctx->d_words) (void)hipFree(ctx->d_words);
         if (ctx->d_large) (void)hipFree(ctx->d_large);
-        if (ctx->h_ctl) (void)hipHostFree(ctx->h_ctl);
         if (ctx->d_tscore) (void)hipFree(ctx->d_tscore);
     } else {
         std::fprintf(stderr, "libdcsched: the device did not finish this context's work; its memory is left allocated\n");
