@@ -33,7 +33,7 @@ struct GridCtl {
     // serving form: commands as the fetching workgroup hands them out, and
     // their way back (below)
     unsigned long long *cmd;      // [kCmdRing][kCmdWords], tagged with position + 1
-    long long *times;             // [kCmdRing][2] device clock at admission and decision
+    long long *times;             // [kCmdRing][2] device clock when the command was seen, and at its decision
     int *done, *reported;         // commands completed / reported to the host
 };
 
@@ -752,6 +752,7 @@ __device__ void serve_fetch(const ServeArgs &a, const GridCtl &g, int *lds) {
                 if (dev_clock() - idle0 > a.idle_ticks) break;
                 __builtin_amdgcn_s_sleep(8);
             }
+            g.times[2 * (pos & (kCmdRing - 1))] = dev_clock();
             lds[CW_TYPE] = got ? __hip_atomic_load(&c->type, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) : CMD_STOP;
             if (got) {
                 lds[CW_N] = __hip_atomic_load(&c->n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -870,6 +871,7 @@ __global__ __launch_bounds__(BS) void k_serve_grid(Params p, ServeArgs a, GridCt
     const bool lead = blockIdx.x == 0;
     unsigned rnd = __hip_atomic_load(g.round, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // selection rounds
     bool stale = true;
+    long long free_at = dev_clock();                       // thread 0 of workgroup 0: the last command's end
     for (int pos = a.start;; ++pos) {
         // the command, by one thread per word
         if (threadIdx.x < kCmdWords) {
@@ -900,7 +902,6 @@ __global__ __launch_bounds__(BS) void k_serve_grid(Params p, ServeArgs a, GridCt
         int *sb = a.arena + off;
         const SlotLayout L = slot_layout(n, P);
         const Batch b = slot_batch(sb, L);
-        const long long t_admit = dev_clock();
         if (type == CMD_SUBMIT) {
             for (int x = threadIdx.x; x <= n; x += BS) {
                 rq_poff[x] = sb[L.poff + x];
@@ -945,8 +946,11 @@ __global__ __launch_bounds__(BS) void k_serve_grid(Params p, ServeArgs a, GridCt
         }
         __syncthreads();
         if (lead && threadIdx.x == 0) {
-            g.times[2 * (pos & (kCmdRing - 1))] = t_admit;
-            g.times[2 * (pos & (kCmdRing - 1)) + 1] = dev_clock();
+            // admitted once it had been seen and the command before it was done:
+            // bringing it in from host memory counts unless it passed meanwhile
+            long long *at = g.times + 2 * (pos & (kCmdRing - 1));
+            at[0] = max(at[0], free_at);
+            at[1] = free_at = dev_clock();
             __hip_atomic_store(g.done, pos + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
         }
     }

@@ -38,3 +38,28 @@ def test_serving_departures_seen_by_the_next_request(k, grid):
     s.drain()
     np.testing.assert_array_equal(s.state(0), start)
     s.close()
+
+
+def test_service_latency_covers_bringing_the_request_in():
+    """The service latency of a request that finds the kernel idle covers its
+    way from host memory (at least three reads of a microsecond, one after
+    another: sequence number, fields, request); of one that waits behind
+    another, that way has passed meanwhile."""
+    inst = make_instance(32, 32, 256, 40000, 40000, 40000)
+    none = Request(cpu=np.full(1, 33, np.int32), ram=np.full(1, 1, np.int32), edges=np.zeros((0, 3), np.int32))
+    n = 32
+    edges = np.array([(i, j, 100) for j in range(1, n) for i in range(j)], np.int32)
+    long = Request(cpu=np.full(n, 1, np.int32), ram=np.full(n, 1, np.int32), edges=edges)
+    s = dc.Scheduler([inst], mode=dc.DC_MODE_SERVING)
+    for _ in range(20):
+        s.submit(none)
+        s.drain()
+    lone = s.latency_us()
+    for _ in range(10):
+        s.submit(long)
+        s.submit(none)
+        s.submit(none)
+        s.drain()
+    queued = s.latency_us()[20:].reshape(10, 3)[:, 1:]
+    s.close()
+    assert np.median(lone) >= np.median(queued) + 3.0, (np.median(lone), np.median(queued))
