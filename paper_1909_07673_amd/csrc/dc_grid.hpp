@@ -771,7 +771,18 @@ __device__ void serve_fetch(const ServeArgs &a, const GridCtl &g, int *lds) {
             const SlotLayout L = slot_layout(n, P);
             int *sb = a.arena + lds[CW_SLOT];
             const int *stg = a.staging + (size_t)(pos % a.cap) * a.stage_ints;
-            for (int x = tid; x < L.in_end; x += BS) sb[x] = stg[x];
+            // (a read from host memory takes a microsecond or two: eight a thread
+            // under way, where one after another a request of 64 containers and
+            // all their pairs took 15 us)
+            constexpr int U = 8;
+            for (int base = tid; base < L.in_end; base += U * BS) {
+                int v[U];
+#pragma unroll
+                for (int j = 0; j < U; ++j) v[j] = base + j * BS < L.in_end ? stg[base + j * BS] : 0;
+#pragma unroll
+                for (int j = 0; j < U; ++j)
+                    if (base + j * BS < L.in_end) sb[base + j * BS] = v[j];
+            }
             for (int x = tid; x < n; x += BS) {
                 sb[L.host + x] = -1;
                 sb[L.score + x] = 0;
@@ -782,7 +793,7 @@ __device__ void serve_fetch(const ServeArgs &a, const GridCtl &g, int *lds) {
                 sb[L.status] = 1;
             }
         }
-        __threadfence();
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         __syncthreads();
         if (tid < kCmdWords)
             __hip_atomic_store(cmd_word(g, pos, tid), cmd_tag(pos) | static_cast<unsigned>(lds[tid]), __ATOMIC_RELEASE,
