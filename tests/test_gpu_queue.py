@@ -4,6 +4,8 @@ the sizes where the resident kernel's layout changes."""
 import numpy as np
 import pytest
 
+import oracle as O
+from parity import lockstep
 from workloads import make_instance, make_requests
 
 pytestmark = pytest.mark.gpu
@@ -274,3 +276,47 @@ def test_topsis_queue_where_it_is_faster(k, crit, cost, one):
     assert launches == (1 if one else steps)
     s.close()
     _same(_schedule(inst, reqs, **kw), _schedule(inst, reqs, grid=2, **kw))
+
+
+@pytest.mark.parametrize("k,method", [(48, dc.DC_TOPSIS), (32, dc.DC_AHP)])
+def test_refused_start_runs_launch_by_launch(k, method):
+    """1 us is less than this many workgroups need to meet (measured: twenty of
+    twenty starts refused): the launch count shows the steps that ran after the
+    refused start, and the results are those of the queue kernel."""
+    inst, reqs = _queue(k, 2, 6, 4, seed=17)
+    want = _schedule(inst, reqs, method=method)
+    s = dc.Scheduler([inst], method=method, grid_timeout_us=1)
+    for r in reqs:
+        s.submit(r)
+    refused = 0
+    for _ in range(5):
+        s.rewind()
+        res = s.schedule_array()
+        launches, steps = s.last_timing()[1:]
+        assert launches == 1 or launches >= 1 + steps
+        refused += launches > 1
+        for f in ("status", "n", "failed_at", "host"):
+            np.testing.assert_array_equal(res[f], want[f])
+        np.testing.assert_array_equal(res["score"].view(np.uint32), want["score"].view(np.uint32))
+        np.testing.assert_array_equal(s.state(0), want["state"])
+    s.close()
+    assert refused >= 1
+
+
+@pytest.mark.parametrize("k,up,launches", [(16, 100000, 6), (34, 90000, 5)])
+def test_ahp_past_the_counting_kernels_against_the_oracle(k, up, launches):
+    """Capacities whose position table does not fit LDS (up to 8,192 servers the
+    sorted passes, beyond the pairwise ones): several launches per step, in
+    lockstep with the oracle."""
+    rng = np.random.default_rng([k, up])
+    inst = make_instance(k, 32, 256, up, 100000, 100000, background=0.7, rng=rng)
+    reqs = make_requests(1, rng, 3, 3, bw_lo=1, bw_hi=up // 20)
+    s = dc.Scheduler([inst], method=dc.DC_AHP, crit=C5, cost=(0, 0, 0, 0, 1), trace_stride=1, trace_cap=8)
+    ids = [s.submit(r) for r in reqs]
+    res = {r.req_id: r for r in s.schedule()}
+    n, steps = s.last_timing()[1:]
+    assert n >= launches * steps
+    o = O.Oracle(inst, O.method(kind=O.AHP, crit=(O.CRIT_CPU, O.CRIT_RAM, O.CRIT_UPLINK, O.CRIT_PATHBW, O.CRIT_HOPS),
+                                cost=(0, 0, 0, 0, 1)))
+    lockstep(o, s, ids, reqs, res, check_paths=True)
+    s.close()
