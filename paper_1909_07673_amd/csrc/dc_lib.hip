@@ -2163,15 +2163,19 @@ int dc_autotune_cached(dc_ctx *ctx, const char *cache_path, dc_tune *out) {
     // counters and the current shape as they were
     struct Restore {
         dc_ctx *c;
-        int stride, plain_bs;
+        int stride, plain_bs, queue;
         int *saved = nullptr;
         ~Restore() {
             c->cfg.trace_stride = stride;
             c->plain_bs = plain_bs;
+            c->queue = queue;
             if (saved) (void)hipFree(saved);
         }
-    } guard{ctx, ctx->cfg.trace_stride, ctx->plain_bs};
+    } guard{ctx, ctx->cfg.trace_stride, ctx->plain_bs, ctx->queue};
     ctx->cfg.trace_stride = 0;
+    // a queue kernel has its own block size: what is tuned, and later used
+    // where its workgroups cannot meet, is the launch-by-launch form
+    ctx->queue = dc_ctx::QUEUE_NONE;
     const size_t sbytes = (size_t)ctx->I * 6 * ctx->N * sizeof(int);
     HIPCHK(hipMalloc(&guard.saved, sbytes));
     HIPCHK(hipMemcpyAsync(guard.saved, ctx->d_state, sbytes, hipMemcpyDeviceToDevice, ctx->stream));

@@ -320,3 +320,19 @@ def test_ahp_past_the_counting_kernels_against_the_oracle(k, up, launches):
                                 cost=(0, 0, 0, 0, 1)))
     lockstep(o, s, ids, reqs, res, check_paths=True)
     s.close()
+
+
+@pytest.mark.parametrize("k,method", [(24, dc.DC_TOPSIS), (16, dc.DC_AHP)])
+def test_autotune_times_the_launches_a_block_size_governs(k, method):
+    """A context whose queue runs in one launch over several workgroups takes no
+    block size there: what is timed is the launch-by-launch form."""
+    inst, reqs = _queue(k, 2, 6, 4, seed=19)
+    s = dc.Scheduler([inst], method=method)
+    for r in reqs:
+        s.submit(r)
+    t = s.autotune_cached()
+    _, launches, steps = s.last_timing()
+    assert t["candidates"] == 3 and launches >= steps >= 6 * sum(len(r.cpu) for r in reqs)
+    s.schedule_array()
+    assert s.last_timing()[1] == 1                        # the queue itself as before
+    s.close()
