@@ -51,8 +51,8 @@ WORKLOADS = {
                          "per instance, TOPSIS, batched form (one persistent launch)"),
     "ahp": dict(preset="ahp", mode="plain", method="ahp",
                 text="k=32 fat-tree (8192 hosts), 500 FCFS requests of 8-64 containers, 0-70% background, AHP "
-                     "(Saaty 1-9) on CPU/RAM/uplink/path-bw/hops(cost), the queue in one launch "
-                     "(criteria, run sort, run merge, column sums, row sums, global priority, select)"),
+                     "(Saaty 1-9) on CPU/RAM/uplink/path-bw/hops(cost), the queue in one launch over several workgroups "
+                     "(criteria, value counts, column sums, row sums, global priority, select)"),
     "pods": dict(preset="pods", mode="plain", method="topsis",
                  text="k=16 fat-tree (1024 hosts), 2000 FCFS requests of 2-32 containers with up to half of each "
                       "request's containers in pods of 2-4 (one placement per pod), 0-70% background, TOPSIS, "
@@ -259,7 +259,14 @@ def run_batch(args, wl, insts, reqs):
     if tune is not None:
         out["config"]["autotune"] = tune
     if wl["method"] == "topsis":
-        kname = "k_topsis_grid" if mode == dc.DC_MODE_PLAIN and args.grid == 2 else "k_topsis_resident"
+        # the resident kernel up to k = 20; beyond, a queue in one launch over
+        # one workgroup per pod, or one launch per step
+        if mode == dc.DC_MODE_PLAIN and args.grid == 2:
+            kname = "k_topsis_grid"
+        elif mode == dc.DC_MODE_BATCHED or insts[0].k <= 20:
+            kname = "k_topsis_resident"
+        else:
+            kname = "k_topsis_queue" if per_step_launches == 1 else "k_topsis_plain"
         bytes_per_launch = BYTES_PER_HOST_SCORE * hs / per_step_launches
         achieved = bytes_per_launch / avg_launch_s / 1e9
         traffic = counter_traffic(BATCHED_TRAFFIC, shape) if mode == dc.DC_MODE_BATCHED else None
@@ -273,16 +280,20 @@ def run_batch(args, wl, insts, reqs):
         # the column and row sums take 2*C*N^2 Saaty evaluations per
         # container step by definition; the pairwise passes make them all,
         # at AHP_PAIR_OPS VALU lane-instructions each, so their ceiling is
-        # the VALU lane rate / AHP_PAIR_OPS.  The sorted passes (the 1-9
-        # scale up to AHP_SORT_MAX servers) reach the same sums in
-        # O(C N log N) work: their rate is the equivalent evaluations per
-        # second, which can exceed that ceiling (frac > 1).  Either rate is
-        # taken over the whole step's kernel time.
+        # the VALU lane rate / AHP_PAIR_OPS.  On the 1-9 scale the sums come
+        # from counts (k_ahp_queue), from sorted values (the same launch by
+        # launch) or, beyond AHP_SORT_MAX servers, from one row per distinct
+        # value: their rate is the equivalent evaluations per second, which
+        # can exceed that ceiling (frac > 1), over the whole step's kernel
+        # time.
         pairs, ops = 2.0 * C * N * N * steps, AHP_PAIR_OPS
-        if N <= AHP_SORT_MAX:
-            kname, unit = "AHP step, sorted passes", "pair-evals/s (equivalent)"
+        unit = "pair-evals/s (equivalent)"
+        if per_step_launches == 1:
+            kname = "k_ahp_queue"
+        elif N <= AHP_SORT_MAX:
+            kname = "AHP step, sorted passes"
         else:
-            kname, unit = "k_ahp_colsum+k_ahp_rowsum", "pair-evals/s"
+            kname = "AHP step, k_ahp_count and k_ahp_rows"
         rate = pairs * args.steps / (kern_ms / 1e3)
         out["roofline"] = {"bound": "alu", "kernel": kname, "unit": unit, "achieved": rate,
                            "peak": VALU_LANE_OPS / ops, "frac": rate / (VALU_LANE_OPS / ops),
@@ -304,8 +315,8 @@ def oracle_method(wl):
 
 # VALU instructions per Saaty pair evaluation in the pairwise AHP passes,
 # counted in the compiled inner loops (18.75 in k_ahp_colsum, 18.1 in
-# k_ahp_rowsum); the 1-9 scale takes the sorted passes up to AHP_SORT_MAX
-# servers.
+# k_ahp_rowsum); the 1-9 scale takes the counting or the sorted passes up to
+# AHP_SORT_MAX servers.
 AHP_PAIR_OPS = 18.4
 AHP_SORT_MAX = 8192
 
@@ -595,7 +606,7 @@ def run_serving(args, wl, variants_all=True):
         "scaling": "weak", "vs_baseline": None, "dtype": "f32", "data": "synthetic",
         "config": {"workload": wl["text"], "k": 48, "hosts": N, "trace_s": args.trace_s,
                    "requests": len(reqs), "form": "serving", "method": "topsis"},
-        "latency_us": dict(sv["service_us"], kind="service (admission to decision), device clock"),
+        "latency_us": dict(sv["service_us"], kind="service (command seen by the kernel to decision), device clock"),
         "forms": forms,
     }
 

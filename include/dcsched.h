@@ -111,7 +111,9 @@ typedef struct dc_config {
                                the state fits its LDS and on one per pod beyond
                                (criteria other than the default four: from k = 28
                                on, one launch per step before), AHP (1-9 scale, up
-                               to 8,192 servers) over several;
+                               to 8,192 servers, capacities whose values can be
+                               counted in LDS: up to 41,000, more on fewer
+                               servers) over several;
                                serving from k = 32 on: one workgroup per pod.
                                1 = one workgroup per TOPSIS step (plain AHP: one
                                launch per stage), 2 = TOPSIS on one workgroup per

@@ -10,9 +10,9 @@
 //     one column their entries take one or two neighbouring levels of the
 //     scale, so an entry is one compare and one select instead of the 18
 //     instructions of the mapping.
-// At 27,648 servers and five criteria the pairwise passes took 1.7 ms per
+// At 27,648 servers and five criteria the pairwise passes took 3.4 ms per
 // step that scored, bound by VALU issue; a queue of three requests went from
-// 181 to 10.8 ms.  What bounds it now is still VALU issue in k_ahp_rows: three
+// 181 to 10.9 ms.  What bounds it now is still VALU issue in k_ahp_rows: three
 // instructions per distinct value and column, and some ninety per column.
 #pragma once
 #include "dc_queue.hpp"

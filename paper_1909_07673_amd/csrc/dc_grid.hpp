@@ -16,7 +16,11 @@ namespace dcs {
 // Threads per pod workgroup.  The step is bound by memory latency and the
 // waits between workgroups: a session of 300 requests at k = 48 (576 servers a
 // pod) took 62.6 ms with 256 threads, 60.3 with 512, 65.8 with 576 and 84.7
-// with 1,024, where registers spill.
+// with 1,024, where registers spill.  In smaller pods the fewer waves of 256
+// threads meet sooner: a queue of 100 requests took 14.3 ms with 256 and 15.0
+// with 512 at k = 22 (121 servers a pod), 15.1 and 15.8 at k = 32, 17.6 and
+// 17.7 at k = 40, 17.7 and 17.3 at k = 48, 22.2 and 21.1 at k = 56.  One size
+// serves them all so far.
 constexpr int kGridBlock = 512;
 
 // Cross-workgroup state, in device memory.

@@ -1,7 +1,10 @@
 // libdcsched host runtime: the C ABI of include/dcsched.h over the kernels of
-// dc_kernels.hpp.  Owns the device-resident data-center state, uploads
-// request batches, drives the plain (one launch per container step) and
-// batched (one persistent launch) forms, and collects results.
+// dc_kernels.hpp, dc_grid.hpp, dc_queue.hpp, dc_ahp_large.hpp, dc_serve.hpp
+// and dc_tiles.hpp.  Owns the device-resident data-center state, uploads
+// request batches, drives the plain (a queue in one launch, or one launch per
+// step or stage), batched (one persistent launch over all instances) and
+// serving (one persistent launch fed through a ring) forms, and collects
+// results.
 #include "../../include/dcsched.h"
 #include "dc_kernels.hpp"
 #include "dc_grid.hpp"
@@ -619,8 +622,9 @@ F by_case(const dc_ctx *ctx, int K, F at_k, F at_list, F any) {
     return specialised(ctx, K) ? at_k : default_criteria(ctx) ? at_list : any;
 }
 
-// The cooperative kernels compiled for k = 48 (the large data center of the
-// serving form) on the default criteria, or for any case.
+// The cooperative and queue kernels compiled for k = 48 (the large data center
+// of the serving form) on the default criteria, or for any case: a queue of
+// 100 requests at k = 48 takes 16.8 ms, 19.1 with the sizes at run time.
 constexpr int kGridK = 48;
 const void *grid_step_kernel(const dc_ctx *ctx) {
     return reinterpret_cast<const void *>(by_case(ctx, kGridK, k_topsis_grid<kGridBlock, kGridK, 4>,
@@ -1002,7 +1006,7 @@ int crit_max(const dc_ctx *ctx, int c) {
 }
 
 // AHP on the 1-9 scale by distinct value, where the counts of a criterion's
-// values fit one workgroup's LDS (capacities up to some 75,000) and a count
+// values fit one workgroup's LDS (capacities up to some 72,300) and a count
 // 16 bits; otherwise the pairwise passes remain.
 int large_init(dc_ctx *ctx) {
     const int N = ctx->N, nc = ctx->m.nc;

@@ -152,8 +152,8 @@ struct AhpGrid {
 };
 
 // Threads per workgroup: 1,024, and 512 up to 4,096 servers (at most eight
-// servers a thread): 24 arrivals at k = 20 took 1.72 ms with 1,024, 1.59 with
-// 512, 1.68 with 256, the scans and barriers of the larger ones against the
+// servers a thread): 24 arrivals at k = 20 took 2.20 ms with 1,024, 2.07 with
+// 512, 2.22 with 256, the scans and barriers of the larger ones against the
 // column sums of the smaller.
 constexpr int kAhpQueueBlock = 1024;
 constexpr int kAhpPerThread = kAhpSortMax / kAhpQueueBlock;
