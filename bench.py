@@ -330,10 +330,10 @@ TILE_T, TILE_C, TILE_N = 32768, 4, 1024
 # (their SHA-256); reported as null otherwise.
 TILE_TRAFFIC = {
     "sources": ('paper_1909_07673_amd/csrc/dc_tiles.hpp', 'paper_1909_07673_amd/csrc/dc_step.hpp'),
-    "sha256": "7f40e27858c634f483e1c549eac37205c1597e55ba84af80211d89e26e99c67d",
+    "sha256": "9b19efaabaa93562673ea0bcae34de5de28980ac26081c46810b6ad4ce7b7bc3",
     "copy_kib": 524288.0,
-    "fetch_kib": 262221.28, "fetch_copy_kib": 262161.69,
-    "write_kib": 517.75, "write_copy_kib": 524288.0,
+    "fetch_kib": 262221.10, "fetch_copy_kib": 262161.88,
+    "write_kib": 516.88, "write_copy_kib": 524288.0,
 }
 # the batched kernel at the default workload (taken with
 # `bench.py --workload batched --no-extras --no-cpu-baseline --steps 1
@@ -342,10 +342,10 @@ TILE_TRAFFIC = {
 # launch shape (workgroup size, servers per thread, peer chunk) does not change
 BATCHED_TRAFFIC = {
     "sources": ('paper_1909_07673_amd/csrc/dc_kernels.hpp', 'paper_1909_07673_amd/csrc/dc_step.hpp'),
-    "sha256": "b58b057989f0b14d4ab17054baae64a0b8baf872abe75894376e02df82742d70",
+    "sha256": "edc407804bb7b497c30fcd2859bb9743ce23b319db9a92637384b729e7b70beb",
     "copy_kib": 524288.0,
-    "fetch_kib": 119034.38, "fetch_copy_kib": 262162.06,
-    "write_kib": 39380.88, "write_copy_kib": 524288.0,
+    "fetch_kib": 119039.00, "fetch_copy_kib": 262162.19,
+    "write_kib": 39380.94, "write_copy_kib": 524288.0,
 }
 
 
