@@ -288,9 +288,9 @@ typedef struct dc_tune {
  * built (block, host_group) pair -- (256|512, 1|2|4) and (1024, 1|2) --
  * with the largest peer chunk the workgroup's LDS holds, 32 and 16; plain
  * form: blocks 256, 512, 1024 (not above the server count) with their fixed
- * grouping (a queue in one launch over several workgroups has a block size of
- * its own: there the launch-by-launch form is tuned, which runs when those
- * workgroups cannot meet).  cache_path (nullable): a text file of JSON objects, one per
+ * grouping (a queue in one launch over several workgroups, and the cooperative
+ * step of grid = 2, have a block size of their own: there the form over one
+ * workgroup is tuned, which a queue takes when its workgroups cannot meet).  cache_path (nullable): a text file of JSON objects, one per
  * line, keyed by device architecture, form, method, server count and
  * criterion count; a shape found there for this context is taken without
  * timing, and a measured one is written there (a file that cannot be

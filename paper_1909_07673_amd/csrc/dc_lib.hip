@@ -2168,18 +2168,22 @@ int dc_autotune_cached(dc_ctx *ctx, const char *cache_path, dc_tune *out) {
     struct Restore {
         dc_ctx *c;
         int stride, plain_bs, queue;
+        bool use_grid;
         int *saved = nullptr;
         ~Restore() {
             c->cfg.trace_stride = stride;
             c->plain_bs = plain_bs;
             c->queue = queue;
+            c->use_grid = use_grid;
             if (saved) (void)hipFree(saved);
         }
-    } guard{ctx, ctx->cfg.trace_stride, ctx->plain_bs, ctx->queue};
+    } guard{ctx, ctx->cfg.trace_stride, ctx->plain_bs, ctx->queue, ctx->use_grid};
     ctx->cfg.trace_stride = 0;
-    // a queue kernel has its own block size: what is tuned, and later used
-    // where its workgroups cannot meet, is the launch-by-launch form
+    // the queue kernels and the cooperative step have their own block size:
+    // what is tuned is the form that has one (and runs where a queue's
+    // workgroups cannot meet), so that a cache entry always speaks of it
     ctx->queue = dc_ctx::QUEUE_NONE;
+    ctx->use_grid = false;
     const size_t sbytes = (size_t)ctx->I * 6 * ctx->N * sizeof(int);
     HIPCHK(hipMalloc(&guard.saved, sbytes));
     HIPCHK(hipMemcpyAsync(guard.saved, ctx->d_state, sbytes, hipMemcpyDeviceToDevice, ctx->stream));

@@ -336,3 +336,18 @@ def test_autotune_times_the_launches_a_block_size_governs(k, method):
     s.schedule_array()
     assert s.last_timing()[1] == 1                        # the queue itself as before
     s.close()
+
+
+def test_autotune_of_a_cooperative_context():
+    """The cooperative step has a block size of its own: what is timed is the
+    form over one workgroup (one launch per pass: three sizes, twice each),
+    whose entry other contexts of the size read from a cache."""
+    inst, reqs = _queue(16, 2, 6, 4, seed=23)
+    s = dc.Scheduler([inst], grid=2)
+    for r in reqs:
+        s.submit(r)
+    t = s.autotune_cached()
+    assert t["candidates"] == 3 and s.last_timing()[1] == 6
+    s.schedule_array()
+    assert s.last_timing()[1] >= sum(len(r.cpu) for r in reqs)        # its own launches as before
+    s.close()
